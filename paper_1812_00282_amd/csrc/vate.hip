@@ -218,9 +218,8 @@ __global__ void __launch_bounds__(256) k_init(Geo G, uint4 *__restrict__ pool4, 
 // 16-byte loads, so a wavefront reads 2 x 1 KiB contiguous), hashes them in
 // registers and stores the block ACT into the AT (SetAT).  Concurrent SetATs
 // of one AT in a slice all write the same value, so plain byte/short stores
-// are race-free; 4-bit ATs share a 32-bit word with a neighbour and are
-// written with an atomic OR of the set bits then an atomic AND of the clear
-// bits, which leaves the nibble equal to ACT whatever the interleaving.
+// are race-free; 4-bit ATs share a 32-bit word with their neighbours and are
+// set like exact-width counters (set_bits).
 // ---------------------------------------------------------------------------
 template <int W>
 __device__ __forceinline__ void set_at(uint8_t *__restrict__ pool, uint32_t pid, uint32_t act)
@@ -230,19 +229,37 @@ __device__ __forceinline__ void set_at(uint8_t *__restrict__ pool, uint32_t pid,
     } else if constexpr (W == 16) {
         reinterpret_cast<uint16_t *>(pool)[pid] = (uint16_t)act;
     } else {
-        uint32_t *w32 = reinterpret_cast<uint32_t *>(pool) + (pid >> 3);
-        uint32_t s = (pid & 7u) << 2;
-        atomicOr(w32, act << s);
-        atomicAnd(w32, ~((~act & 0xFu) << s));
+        const uint32_t s = (pid & 7u) << 2;
+        set_bits(reinterpret_cast<uint32_t *>(pool) + (pid >> 3), 0xFu << s, act << s);
     }
 }
 
+// A workgroup's filter of counters it has set already (widths set by
+// compare-and-swap): slot s holds the last pid with pid mod kSeen == s.  A few
+// hosts send most packets (Zipf), and swaps on one address take about 12 ns
+// each one after the other, whoever sends them: 1M packets of 1M Zipf(1.1)
+// hosts took 2.8 ms with every packet going to its word.  The exchange is an
+// LDS atomic, so of the lanes that bring one pid together only one finds
+// another pid in the slot and sets the counter.
+constexpr uint32_t kSeen = 2048;
+
+__device__ __forceinline__ void seen_clear(uint32_t *seen)
+{
+    for (uint32_t q = threadIdx.x; q < kSeen; q += blockDim.x) seen[q] = q ^ 1u;   // no pid of slot q
+}
+
+template <int W>
+constexpr bool kUsesSeen = W == 0 || W == 4;
+
 template <int W>
 __device__ __forceinline__ void ingest_one(const Geo &G, uint8_t *__restrict__ pool, uint32_t bact0,
-                                           uint32_t aip, uint32_t bip)
+                                           uint32_t aip, uint32_t bip, uint32_t *seen)
 {
     uint32_t vid = bh(G, bip);
     uint32_t pid = vat_pid(G, host_key(G, aip), vid);
+    if constexpr (kUsesSeen<W>) {
+        if (atomicExch(&seen[pid & (kSeen - 1u)], pid) == pid) return;
+    }
     // SetAT stores the block's ACT; a DR is reset to 0
     uint32_t val = G.dr ? 0u : block_act(G, bact0, block_of(G, pid));
     if constexpr (W == 0)
@@ -255,19 +272,25 @@ template <int W, bool ALIGNED16>
 __global__ void __launch_bounds__(256) k_ingest(Geo G, const uint32_t *__restrict__ pairs, uint64_t n,
                                                 uint8_t *__restrict__ pool, const DevState *__restrict__ st)
 {
+    __shared__ uint32_t seen[kUsesSeen<W> ? kSeen : 1];
+    if constexpr (kUsesSeen<W>) {
+        seen_clear(seen);
+        __syncthreads();
+    }
     const uint32_t bact0 = st->bact0;
-    const uint64_t base = (uint64_t)blockIdx.x * 1024;   // packets per block
+    for (uint64_t base = (uint64_t)blockIdx.x * 1024; base < n; base += (uint64_t)gridDim.x * 1024) {
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        const uint64_t j = base + (uint64_t)half * 512 + 2ull * threadIdx.x;   // first of 2 packets
-        if (ALIGNED16 && j + 2 <= n) {
-            uint4 v = reinterpret_cast<const uint4 *>(pairs)[j >> 1];
-            ingest_one<W>(G, pool, bact0, v.x, v.y);
-            ingest_one<W>(G, pool, bact0, v.z, v.w);
-        } else {
-            for (uint64_t q = j; q < j + 2 && q < n; ++q) {
-                uint2 v = reinterpret_cast<const uint2 *>(pairs)[q];
-                ingest_one<W>(G, pool, bact0, v.x, v.y);
+        for (int half = 0; half < 2; ++half) {
+            const uint64_t j = base + (uint64_t)half * 512 + 2ull * threadIdx.x;   // first of 2 packets
+            if (ALIGNED16 && j + 2 <= n) {
+                uint4 v = reinterpret_cast<const uint4 *>(pairs)[j >> 1];
+                ingest_one<W>(G, pool, bact0, v.x, v.y, seen);
+                ingest_one<W>(G, pool, bact0, v.z, v.w, seen);
+            } else {
+                for (uint64_t q = j; q < j + 2 && q < n; ++q) {
+                    uint2 v = reinterpret_cast<const uint2 *>(pairs)[q];
+                    ingest_one<W>(G, pool, bact0, v.x, v.y, seen);
+                }
             }
         }
     }
@@ -1072,7 +1095,9 @@ static void launch_dr_maintain(vate_sketch *s, hipStream_t st)
 template <int W>
 static void launch_ingest(vate_sketch *s, const uint32_t *pairs, uint64_t n, hipStream_t st)
 {
-    unsigned blocks = grid_for(n, 1024, 1u << 30);
+    // Widths with a filter: few enough workgroups that each sees several
+    // thousand packets.  Others: one workgroup per 1024 packets.
+    unsigned blocks = grid_for(n, 1024, kUsesSeen<W> ? 4u * s->n_cu : 1u << 30);
     if ((reinterpret_cast<uintptr_t>(pairs) & 15u) == 0)
         k_ingest<W, true><<<blocks, 256, 0, st>>>(s->G, pairs, n, s->pool, s->st);
     else

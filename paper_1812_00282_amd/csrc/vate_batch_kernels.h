@@ -144,17 +144,21 @@ __global__ void __launch_bounds__(256) k_batch_preserve(const BatchItem *__restr
 }
 
 template <int W>
-__device__ __forceinline__ void batch_ingest_tile(const BatchItem &it, uint64_t p0, uint64_t p1)
+__device__ __forceinline__ void batch_ingest_tile(const BatchItem &it, uint64_t p0, uint64_t p1, uint32_t *seen)
 {
     const uint32_t bact0 = it.st->bact0;
+    if constexpr (kUsesSeen<W>) {      // the filter belongs to one sketch (the tile's)
+        seen_clear(seen);
+        __syncthreads();
+    }
     for (uint64_t j = p0 + 2ull * threadIdx.x; j < p1; j += 2ull * blockDim.x) {
         if (j + 2 <= p1) {
             const uint4 v = *reinterpret_cast<const uint4 *>(it.pairs + 2 * j);
-            ingest_one<W>(it.G, it.pool, bact0, v.x, v.y);
-            ingest_one<W>(it.G, it.pool, bact0, v.z, v.w);
+            ingest_one<W>(it.G, it.pool, bact0, v.x, v.y, seen);
+            ingest_one<W>(it.G, it.pool, bact0, v.z, v.w, seen);
         } else {
             const uint2 v = *reinterpret_cast<const uint2 *>(it.pairs + 2 * j);
-            ingest_one<W>(it.G, it.pool, bact0, v.x, v.y);
+            ingest_one<W>(it.G, it.pool, bact0, v.x, v.y, seen);
         }
     }
 }
@@ -165,6 +169,7 @@ __global__ void __launch_bounds__(256) k_batch_ingest(const BatchItem *__restric
                                                       const unsigned long long *__restrict__ n_pairs, BatchTune tune,
                                                       BatchTables *__restrict__ tab)
 {
+    __shared__ uint32_t seen[kSeen];
     const unsigned long long total = tab->prefix[PH_INGEST][S];
     for (;;) {
         const unsigned long long tile = claim_tile(&tab->claim[PH_INGEST]);
@@ -173,10 +178,10 @@ __global__ void __launch_bounds__(256) k_batch_ingest(const BatchItem *__restric
         const BatchItem &it = items[s];
         const uint64_t p0 = (tile - tab->prefix[PH_INGEST][s]) * tune.ingest_tile;
         const uint64_t p1 = min(p0 + tune.ingest_tile, min((uint64_t)n_pairs[s], it.pairs_cap));
-        if (it.width == 0) batch_ingest_tile<0>(it, p0, p1);
-        else if (it.width == 4) batch_ingest_tile<4>(it, p0, p1);
-        else if (it.width == 8) batch_ingest_tile<8>(it, p0, p1);
-        else batch_ingest_tile<16>(it, p0, p1);
+        if (it.width == 0) batch_ingest_tile<0>(it, p0, p1, seen);
+        else if (it.width == 4) batch_ingest_tile<4>(it, p0, p1, seen);
+        else if (it.width == 8) batch_ingest_tile<8>(it, p0, p1, seen);
+        else batch_ingest_tile<16>(it, p0, p1, seen);
     }
 }
 

@@ -10,10 +10,10 @@
 // thread whole groups: the group's w words are read in order through a
 // 64-bit bit buffer and, where counters change, written back the same way.
 // SetAT writes the w bits of one counter, which may straddle two words, with
-// an atomic OR of its set bits then an atomic AND of its clear bits on each
-// word: every writer of a counter within a slice writes the same value, so
-// the counter ends at that value under any interleaving, and the bits of
-// neighbouring counters are never touched.
+// a compare-and-swap on each word that does not hold them yet: the bits of
+// neighbouring counters are never changed, and every writer of a counter
+// within a slice writes the same value, so the counter ends at that value
+// under any interleaving.
 
 __device__ __forceinline__ uint32_t low_mask(uint32_t w) { return w >= 32 ? ~0u : (1u << w) - 1u; }
 
@@ -28,6 +28,24 @@ __device__ __forceinline__ uint32_t load_x(const uint32_t *__restrict__ words, u
     return v & low_mask(wb);
 }
 
+// SetAT on the bits that one 32-bit word holds of a counter (mask m, value v
+// in place).  Every writer of a slice writes the same value, so a word whose
+// bits already equal it needs no write: the word is read first (a load that
+// passes L1 by, so that a hot counter set by another CU is seen as set; a
+// stale word only costs a needless exchange), and one compare-and-swap then
+// sets it.  A failed swap returns the word as another writer left it; a
+// counter changes once per slice, so at most as many swaps fail as the word
+// holds counters.
+__device__ __forceinline__ void set_bits(uint32_t *__restrict__ p, uint32_t m, uint32_t v)
+{
+    uint32_t old = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while ((old & m) != v) {
+        const uint32_t got = atomicCAS(p, old, (old & ~m) | v);
+        if (got == old) break;
+        old = got;
+    }
+}
+
 __device__ __forceinline__ void set_x(uint32_t *__restrict__ words, uint64_t pid, uint32_t wb, uint32_t val)
 {
     const uint64_t o = pid * wb;
@@ -35,13 +53,8 @@ __device__ __forceinline__ void set_x(uint32_t *__restrict__ words, uint64_t pid
     const uint32_t sh = (uint32_t)o & 31u;
     const uint32_t n0 = min(wb, 32u - sh);             // bits in the first word
     const uint32_t m0 = low_mask(n0);
-    atomicOr(p, (val & m0) << sh);
-    atomicAnd(p, ~((~val & m0) << sh));
-    if (n0 < wb) {
-        const uint32_t m1 = low_mask(wb - n0), hi = val >> n0;
-        atomicOr(p + 1, hi & m1);
-        atomicAnd(p + 1, ~(~hi & m1));
-    }
+    set_bits(p, m0 << sh, (val & m0) << sh);
+    if (n0 < wb) set_bits(p + 1, low_mask(wb - n0), val >> n0);
 }
 
 // The 32 counters of group gi (its wb words in order).
