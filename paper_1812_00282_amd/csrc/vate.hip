@@ -47,8 +47,8 @@ __host__ __device__ __forceinline__ const unsigned long long *census_of(const De
 {
     return reinterpret_cast<const unsigned long long *>(st + 1);
 }
-constexpr int kMaxHistK = 256;
-constexpr uint32_t kCensusLdsBins = 4096;   // census histogram bins kept in LDS      // per-host histogram limit (LDS budget)
+constexpr int kMaxHistK = 256;              // largest k of the direct gather's histograms
+constexpr uint32_t kCensusLdsBins = 4096;   // census histogram bins kept in LDS
 
 // State block layout: header, k census counters, then (256-byte aligned) the
 // activity bitmap of N bits.
@@ -604,13 +604,11 @@ __global__ void __launch_bounds__(256) k_census_fold(Geo G, DevState *__restrict
 }
 
 // ---------------------------------------------------------------------------
-// k_estimate: one thread per host.  The g VATs of the host are gathered in
-// batches of U independent byte loads (U gathers of 64 random lines in flight
-// per wavefront), decoded with CheckAT (Alg. 1), counted, and the estimate
-// of Eq. 11 is formed in FP32 from exact integer counts.  With HIST each
-// lane also keeps the host's distance histogram in LDS as pairs of 16-bit
-// counters in lane-private columns (conflict-free increments), written out
-// transposed so that the (hosts x (k+1)) output is stored contiguously.
+// k_estimate: the closed form by a direct gather, L lanes per host.  The g
+// VATs of a host are gathered in batches of U independent byte loads per lane,
+// decoded with CheckAT (Alg. 1), counted and summed over the host's lanes, and
+// the estimate of Eq. 11 is formed in FP32 from exact integer counts.  (With
+// the distance histogram: k_gather.)
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float estimate_from_counts(uint64_t u_v, uint64_t u_p, uint32_t g, uint32_t c)
 {
@@ -636,76 +634,68 @@ __device__ __forceinline__ uint64_t pool_active(const DevState *__restrict__ st,
     return s;
 }
 
-constexpr int kEstU = 16;   // VAT gathers in flight per thread
+// VATs sub, sub + L, ... of one host that are active for k', by U gathers in
+// flight.  The activity bitmap answers CheckAT(., k) directly; the AT value
+// (for its distance) is only read for VATs that are active at all, and only
+// when a shorter window needs it, again with all of a batch in flight.
+template <int W, int L, int U>
+__device__ __forceinline__ uint32_t lane_live(const Geo &G, const uint8_t *__restrict__ pool,
+                                              const uint8_t *__restrict__ bitmap, uint32_t kprime, uint32_t key,
+                                              bool valid, uint32_t bact0, uint32_t sub)
+{
+    const bool need_dist = kprime < G.k;
+    uint32_t live = 0;
+    for (uint32_t i0 = sub; i0 < G.g; i0 += L * U) {
+        uint32_t pid[U], byte[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) pid[u] = vat_pid(G, key, i0 + u * L);
+#pragma unroll
+        for (int u = 0; u < U; ++u) byte[u] = (valid && i0 + u * L < G.g) ? bitmap[pid[u] >> 3] : 0u;
+        if (!need_dist) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) live += (byte[u] >> (pid[u] & 7u)) & 1u;
+            continue;
+        }
+        uint32_t val[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            byte[u] = (byte[u] >> (pid[u] & 7u)) & 1u;
+            val[u] = byte[u] ? load_at<W>(pool, pid[u], G.wb) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (byte[u] && value_dist(G, bact0, pid[u], val[u]) < kprime) ++live;
+    }
+    return live;
+}
 
-template <int W, bool HIST>
+template <int L>
+__device__ __forceinline__ uint32_t sum_lanes(uint32_t x)
+{
+#pragma unroll
+    for (int off = 1; off < L; off <<= 1) x += __shfl_xor(x, off, 64);
+    return x;
+}
+
+template <int W, int L, int U>
 __global__ void __launch_bounds__(256) k_estimate(Geo G, const uint8_t *__restrict__ pool,
                                                   const DevState *__restrict__ st,
                                                   const uint8_t *__restrict__ bitmap,
                                                   const uint32_t *__restrict__ hosts, uint32_t n,
                                                   uint32_t kprime, float *__restrict__ est,
-                                                  uint32_t *__restrict__ live_out,
-                                                  uint32_t *__restrict__ hist_out)
+                                                  uint32_t *__restrict__ live_out)
 {
-    extern __shared__ uint32_t lds_hist[];   // HIST: [waves][rows + 1][65]
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const uint32_t rows = (G.k + 1) / 2;     // bins d and d^1 share a dword
-    uint32_t *my = lds_hist + (size_t)wave * (rows + 1) * 65;
-    if (HIST) {
-        for (uint32_t r = 0; r < rows; ++r) my[r * 65 + lane] = 0;
-    }
-    const uint64_t active_pool = pool_active(st, kprime);
+    const uint32_t sub = threadIdx.x % L;
     const uint32_t bact0 = st->bact0;
-    // The bitmap answers CheckAT(., k) directly; the AT value (for its
-    // distance) is only fetched for VATs that are active at all, and only
-    // when a shorter window or the histogram needs it.
-    const bool need_dist = HIST || kprime < G.k;
-    const uint32_t h = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool valid = h < n;
-    const uint32_t key = host_key(G, valid ? hosts[h] : 0u);
-    uint32_t live = 0, live_k = 0;
-    for (uint32_t i0 = 0; i0 < G.g; i0 += kEstU) {
-        uint32_t pid[kEstU], byte[kEstU];
-#pragma unroll
-        for (int u = 0; u < kEstU; ++u) pid[u] = vat_pid(G, key, i0 + u);
-#pragma unroll
-        for (int u = 0; u < kEstU; ++u)
-            byte[u] = (valid && i0 + u < G.g) ? bitmap[pid[u] >> 3] : 0u;
-#pragma unroll
-        for (int u = 0; u < kEstU; ++u) {
-            if (!((byte[u] >> (pid[u] & 7u)) & 1u)) continue;
-            if (!need_dist) {
-                ++live;
-                continue;
-            }
-            const uint32_t d = value_dist(G, bact0, pid[u], load_at<W>(pool, pid[u], G.wb));
-            live += d < kprime;
-            if (HIST) {
-                ++live_k;
-                atomicAdd(&my[(d >> 1) * 65 + lane], 1u << ((d & 1u) << 4));
-            }
-        }
-    }
-    if (valid) {
-        est[h] = estimate_from_counts(G.g - live, G.N - active_pool, G.g, G.c);
-        if (live_out) live_out[h] = live;
-    }
-    if (HIST) {
-        my[rows * 65 + lane] = live_k;
-        __syncthreads();
-        const uint32_t h0 = blockIdx.x * blockDim.x + wave * 64;
-        if (h0 < n) {
-            const uint32_t nh = min(64u, n - h0), kp1 = G.k + 1;
-            uint32_t *out = hist_out + (size_t)h0 * kp1;
-            for (uint32_t e = lane; e < nh * kp1; e += 64) {
-                const uint32_t host = e / kp1, bin = e - host * kp1;
-                uint32_t v;
-                if (bin < G.k)
-                    v = (my[(bin >> 1) * 65 + host] >> ((bin & 1u) << 4)) & 0xFFFFu;
-                else
-                    v = G.g - my[rows * 65 + host];
-                out[e] = v;
-            }
+    const uint64_t active_pool = pool_active(st, kprime);
+    for (uint64_t h0 = (uint64_t)blockIdx.x * (256 / L); h0 < n; h0 += (uint64_t)gridDim.x * (256 / L)) {
+        const uint64_t h = h0 + threadIdx.x / L;
+        const bool valid = h < n;
+        const uint32_t key = host_key(G, valid ? hosts[h] : 0u);
+        const uint32_t live = sum_lanes<L>(lane_live<W, L, U>(G, pool, bitmap, kprime, key, valid, bact0, sub));
+        if (valid && sub == 0) {
+            est[h] = estimate_from_counts(G.g - live, G.N - active_pool, G.g, G.c);
+            if (live_out) live_out[h] = live;
         }
     }
 }
@@ -752,118 +742,9 @@ __global__ void __launch_bounds__(256) k_estimate_blocked(Geo G, const DevState 
     }
 }
 
-static bool blocked_gather_ok(const Geo &G, uint32_t kprime, const uint32_t *hist)
-{
-    return G.blog >= 5 && kprime == G.k && hist == nullptr;
-}
+static bool blocked_gather_ok(const Geo &G, uint32_t kprime) { return G.blog >= 5 && kprime == G.k; }
 
-// ---------------------------------------------------------------------------
-// k_estimate_learned: the gather of k_estimate (histogram path, window k)
-// followed, in the same workgroup, by the learned estimator on the matrix
-// cores.  Each wavefront's 64 hosts are fed to the network as four 16-row
-// tiles built straight from the LDS histograms; the closed form is kept as
-// the output where the network's result is not finite.
-// ---------------------------------------------------------------------------
 constexpr int kLearnMaxK = VATE_MLP_FEATURES - 3;
-
-template <int W>
-__global__ void __launch_bounds__(256) k_estimate_learned(Geo G, const uint8_t *__restrict__ pool,
-                                                          const DevState *__restrict__ st,
-                                                          const uint8_t *__restrict__ bitmap,
-                                                          const uint32_t *__restrict__ hosts, uint32_t n,
-                                                          const mlp::Packed *__restrict__ P,
-                                                          float *__restrict__ est_out,
-                                                          float *__restrict__ cf_out)
-{
-    constexpr int ROWS = (kLearnMaxK + 1) / 2 + 1;   // packed 16-bit bin pairs + live row
-    __shared__ uint32_t hist_all[4][ROWS * 65];
-    __shared__ __attribute__((aligned(16))) uint16_t xs_all[4][16 * mlp::LDS_STRIDE];
-    __shared__ __attribute__((aligned(16))) uint16_t a1_all[4][16 * mlp::LDS_STRIDE];
-    __shared__ float cf_all[4][64];
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const uint32_t rows = (G.k + 1) / 2;
-    uint32_t *my = hist_all[wave];
-    for (uint32_t r = 0; r < rows; ++r) my[r * 65 + lane] = 0;
-    const uint64_t active_pool = pool_active(st, G.k);
-    const uint32_t bact0 = st->bact0;
-    const uint32_t h = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool valid = h < n;
-    const uint32_t key = host_key(G, valid ? hosts[h] : 0u);
-    uint32_t live = 0;
-    for (uint32_t i0 = 0; i0 < G.g; i0 += kEstU) {
-        uint32_t pid[kEstU], byte[kEstU];
-#pragma unroll
-        for (int u = 0; u < kEstU; ++u) pid[u] = vat_pid(G, key, i0 + u);
-#pragma unroll
-        for (int u = 0; u < kEstU; ++u)
-            byte[u] = (valid && i0 + u < G.g) ? bitmap[pid[u] >> 3] : 0u;
-#pragma unroll
-        for (int u = 0; u < kEstU; ++u) {
-            if (!((byte[u] >> (pid[u] & 7u)) & 1u)) continue;
-            const uint32_t val = load_at<W>(pool, pid[u], G.wb);
-            const uint32_t d = value_dist(G, bact0, pid[u], val);
-            ++live;
-            atomicAdd(&my[(d >> 1) * 65 + lane], 1u << ((d & 1u) << 4));
-        }
-    }
-    const float cf = estimate_from_counts(G.g - live, G.N - active_pool, G.g, G.c);
-    my[rows * 65 + lane] = live;
-    cf_all[wave][lane] = cf;
-    if (valid) cf_out[h] = cf;
-    const float occupancy = (float)active_pool / (float)G.N;
-    const float fg = (float)G.g;
-    const int q = lane >> 4, c = lane & 15;
-    uint16_t *xs = xs_all[wave];
-    __syncthreads();
-    const bool geo_off = mlp::env_geometry_off(P, G.k, G.g, G.c, G.wb);
-    const mlp::EnvRange rng = mlp::env_range(P, (int)lane);   // this lane's feature in every row
-    __shared__ uint32_t fell_wg;      // the workgroup's fallback hosts (one counter atomic per workgroup)
-    if (threadIdx.x == 0) fell_wg = 0;
-    uint32_t fell_wave = 0;
-    for (int t = 0; t < 4; ++t) {
-        // features of hosts 16t .. 16t+15 of this wavefront (row m = host - 16t);
-        // lane f builds feature f of a row, so one ballot per row says whether
-        // the host is outside the network's envelope
-        uint32_t outside = geo_off ? 0xFFFFu : 0u;
-        for (int e = lane; e < 16 * VATE_MLP_FEATURES; e += 64) {
-            const int m = e >> 6, f = e & 63, host = 16 * t + m;
-            float x = 0.f;
-            if (f < (int)G.k)
-                x = (float)((my[(f >> 1) * 65 + host] >> ((f & 1) << 4)) & 0xFFFFu) / fg;
-            else if (f == (int)G.k)
-                x = (float)my[rows * 65 + host] / fg;
-            else if (f == (int)G.k + 1)
-                x = occupancy;
-            else if (f == (int)G.k + 2)
-                x = logf(fmaxf(cf_all[wave][host], 1.0f)) * 0.0625f;
-            const uint16_t xb = mlp::bf16_bits(x);
-            xs[m * mlp::LDS_STRIDE + f] = xb;
-            if (__ballot(mlp::env_outside(rng, xb))) outside |= 1u << m;
-        }
-        __syncthreads();
-        float r4[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) r4[r] = logf(fmaxf(cf_all[wave][16 * t + 4 * q + r], 1.0f));
-        mlp::f32x4 z1[4], z2[4];
-        float a2v[4][4], o4[4];
-        mlp::forward16(P, xs, a1_all[wave], r4, z1, z2, a2v, o4);
-        bool fell = false;
-        if (c < 4) {
-            const int host = 16 * t + 4 * q + c;
-            const uint32_t hg = blockIdx.x * blockDim.x + wave * 64 + host;
-            if (hg < n) {
-                const float e = expf(o4[c]);
-                fell = ((outside >> (4 * q + c)) & 1u) || !isfinite(e);
-                est_out[hg] = fell ? cf_all[wave][host] : e;
-            }
-        }
-        fell_wave += (uint32_t)__popcll(__ballot(fell));
-        __syncthreads();
-    }
-    if (lane == 0 && fell_wave) atomicAdd(&fell_wg, fell_wave);
-    __syncthreads();
-    if (threadIdx.x == 0) mlp::env_count(P, fell_wg);
-}
 
 #include "vate_part.h"
 
@@ -1125,11 +1006,13 @@ static int advance(vate_sketch *s, hipStream_t st)
     return check_launch(s, "advance/preserve");
 }
 
+// The closed form without histograms.  Lanes per host: as many as keep the
+// chip's 2048 threads per CU busy, so that few hosts take few serial rounds.
 template <int W>
 static void launch_estimate(vate_sketch *s, const uint32_t *hosts, uint32_t n, uint32_t kprime, float *est,
-                            uint32_t *live, uint32_t *hist, hipStream_t st)
+                            uint32_t *live, hipStream_t st)
 {
-    if (blocked_gather_ok(s->G, kprime, hist)) {
+    if (blocked_gather_ok(s->G, kprime)) {
         const uint32_t nb = (s->G.g + (1u << s->G.blog) - 1u) >> s->G.blog;
         uint32_t lg = 0;
         while ((1u << lg) < nb && lg < 6) ++lg;
@@ -1137,25 +1020,56 @@ static void launch_estimate(vate_sketch *s, const uint32_t *hosts, uint32_t n, u
             s->G, s->st, reinterpret_cast<const uint32_t *>(s->bitmap), hosts, n, lg, est, live);
         return;
     }
-    if (hist) {
-        const uint32_t k = s->G.k;
-        const unsigned threads = k <= 64 ? 256 : k <= 128 ? 128 : 64;
-        const size_t lds = (size_t)(threads / 64) * ((k + 1) / 2 + 1) * 65 * sizeof(uint32_t);
-        k_estimate<W, true><<<grid_for(n, threads, 1u << 30), threads, lds, st>>>(s->G, s->pool, s->st, s->bitmap,
-                                                                                  hosts, n, kprime, est, live,
-                                                                                  hist);
-    } else {
-        k_estimate<W, false><<<grid_for(n, 256, 1u << 30), 256, 0, st>>>(s->G, s->pool, s->st, s->bitmap,
-                                                                         hosts, n, kprime, est, live, nullptr);
-    }
+    const uint64_t lanes = (uint64_t)s->n_cu * 2048u / n;       // lanes a host may take (n >= 1)
+    const unsigned cap = 16u * s->n_cu;
+    auto go = [&](auto L, auto U) {
+        constexpr int l = decltype(L)::value, u = decltype(U)::value;
+        k_estimate<W, l, u><<<grid_for(n, 256 / l, cap), 256, 0, st>>>(s->G, s->pool, s->st, s->bitmap, hosts, n,
+                                                                       kprime, est, live);
+    };
+    using std::integral_constant;
+    if (lanes >= 64 && s->G.g <= 256) go(integral_constant<int, 64>{}, integral_constant<int, 4>{});
+    else if (lanes >= 64) go(integral_constant<int, 64>{}, integral_constant<int, 16>{});
+    else if (lanes >= 16 || s->G.g >= 256) go(integral_constant<int, 16>{}, integral_constant<int, 16>{});
+    else go(integral_constant<int, 4>{}, integral_constant<int, 16>{});
 }
 
-template <int W>
-static void launch_estimate_learned(vate_sketch *s, const uint32_t *hosts, uint32_t n, const void *weights,
-                                    float *est, float *cf, hipStream_t st)
+// The direct gather with per-host distance histograms (MODE as in
+// finish_hosts).  Hosts per workgroup: 1 while the chip has room for a
+// workgroup per host, up to 16 (the network's tile).
+template <int W, int MODE>
+static void launch_gather(vate_sketch *s, const uint32_t *hosts, uint32_t n, uint32_t kprime, float *est,
+                          uint32_t *live, uint32_t *hist, const Windows &win, const void *weights, float *cf,
+                          hipStream_t st)
 {
-    k_estimate_learned<W><<<grid_for(n, 256, 1u << 30), 256, 0, st>>>(
-        s->G, s->pool, s->st, s->bitmap, hosts, n, static_cast<const mlp::Packed *>(weights), est, cf);
+    uint32_t lg = 0;
+    while (lg < 4 && ((uint64_t)n >> lg) > 8u * s->n_cu) ++lg;
+    const uint32_t rowp = hist_row_words(s->G.k);
+    k_gather<W, MODE><<<(unsigned)(((uint64_t)n + (1u << lg) - 1) >> lg), kFinThreads, (rowp * 4u) << lg, st>>>(
+        s->G, s->pool, s->st, s->bitmap, hosts, n, lg, rowp, kprime, est, live, hist, win,
+        static_cast<const mlp::Packed *>(weights), cf);
+}
+
+// vate_estimate's gather, with or without histograms.
+static void direct_estimate(vate_sketch *s, const uint32_t *hosts, uint32_t n, uint32_t kprime, float *est,
+                            uint32_t *live, uint32_t *hist, hipStream_t st)
+{
+    by_width(s->p.width, [&](auto W) {
+        constexpr int w = decltype(W)::value;
+        if (hist)
+            launch_gather<w, kFinClosedForm>(s, hosts, n, kprime, est, live, hist, Windows{}, nullptr, nullptr, st);
+        else
+            launch_estimate<w>(s, hosts, n, kprime, est, live, st);
+    });
+}
+
+static void direct_learned(vate_sketch *s, const uint32_t *hosts, uint32_t n, const void *weights, float *est,
+                           float *cf, hipStream_t st)
+{
+    by_width(s->p.width, [&](auto W) {
+        launch_gather<decltype(W)::value, kFinLearned>(s, hosts, n, s->p.k, est, nullptr, nullptr, Windows{}, weights,
+                                                       cf, st);
+    });
 }
 
 // ---- partitioned estimate: geometry, workspace layout and launches ----
@@ -1174,9 +1088,7 @@ static bool part_geo(const vate_sketch *s, uint64_t n, PartGeo *out)
     p.n_slices = (uint32_t)ns;
     p.bm_words = sl >= 5 ? 1u << (sl - 5) : 1u;
     p.xcd = ns >= 8 ? 1u : 0u;
-    // Histogram rows of ceil((k+1)/2) words, made odd: an odd stride puts
-    // the bins of different hosts in different LDS banks.
-    p.rowp = ((G.k + 2u) / 2u) | 1u;
+    p.rowp = hist_row_words(G.k);
     // Hosts per subgroup: the largest count whose VATs' pids fit the scatter
     // threads' registers (kRunPerThread each), whose padded sort of 32-bit
     // entries (+ slice counters, keys) fits its LDS, and whose histograms fit
@@ -1313,9 +1225,8 @@ static int launch_part(vate_sketch *s, const PartGeo &pg, void *ws, const uint32
     k_run_lookup<W><<<pg.n_slices * pg.split, kRunThreads, pg.lds_lookup, st>>>(
         s->G, pg, s->pool, reinterpret_cast<const uint32_t *>(s->bitmap), s->st, w.entries, w.table, w.hits,
         w.heads);
-    if (MODE == kFinMulti) k_census_prefix<<<1, 64, 0, st>>>(s->G, s->st, w.cum);
     k_run_finalize<MODE><<<(pg.n_sub + pg.fgroup - 1) / pg.fgroup, kFinThreads, pg.lds_final, st>>>(
-        s->G, pg, s->st, n, kprime, w.hits, w.heads, w.table, est, live, hist, win, w.cum,
+        s->G, pg, s->st, n, kprime, w.hits, w.heads, w.table, est, live, hist, win,
         static_cast<const mlp::Packed *>(weights), cf);
     return VATE_OK;
 }
@@ -1450,9 +1361,7 @@ int vate_estimate(vate_sketch *s, const uint32_t *hosts_dev, size_t n_hosts, uin
         return fail(s, VATE_E_INVAL, "hosts/est/live/hist must be non-NULL (live, hist may be NULL) and 4-byte aligned");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const uint32_t n = (uint32_t)n_hosts;
-    by_width(s->p.width, [&](auto W) {
-        launch_estimate<decltype(W)::value>(s, hosts_dev, n, kprime, est_dev, live_dev, hist_dev, st);
-    });
+    direct_estimate(s, hosts_dev, n, kprime, est_dev, live_dev, hist_dev, st);
     return check_launch(s, "estimate");
 }
 
@@ -1491,9 +1400,7 @@ static int estimate_ws_impl(vate_sketch *s, const uint32_t *hosts_dev, size_t n_
     if (!part_geo(s, n, &pg)) {      // outside the partitioned limits: direct gather
         if (hist_dev && s->p.k > (uint32_t)kMaxHistK)
             return fail(s, VATE_E_UNSUPPORTED, "per-host histogram of this geometry needs k <= 256");
-        by_width(s->p.width, [&](auto W) {
-            launch_estimate<decltype(W)::value>(s, hosts_dev, n, kprime, est_dev, live_dev, hist_dev, st);
-        });
+        direct_estimate(s, hosts_dev, n, kprime, est_dev, live_dev, hist_dev, st);
         return check_launch(s, what);
     }
     const int rc = launch_part_w<kFinClosedForm>(s, pg, workspace_dev, hosts_dev, n, kprime, est_dev, live_dev,
@@ -1661,9 +1568,7 @@ int vate_estimate_learned_ws(vate_sketch *s, const uint32_t *hosts_dev, size_t n
     const uint32_t n = (uint32_t)n_hosts;
     PartGeo pg;
     if (!part_geo(s, n, &pg)) {      // outside the partitioned limits: fused direct gather
-        by_width(s->p.width, [&](auto W) {
-            launch_estimate_learned<decltype(W)::value>(s, hosts_dev, n, weights_dev, est_dev, est_cf_dev, st);
-        });
+        direct_learned(s, hosts_dev, n, weights_dev, est_dev, est_cf_dev, st);
         return check_launch(s, "estimate_learned_ws");
     }
     const int rc = launch_part_w<kFinLearned>(s, pg, workspace_dev, hosts_dev, n, s->p.k, est_dev, nullptr, nullptr,
@@ -1718,15 +1623,10 @@ int vate_estimate_multi_ws(vate_sketch *s, const uint32_t *hosts_dev, size_t n_h
     }
     if (s->p.k > (uint32_t)kMaxHistK)
         return fail(s, VATE_E_UNSUPPORTED, "several windows for this geometry need k <= 256");
-    uint8_t *ws = static_cast<uint8_t *>(workspace_dev);
-    uint32_t *hist = reinterpret_cast<uint32_t *>(ws);
-    unsigned long long *cum = reinterpret_cast<unsigned long long *>(ws + align256((size_t)n * (s->p.k + 1) * 4));
-    // the direct gather for window k fills the per-host histograms (est is scratch here)
     by_width(s->p.width, [&](auto W) {
-        launch_estimate<decltype(W)::value>(s, hosts_dev, n, s->p.k, est_dev, nullptr, hist, st);
+        launch_gather<decltype(W)::value, kFinMulti>(s, hosts_dev, n, s->p.k, est_dev, nullptr, nullptr, win, nullptr,
+                                                     nullptr, st);
     });
-    k_census_prefix<<<1, 64, 0, st>>>(s->G, s->st, cum);
-    k_multi_from_hist<<<grid_for(n, 256, 1u << 30), 256, 0, st>>>(s->G, n, win, cum, hist, est_dev);
     return check_launch(s, "estimate_multi_ws");
 }
 
@@ -1754,9 +1654,7 @@ int vate_estimate_learned(vate_sketch *s, const uint32_t *hosts_dev, size_t n_ho
         return fail(s, VATE_E_INVAL, "hosts/est/est_cf must be 4-byte and weights 256-byte aligned, non-NULL");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const uint32_t n = (uint32_t)n_hosts;
-    by_width(s->p.width, [&](auto W) {
-        launch_estimate_learned<decltype(W)::value>(s, hosts_dev, n, weights_dev, est_dev, est_cf_dev, st);
-    });
+    direct_learned(s, hosts_dev, n, weights_dev, est_dev, est_cf_dev, st);
     return check_launch(s, "estimate_learned");
 }
 

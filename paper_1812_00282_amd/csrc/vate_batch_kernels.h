@@ -250,36 +250,13 @@ __global__ void __launch_bounds__(256) k_batch_census(const BatchItem *__restric
     }
 }
 
-// Live VATs of one host counted by L lanes: lane `sub` of the host's L takes
-// VATs sub, sub + L, ... (kEstU gathers in flight), and the L partial counts
-// are summed across the lanes (every lane of the wavefront takes part).
+// Live VATs of one host counted by L lanes (every lane of the wavefront takes
+// part in their sum).
 template <int W, int L>
 __device__ __forceinline__ uint32_t batch_host_live(const BatchItem &it, uint32_t key, bool valid, uint32_t bact0,
                                                     uint32_t sub)
 {
-    const Geo &G = it.G;
-    const bool need_dist = it.kprime < G.k;
-    uint32_t live = 0;
-    for (uint32_t i0 = sub; i0 < G.g; i0 += L * kEstU) {
-        uint32_t pid[kEstU], byte[kEstU];
-#pragma unroll
-        for (int u = 0; u < kEstU; ++u) pid[u] = vat_pid(G, key, i0 + u * L);
-#pragma unroll
-        for (int u = 0; u < kEstU; ++u) byte[u] = (valid && i0 + u * L < G.g) ? it.bitmap[pid[u] >> 3] : 0u;
-#pragma unroll
-        for (int u = 0; u < kEstU; ++u) {
-            if (!((byte[u] >> (pid[u] & 7u)) & 1u)) continue;
-            if (!need_dist) {
-                ++live;
-                continue;
-            }
-            const uint32_t d = value_dist(G, bact0, pid[u], load_at<W>(it.pool, pid[u], it.G.wb));
-            live += d < it.kprime;
-        }
-    }
-#pragma unroll
-    for (int off = 1; off < L; off <<= 1) live += __shfl_xor(live, off, 64);
-    return live;
+    return sum_lanes<L>(lane_live<W, L, 16>(it.G, it.pool, it.bitmap, it.kprime, key, valid, bact0, sub));
 }
 
 template <int L>

@@ -664,6 +664,156 @@ __device__ __forceinline__ uint32_t learned16(const Geo &G, float occupancy, con
     return (uint32_t)__popcll(__ballot(fell));
 }
 
+// The active ATs of the pool for each window, summed from the census by one
+// wavefront (every lane takes part): act[j] = ATs with distance below kp[j].
+__device__ __forceinline__ void window_counts(const Geo &G, const DevState *__restrict__ st, const Windows &win,
+                                              unsigned long long *act)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t last = lane < win.m ? win.kp[lane] - 1u : ~0u;   // the window's last distance
+    unsigned long long before = 0;
+    for (uint32_t base = 0; base < G.k; base += 64) {
+        unsigned long long incl = base + lane < G.k ? census_of(st)[base + lane] : 0ull;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const unsigned long long y = __shfl_up(incl, off, 64);
+            if (lane >= (uint32_t)off) incl += y;
+        }
+        const unsigned long long at = __shfl(incl, (int)(last & 63u), 64);
+        if (last - base < 64u) act[lane] = before + at;
+        before += __shfl(incl, 63, 64);
+    }
+}
+
+// Words of a host's packed 16-bit histogram row (bins 0 .. k): made odd, so
+// that one bin of different hosts lies in different LDS banks.
+__host__ __device__ __forceinline__ uint32_t hist_row_words(uint32_t k) { return ((k + 2u) / 2u) | 1u; }
+
+// The outputs of hosts h0 .. h0 + nh - 1 from their histogram rows in LDS
+// (bins 0 .. k - 1 counted, bin k zero), by a workgroup of kFinThreads: the
+// closed form (and histograms), several windows, or the learned estimate.
+// Four threads share a host's row; a row's 16-bit halves are summed packed,
+// which cannot carry because all bins of a host add up to at most g < 2^16.
+// act: kFinMulti's window counts.  Starts after a barrier.
+template <int MODE>
+__device__ __forceinline__ void finish_hosts(const Geo &G, const DevState *__restrict__ st, uint32_t *hist,
+                                             uint32_t rowp, uint32_t nh, uint32_t h0, uint32_t kprime,
+                                             float *__restrict__ est, uint32_t *__restrict__ live_out,
+                                             uint32_t *__restrict__ hist_out, const Windows &win,
+                                             const unsigned long long *act, const mlp::Packed *__restrict__ P,
+                                             float *__restrict__ cf_out)
+{
+    const uint32_t t = threadIdx.x, hh = t >> 2, qq = t & 3u;
+    // this thread's share of the bins below d of a row, as packed sums, from
+    // word j on; and all four threads' total
+    auto total = [&](uint32_t acc, const uint32_t *row, uint32_t d) -> uint32_t {
+        uint32_t live = (acc & 0xFFFFu) + (acc >> 16);
+        if ((d & 1u) && qq == 0) live += row[d >> 1] & 0xFFFFu;
+        live += __shfl_xor(live, 1, 64);
+        live += __shfl_xor(live, 2, 64);
+        return live;
+    };
+    if constexpr (MODE == kFinClosedForm) {
+        const uint64_t active_pool = pool_active(st, kprime);
+        for (uint32_t base = 0; base < nh; base += kFinThreads / 4) {
+            const bool valid = base + hh < nh;
+            uint32_t *row = hist + (valid ? base + hh : 0u) * rowp;
+            uint32_t acc = 0, j = qq;
+            for (; j < kprime / 2; j += 4) acc += row[j];
+            const uint32_t live = total(acc, row, kprime);
+            if (valid && qq == 0) {
+                est[h0 + base + hh] = estimate_from_counts(G.g - live, G.N - active_pool, G.g, G.c);
+                if (live_out) live_out[h0 + base + hh] = live;
+            }
+            if (hist_out) {      // bin k = g - (bins 0 .. k - 1), for the histogram output only
+                for (; j < G.k / 2; j += 4) acc += row[j];
+                const uint32_t all = total(acc, row, G.k);
+                if (valid && qq == 0) row[G.k >> 1] += (G.g - all) << ((G.k & 1u) << 4);
+            }
+        }
+        if (hist_out) {
+            __syncthreads();
+            const uint32_t kp1 = G.k + 1;
+            uint32_t *out = hist_out + (size_t)h0 * kp1;
+            for (uint32_t q = t; q < nh * kp1; q += kFinThreads) {
+                const uint32_t h = q / kp1, d = q - h * kp1;
+                out[q] = hist_bin(hist + h * rowp, d);
+            }
+        }
+    } else if constexpr (MODE == kFinMulti) {
+        for (uint32_t base = 0; base < nh; base += kFinThreads / 4) {
+            const bool valid = base + hh < nh;
+            const uint32_t *row = hist + (valid ? base + hh : 0u) * rowp;
+            float *e = est + (size_t)(h0 + base + hh) * win.m;
+            uint32_t acc = 0, j = qq;
+            for (uint32_t w0 = 0; w0 < win.m; w0 += 4) {   // four windows, one estimate per thread
+                uint32_t mine = 0;
+                for (uint32_t w = w0; w < min(w0 + 4u, win.m); ++w) {
+                    for (; j < win.kp[w] / 2; j += 4) acc += row[j];
+                    const uint32_t live = total(acc, row, win.kp[w]);
+                    if ((w & 3u) == qq) mine = live;
+                }
+                if (valid && w0 + qq < win.m)
+                    e[w0 + qq] = estimate_from_counts(G.g - mine, G.N - act[w0 + qq], G.g, G.c);
+            }
+        }
+    } else {
+        // Learned estimate, in groups of 64 hosts (16 per wavefront): the
+        // closed form for window k, then the network fed from the LDS rows.
+        // One 16-row staging tile per wavefront holds its features and then
+        // its first layer's activations: the layer's inputs are in registers
+        // (its products depend on them) before its outputs are written.
+        __shared__ __attribute__((aligned(16))) uint16_t xs_all[kFinThreads / 64][16 * mlp::LDS_STRIDE];
+        __shared__ float cf_s[kFinThreads / 4];
+        __shared__ uint32_t live_s[kFinThreads / 4];
+        const uint64_t active_pool = pool_active(st, G.k);
+        const float occupancy = (float)active_pool / (float)G.N;
+        const uint32_t w = t >> 6;
+        const bool geo_off = mlp::env_geometry_off(P, G.k, G.g, G.c, G.wb);
+        __shared__ uint32_t fell_wg;      // the workgroup's fallback hosts (one counter atomic per workgroup)
+        if (t == 0) fell_wg = 0;
+        __syncthreads();                  // (the loop below synchronizes wavefronts only with themselves)
+        uint32_t fell_wave = 0;
+        for (uint32_t base = 0; base < nh; base += kFinThreads / 4) {
+            {   // live count and closed form of host base + hh, four threads a host
+                uint32_t live = 0;
+                if (base + hh < nh) {
+                    const uint32_t *row = hist + (base + hh) * rowp;
+                    for (uint32_t j = qq; j < G.k / 2; j += 4) live += (row[j] & 0xFFFFu) + (row[j] >> 16);
+                    if (qq == 0 && (G.k & 1u)) live += row[G.k / 2] & 0xFFFFu;
+                }
+                live += __shfl_xor(live, 1, 64);
+                live += __shfl_xor(live, 2, 64);
+                if (qq == 0) {
+                    float cf = 0.f;
+                    if (base + hh < nh) {
+                        cf = estimate_from_counts(G.g - live, G.N - active_pool, G.g, G.c);
+                        cf_out[h0 + base + hh] = cf;
+                    }
+                    cf_s[hh] = cf;
+                    live_s[hh] = live;
+                }
+            }
+            mlp::wave_sync();   // hosts 16 w .. 16 w + 15 are wavefront w's, here and below
+            const uint32_t m0 = base + 16 * w;
+            const uint32_t n16 = nh > m0 ? min(16u, nh - m0) : 0u;
+            // An opaque zero offset per group, so the weight fragments are
+            // loaded where they are used rather than hoisted out of the loop
+            // into registers (the pointer stays a global one, so the loads
+            // are global loads that wait only on the vector-memory counter).
+            uint32_t zero = 0;
+            asm volatile("" : "+s"(zero));
+            const mlp::Packed *Pg = P + zero;
+            fell_wave += learned16(G, occupancy, hist + m0 * rowp, rowp, n16, cf_s + 16 * w, live_s + 16 * w,
+                                       xs_all[w], xs_all[w], Pg, est + h0 + m0, geo_off);
+            mlp::wave_sync();
+        }
+        if ((t & 63u) == 0 && fell_wave) atomicAdd(&fell_wg, fell_wave);
+        __syncthreads();
+        if (t == 0) mlp::env_count(P, fell_wg);
+    }
+}
+
 // At least 5 wavefronts per SIMD: the network's registers would otherwise
 // hold the streaming pass to 4 (measured 0.64 against 0.58 ms on the 40G
 // workload; 6 would spill).
@@ -677,7 +827,6 @@ __global__ void __launch_bounds__(kFinThreads, 5) k_run_finalize(Geo G, PartGeo 
                                                              const uint32_t *__restrict__ table, float *__restrict__ est,
                                                              uint32_t *__restrict__ live_out,
                                                              uint32_t *__restrict__ hist_out, Windows win,
-                                                             const unsigned long long *__restrict__ cum,
                                                              const mlp::Packed *__restrict__ P,
                                                              float *__restrict__ cf_out)
 {
@@ -690,7 +839,10 @@ __global__ void __launch_bounds__(kFinThreads, 5) k_run_finalize(Geo G, PartGeo 
     const uint32_t nh = min(nsg * PG.hosts, n - h0);
     const uint32_t rowp = PG.rowp;
     const uint32_t ns = PG.n_slices, nr = nsg * ns;
+    __shared__ unsigned long long act[MODE == kFinMulti ? kMaxWindows : 1u];
     for (uint32_t q = t; q < nh * rowp; q += kFinThreads) hist[q] = 0;
+    if constexpr (MODE == kFinMulti)
+        if (t < 64) window_counts(G, st, win, act);
     __syncthreads();
     {
         // Live results (host within its subgroup << 16 | distance) of run r
@@ -744,136 +896,63 @@ __global__ void __launch_bounds__(kFinThreads, 5) k_run_finalize(Geo G, PartGeo 
         }
     }
     __syncthreads();
-    if (MODE == kFinClosedForm && hist_out) {   // only the histogram output has bin k
-        for (uint32_t h = t; h < nh; h += kFinThreads) {   // bin k = g - (bins 0 .. k-1)
-            uint32_t *row = hist + h * rowp;
-            uint32_t live = 0;
-            for (uint32_t j = 0; j < G.k / 2; ++j) live += (row[j] & 0xFFFFu) + (row[j] >> 16);
-            const uint32_t w = G.k >> 1;
-            if (G.k & 1u) {
-                live += row[w] & 0xFFFFu;
-                row[w] = (row[w] & 0xFFFFu) | ((G.g - live) << 16);
-            } else {
-                row[w] = G.g - live;
-            }
-        }
-        __syncthreads();
-    }
-
-    if constexpr (MODE == kFinClosedForm) {
-        const uint64_t active_pool = pool_active(st, kprime);
-        for (uint32_t h = t; h < nh; h += kFinThreads) {
-            const uint32_t *row = hist + h * rowp;
-            uint32_t live = 0;
-            for (uint32_t d = 0; d < kprime; ++d) live += hist_bin(row, d);
-            est[h0 + h] = estimate_from_counts(G.g - live, G.N - active_pool, G.g, G.c);
-            if (live_out) live_out[h0 + h] = live;
-        }
-        if (hist_out) {
-            const uint32_t kp1 = G.k + 1;
-            uint32_t *out = hist_out + (size_t)h0 * kp1;
-            for (uint32_t q = t; q < nh * kp1; q += kFinThreads) {
-                const uint32_t h = q / kp1, d = q - h * kp1;
-                out[q] = hist_bin(hist + h * rowp, d);
-            }
-        }
-    } else if constexpr (MODE == kFinMulti) {
-        for (uint32_t h = t; h < nh; h += kFinThreads) {
-            const uint32_t *row = hist + h * rowp;
-            float *e = est + (size_t)(h0 + h) * win.m;
-            uint32_t live = 0, jw = 0;
-            for (uint32_t d = 0; d < G.k && jw < win.m; ++d) {
-                live += hist_bin(row, d);
-                while (jw < win.m && win.kp[jw] == d + 1) {
-                    e[jw] = estimate_from_counts(G.g - live, G.N - cum[d + 1], G.g, G.c);
-                    ++jw;
-                }
-            }
-        }
-    } else {
-        // Learned estimate, in groups of 64 hosts (16 per wavefront): the
-        // closed form for window k, then the network fed from the LDS rows.
-        // One 16-row staging tile per wavefront holds its features and then
-        // its first layer's activations: the layer's inputs are in registers
-        // (its products depend on them) before its outputs are written.
-        __shared__ __attribute__((aligned(16))) uint16_t xs_all[kFinThreads / 64][16 * mlp::LDS_STRIDE];
-        __shared__ float cf_s[kFinThreads / 4];
-        __shared__ uint32_t live_s[kFinThreads / 4];
-        const uint64_t active_pool = pool_active(st, G.k);
-        const float occupancy = (float)active_pool / (float)G.N;
-        const uint32_t w = t >> 6;
-        const bool geo_off = mlp::env_geometry_off(P, G.k, G.g, G.c, G.wb);
-        __shared__ uint32_t fell_wg;      // the workgroup's fallback hosts (one counter atomic per workgroup)
-        if (t == 0) fell_wg = 0;
-        __syncthreads();                  // (the loop below synchronizes wavefronts only with themselves)
-        uint32_t fell_wave = 0;
-        for (uint32_t base = 0; base < nh; base += kFinThreads / 4) {
-            {   // live count and closed form of host base + t / 4, four threads a host
-                const uint32_t hh = t >> 2, qq = t & 3u;
-                uint32_t live = 0;
-                if (base + hh < nh) {
-                    const uint32_t *row = hist + (base + hh) * rowp;
-                    for (uint32_t j = qq; j < G.k / 2; j += 4) live += (row[j] & 0xFFFFu) + (row[j] >> 16);
-                    if (qq == 0 && (G.k & 1u)) live += row[G.k / 2] & 0xFFFFu;
-                }
-                live += __shfl_xor(live, 1, 64);
-                live += __shfl_xor(live, 2, 64);
-                if (qq == 0) {
-                    float cf = 0.f;
-                    if (base + hh < nh) {
-                        cf = estimate_from_counts(G.g - live, G.N - active_pool, G.g, G.c);
-                        cf_out[h0 + base + hh] = cf;
-                    }
-                    cf_s[hh] = cf;
-                    live_s[hh] = live;
-                }
-            }
-            mlp::wave_sync();   // hosts 16 w .. 16 w + 15 are wavefront w's, here and below
-            const uint32_t m0 = base + 16 * w;
-            const uint32_t n16 = nh > m0 ? min(16u, nh - m0) : 0u;
-            // An opaque zero offset per group, so the weight fragments are
-            // loaded where they are used rather than hoisted out of the loop
-            // into registers (the pointer stays a global one, so the loads
-            // are global loads that wait only on the vector-memory counter).
-            uint32_t zero = 0;
-            asm volatile("" : "+s"(zero));
-            const mlp::Packed *Pg = P + zero;
-            fell_wave += learned16(G, occupancy, hist + m0 * rowp, rowp, n16, cf_s + 16 * w, live_s + 16 * w,
-                                   xs_all[w], xs_all[w], Pg, est + h0 + m0, geo_off);
-            mlp::wave_sync();
-        }
-        if ((t & 63u) == 0 && fell_wave) atomicAdd(&fell_wg, fell_wave);
-        __syncthreads();
-        if (t == 0) mlp::env_count(P, fell_wg);
-    }
+    finish_hosts<MODE>(G, st, hist, rowp, nh, h0, kprime, est, live_out, hist_out, win, act, P, cf_out);
 }
 
-// Per-host windows from full histograms in memory (the fallback when the
-// partitioned lookups are not available for a geometry).
-__global__ void k_multi_from_hist(Geo G, uint32_t n, Windows win, const unsigned long long *__restrict__ cum,
-                                  const uint32_t *__restrict__ hist, float *__restrict__ est)
-{
-    const uint32_t h = blockIdx.x * blockDim.x + threadIdx.x;
-    if (h >= n) return;
-    const uint32_t *row = hist + (size_t)h * (G.k + 1);
-    uint32_t live = 0, j = 0;
-    for (uint32_t d = 0; d < G.k && j < win.m; ++d) {
-        live += row[d];
-        while (j < win.m && win.kp[j] == d + 1) {
-            est[(size_t)h * win.m + j] = estimate_from_counts(G.g - live, G.N - cum[d + 1], G.g, G.c);
-            ++j;
-        }
-    }
-}
+// ---------------------------------------------------------------------------
+// k_gather: the direct gather with a distance histogram per host: 2^lg hosts
+// per workgroup of kFinThreads threads, whose lanes share a host's VATs
+// (kFinThreads >> lg of them, kGatherU gathers in flight per lane, then the
+// values of a batch's active ATs in flight together).  The histograms are
+// counted in LDS rows and finished as in k_run_finalize.  It is bound by the
+// latency of those two gathers while there are few hosts: one host per
+// workgroup then (a wavefront per 64 hosts and a lane per host, as before,
+// took 64 serial rounds of bitmap gathers at g = 1024 and up to 1024 of
+// values: 509 us for 331 hosts on a 2^28 pool).
+// ---------------------------------------------------------------------------
+constexpr uint32_t kGatherU = 8;
 
-__global__ void k_census_prefix(Geo G, const DevState *__restrict__ st, unsigned long long *__restrict__ cum)
+template <int W, int MODE>
+__global__ void __launch_bounds__(kFinThreads) k_gather(Geo G, const uint8_t *__restrict__ pool,
+                                                       const DevState *__restrict__ st,
+                                                       const uint8_t *__restrict__ bitmap,
+                                                       const uint32_t *__restrict__ hosts, uint32_t n, uint32_t lg,
+                                                       uint32_t rowp, uint32_t kprime, float *__restrict__ est,
+                                                       uint32_t *__restrict__ live_out, uint32_t *__restrict__ hist_out,
+                                                       Windows win, const mlp::Packed *__restrict__ P,
+                                                       float *__restrict__ cf_out)
 {
-    if (threadIdx.x == 0) {
-        unsigned long long run = 0;
-        cum[0] = 0;
-        for (uint32_t d = 0; d < G.k; ++d) {
-            run += census_of(st)[d];
-            cum[d + 1] = run;
+    extern __shared__ __attribute__((aligned(16))) uint32_t hist[];   // [2^lg][rowp] packed 16-bit bins
+    __shared__ unsigned long long act[MODE == kFinMulti ? kMaxWindows : 1u];
+    const uint32_t t = threadIdx.x;
+    const uint32_t h0 = blockIdx.x << lg, nh = min(1u << lg, n - h0);
+    for (uint32_t q = t; q < nh * rowp; q += kFinThreads) hist[q] = 0;
+    if constexpr (MODE == kFinMulti)
+        if (t < 64) window_counts(G, st, win, act);
+    const uint32_t lanes = kFinThreads >> lg, sub = t & (lanes - 1u), h = t / lanes;
+    const uint32_t bact0 = st->bact0;
+    const uint32_t key = host_key(G, hosts[h0 + min(h, nh - 1u)]);
+    uint32_t *row = hist + h * rowp;
+    __syncthreads();
+    if (h < nh)
+        for (uint32_t i0 = sub; i0 < G.g; i0 += kGatherU * lanes) {
+            uint32_t pid[kGatherU], bit[kGatherU], val[kGatherU];
+#pragma unroll
+            for (uint32_t u = 0; u < kGatherU; ++u) pid[u] = vat_pid(G, key, i0 + u * lanes);
+#pragma unroll
+            for (uint32_t u = 0; u < kGatherU; ++u) bit[u] = i0 + u * lanes < G.g ? bitmap[pid[u] >> 3] : 0u;
+#pragma unroll
+            for (uint32_t u = 0; u < kGatherU; ++u) {
+                bit[u] = (bit[u] >> (pid[u] & 7u)) & 1u;
+                val[u] = bit[u] ? load_at<W>(pool, pid[u], G.wb) : 0u;
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < kGatherU; ++u)
+                if (bit[u]) {
+                    const uint32_t d = value_dist(G, bact0, pid[u], val[u]);
+                    if (d < G.k) atomicAdd(&row[d >> 1], 1u << ((d & 1u) << 4));
+                }
         }
-    }
+    __syncthreads();
+    finish_hosts<MODE>(G, st, hist, rowp, nh, h0, kprime, est, live_out, hist_out, win, act, P, cf_out);
 }
