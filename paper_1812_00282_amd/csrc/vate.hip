@@ -605,10 +605,13 @@ __global__ void __launch_bounds__(256) k_census_fold(Geo G, DevState *__restrict
 
 // ---------------------------------------------------------------------------
 // k_estimate: the closed form by a direct gather, L lanes per host.  The g
-// VATs of a host are gathered in batches of U independent byte loads per lane,
+// VATs of a host are gathered in batches of U independent reads per lane,
 // decoded with CheckAT (Alg. 1), counted and summed over the host's lanes, and
 // the estimate of Eq. 11 is formed in FP32 from exact integer counts.  (With
-// the distance histogram: k_gather.)
+// the distance histogram: k_gather.)  LOCAL: the whole activity bitmap of a
+// pool of at most 2^20 ATs is copied to the workgroup's LDS first and the bits
+// are read there, so a lookup costs its hash and an LDS read; else each is a
+// read through L2, which serves about 2.5e11 of them a second.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float estimate_from_counts(uint64_t u_v, uint64_t u_p, uint32_t g, uint32_t c)
 {
@@ -634,37 +637,65 @@ __device__ __forceinline__ uint64_t pool_active(const DevState *__restrict__ st,
     return s;
 }
 
+constexpr uint32_t kLocalLog2 = 20;       // largest pool whose bitmap a workgroup keeps in LDS (128 KiB)
+constexpr uint32_t kLocalThreads = 512;   // LOCAL workgroups; others 256
+
+// Activity bit of AT pid (CheckAT for window k), from the bitmap in memory or
+// from its copy in LDS.
+template <bool LOCAL>
+__device__ __forceinline__ uint32_t active_bit(const void *bitmap, uint32_t pid)
+{
+    if constexpr (LOCAL)
+        return __builtin_amdgcn_ubfe(static_cast<const uint32_t *>(bitmap)[pid >> 5], pid, 1u);   // bit pid mod 32
+    else
+        return ((uint32_t)static_cast<const uint8_t *>(bitmap)[pid >> 3] >> (pid & 7u)) & 1u;
+}
+
+// Copies the bitmap of a pool of N <= 2^20 ATs to LDS, a thread's 16-byte
+// groups all in flight (a bitmap has at least 16 bytes).
+__device__ __forceinline__ void copy_bitmap(const Geo &G, const uint8_t *__restrict__ bitmap, uint32_t *bits)
+{
+    const uint32_t nv = G.c > 7 ? 1u << (G.c - 7) : 1u;
+    const uint4 *src = reinterpret_cast<const uint4 *>(bitmap);
+    uint4 *dst = reinterpret_cast<uint4 *>(bits);
+    constexpr uint32_t B = 8;
+    for (uint32_t q0 = threadIdx.x; q0 < nv; q0 += B * kLocalThreads) {
+        uint4 v[B];
+#pragma unroll
+        for (uint32_t u = 0; u < B; ++u) v[u] = src[min(q0 + u * kLocalThreads, nv - 1u)];
+#pragma unroll
+        for (uint32_t u = 0; u < B; ++u)
+            if (q0 + u * kLocalThreads < nv) dst[q0 + u * kLocalThreads] = v[u];
+    }
+}
+
 // VATs sub, sub + L, ... of one host that are active for k', by U gathers in
 // flight.  The activity bitmap answers CheckAT(., k) directly; the AT value
 // (for its distance) is only read for VATs that are active at all, and only
 // when a shorter window needs it, again with all of a batch in flight.
-template <int W, int L, int U>
-__device__ __forceinline__ uint32_t lane_live(const Geo &G, const uint8_t *__restrict__ pool,
-                                              const uint8_t *__restrict__ bitmap, uint32_t kprime, uint32_t key,
-                                              bool valid, uint32_t bact0, uint32_t sub)
+template <int W, int L, int U, bool LOCAL>
+__device__ __forceinline__ uint32_t lane_live(const Geo &G, const uint8_t *__restrict__ pool, const void *bitmap,
+                                              uint32_t kprime, uint32_t key, bool valid, uint32_t bact0, uint32_t sub)
 {
     const bool need_dist = kprime < G.k;
     uint32_t live = 0;
     for (uint32_t i0 = sub; i0 < G.g; i0 += L * U) {
-        uint32_t pid[U], byte[U];
+        uint32_t pid[U], bit[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) pid[u] = vat_pid(G, key, i0 + u * L);
 #pragma unroll
-        for (int u = 0; u < U; ++u) byte[u] = (valid && i0 + u * L < G.g) ? bitmap[pid[u] >> 3] : 0u;
+        for (int u = 0; u < U; ++u) bit[u] = (valid && i0 + u * L < G.g) ? active_bit<LOCAL>(bitmap, pid[u]) : 0u;
         if (!need_dist) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) live += (byte[u] >> (pid[u] & 7u)) & 1u;
+            for (int u = 0; u < U; ++u) live += bit[u];
             continue;
         }
         uint32_t val[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            byte[u] = (byte[u] >> (pid[u] & 7u)) & 1u;
-            val[u] = byte[u] ? load_at<W>(pool, pid[u], G.wb) : 0u;
-        }
+        for (int u = 0; u < U; ++u) val[u] = bit[u] ? load_at<W>(pool, pid[u], G.wb) : 0u;
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (byte[u] && value_dist(G, bact0, pid[u], val[u]) < kprime) ++live;
+            if (bit[u] && value_dist(G, bact0, pid[u], val[u]) < kprime) ++live;
     }
     return live;
 }
@@ -677,22 +708,27 @@ __device__ __forceinline__ uint32_t sum_lanes(uint32_t x)
     return x;
 }
 
-template <int W, int L, int U>
-__global__ void __launch_bounds__(256) k_estimate(Geo G, const uint8_t *__restrict__ pool,
+template <int W, int L, int U, bool LOCAL>
+__global__ void __launch_bounds__(LOCAL ? kLocalThreads : 256) k_estimate(Geo G, const uint8_t *__restrict__ pool,
                                                   const DevState *__restrict__ st,
                                                   const uint8_t *__restrict__ bitmap,
                                                   const uint32_t *__restrict__ hosts, uint32_t n,
                                                   uint32_t kprime, float *__restrict__ est,
                                                   uint32_t *__restrict__ live_out)
 {
+    extern __shared__ __attribute__((aligned(16))) uint32_t bits[];   // LOCAL
+    if constexpr (LOCAL) copy_bitmap(G, bitmap, bits);
+    const void *bm = LOCAL ? static_cast<const void *>(bits) : bitmap;
+    constexpr uint32_t per = (LOCAL ? kLocalThreads : 256) / L;
     const uint32_t sub = threadIdx.x % L;
     const uint32_t bact0 = st->bact0;
     const uint64_t active_pool = pool_active(st, kprime);
-    for (uint64_t h0 = (uint64_t)blockIdx.x * (256 / L); h0 < n; h0 += (uint64_t)gridDim.x * (256 / L)) {
+    if constexpr (LOCAL) __syncthreads();
+    for (uint64_t h0 = (uint64_t)blockIdx.x * per; h0 < n; h0 += (uint64_t)gridDim.x * per) {
         const uint64_t h = h0 + threadIdx.x / L;
         const bool valid = h < n;
         const uint32_t key = host_key(G, valid ? hosts[h] : 0u);
-        const uint32_t live = sum_lanes<L>(lane_live<W, L, U>(G, pool, bitmap, kprime, key, valid, bact0, sub));
+        const uint32_t live = sum_lanes<L>(lane_live<W, L, U, LOCAL>(G, pool, bm, kprime, key, valid, bact0, sub));
         if (valid && sub == 0) {
             est[h] = estimate_from_counts(G.g - live, G.N - active_pool, G.g, G.c);
             if (live_out) live_out[h] = live;
@@ -875,6 +911,7 @@ struct vate_sketch {
     uint32_t n_cu;               // compute units of the device
     const void *plan_ws;         // workspace holding a host plan (vate_estimate_plan), or null
     uint64_t plan_n;             // its host count
+    uint32_t plan_hosts;         // its hosts per subgroup; 0: the workspace holds the host list itself
     char err[256];
 };
 
@@ -1006,6 +1043,36 @@ static int advance(vate_sketch *s, hipStream_t st)
     return check_launch(s, "advance/preserve");
 }
 
+// Raises a kernel's dynamic-LDS limit to the device's: a per-device function
+// attribute, set once per kernel and device (bit d of the mask).  A failure is
+// reported by the check_launch after the launches.
+template <auto Kernel>
+static bool allow_lds(const vate_sketch *s)
+{
+    static std::atomic<uint64_t> done{0};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+    const uint64_t bit = 1ull << (dev & 63);
+    if (done.load(std::memory_order_acquire) & bit) return true;
+    const void *fn = reinterpret_cast<const void *>(Kernel);
+    hipFuncAttributes a;
+    if (hipFuncGetAttributes(&a, fn) != hipSuccess) return false;
+    const size_t most = s->lds_budget + kRunLdsStatic - std::max<size_t>(kRunLdsStatic, a.sharedSizeBytes);
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most) != hipSuccess) return false;
+    done.fetch_or(bit, std::memory_order_release);
+    return true;
+}
+
+static uint32_t local_bits_bytes(const Geo &G) { return G.c > 7 ? 1u << (G.c - 3) : 16u; }
+
+// Whether the lookups of n hosts read the activity bits from LDS: the pool's
+// bitmap has to fit, and there have to be enough lookups to pay for one copy
+// of it per workgroup.
+static bool local_lookups(const vate_sketch *s, uint32_t n)
+{
+    return s->G.c <= kLocalLog2 && (uint64_t)n * s->G.g >= kLocalMin;
+}
+
 // The closed form without histograms.  Lanes per host: as many as keep the
 // chip's 2048 threads per CU busy, so that few hosts take few serial rounds.
 template <int W>
@@ -1021,13 +1088,27 @@ static void launch_estimate(vate_sketch *s, const uint32_t *hosts, uint32_t n, u
         return;
     }
     const uint64_t lanes = (uint64_t)s->n_cu * 2048u / n;       // lanes a host may take (n >= 1)
+    using std::integral_constant;
+    if (local_lookups(s, n)) {
+        const uint32_t lds = local_bits_bytes(s->G);
+        const unsigned cap = s->n_cu * std::min<uint32_t>(2048u / kLocalThreads, s->lds_budget / lds);
+        auto go = [&](auto L) {
+            constexpr int l = decltype(L)::value;
+            if (!allow_lds<k_estimate<W, l, 16, true>>(s)) return;
+            k_estimate<W, l, 16, true><<<grid_for(n, kLocalThreads / l, cap), kLocalThreads, lds, st>>>(
+                s->G, s->pool, s->st, s->bitmap, hosts, n, kprime, est, live);
+        };
+        if (lanes >= 64 && s->G.g >= 512) go(integral_constant<int, 64>{});
+        else if (s->G.g >= 128) go(integral_constant<int, 16>{});
+        else go(integral_constant<int, 4>{});
+        return;
+    }
     const unsigned cap = 16u * s->n_cu;
     auto go = [&](auto L, auto U) {
         constexpr int l = decltype(L)::value, u = decltype(U)::value;
-        k_estimate<W, l, u><<<grid_for(n, 256 / l, cap), 256, 0, st>>>(s->G, s->pool, s->st, s->bitmap, hosts, n,
-                                                                       kprime, est, live);
+        k_estimate<W, l, u, false><<<grid_for(n, 256 / l, cap), 256, 0, st>>>(s->G, s->pool, s->st, s->bitmap, hosts,
+                                                                              n, kprime, est, live);
     };
-    using std::integral_constant;
     if (lanes >= 64 && s->G.g <= 256) go(integral_constant<int, 64>{}, integral_constant<int, 4>{});
     else if (lanes >= 64) go(integral_constant<int, 64>{}, integral_constant<int, 16>{});
     else if (lanes >= 16 || s->G.g >= 256) go(integral_constant<int, 16>{}, integral_constant<int, 16>{});
@@ -1036,18 +1117,38 @@ static void launch_estimate(vate_sketch *s, const uint32_t *hosts, uint32_t n, u
 
 // The direct gather with per-host distance histograms (MODE as in
 // finish_hosts).  Hosts per workgroup: 1 while the chip has room for a
-// workgroup per host, up to 16 (the network's tile).
+// workgroup per host, up to 16, or 64 for the network and where the lookups are
+// local and the rows fit beside the bitmap.
 template <int W, int MODE>
 static void launch_gather(vate_sketch *s, const uint32_t *hosts, uint32_t n, uint32_t kprime, float *est,
                           uint32_t *live, uint32_t *hist, const Windows &win, const void *weights, float *cf,
                           hipStream_t st)
 {
+    const uint32_t rowp = hist_row_words(s->G.k), row_bytes = rowp * 4u;
+    const auto *P = static_cast<const mlp::Packed *>(weights);
+    if (local_lookups(s, n)) {
+        // static LDS of the LOCAL kernels: the network's tiles, windows
+        constexpr uint32_t fixed = (MODE == kFinLearned ? 20u : 1u) * 1024u;
+        const uint32_t bits = local_bits_bytes(s->G);
+        const uint32_t room = s->lds_budget > bits + fixed ? s->lds_budget - bits - fixed : 0u;
+        if (room >= row_bytes) {
+            if (!allow_lds<k_gather<W, MODE, true>>(s)) return;
+            uint32_t lg = 0;
+            while (lg < 6 && (row_bytes << (lg + 1)) <= room && ((uint64_t)n >> lg) > 2u * s->n_cu) ++lg;
+            const uint32_t lds = bits + (row_bytes << lg);
+            const unsigned cap = s->n_cu * std::min<uint32_t>(2048u / kLocalThreads, s->lds_budget / (lds + fixed));
+            k_gather<W, MODE, true><<<grid_for(n, 1u << lg, cap), kLocalThreads, lds, st>>>(
+                s->G, s->pool, s->st, s->bitmap, hosts, n, lg, rowp, kprime, est, live, hist, win, P, cf);
+            return;
+        }
+    }
+    // (the network takes 16 hosts a wavefront: a tile as soon as every CU has one)
+    constexpr uint32_t most = MODE == kFinLearned ? 6u : 4u, room = (MODE == kFinLearned ? 2u : 8u);
     uint32_t lg = 0;
-    while (lg < 4 && ((uint64_t)n >> lg) > 8u * s->n_cu) ++lg;
-    const uint32_t rowp = hist_row_words(s->G.k);
-    k_gather<W, MODE><<<(unsigned)(((uint64_t)n + (1u << lg) - 1) >> lg), kFinThreads, (rowp * 4u) << lg, st>>>(
-        s->G, s->pool, s->st, s->bitmap, hosts, n, lg, rowp, kprime, est, live, hist, win,
-        static_cast<const mlp::Packed *>(weights), cf);
+    while (lg < most && (row_bytes << (lg + 1)) <= 32u * 1024u && ((uint64_t)n >> lg) > room * s->n_cu) ++lg;
+    if (!allow_lds<k_gather<W, MODE, false>>(s)) return;
+    k_gather<W, MODE, false><<<grid_for(n, 1u << lg, 1u << 30), 256, row_bytes << lg, st>>>(
+        s->G, s->pool, s->st, s->bitmap, hosts, n, lg, rowp, kprime, est, live, hist, win, P, cf);
 }
 
 // vate_estimate's gather, with or without histograms.
@@ -1073,86 +1174,38 @@ static void direct_learned(vate_sketch *s, const uint32_t *hosts, uint32_t n, co
 }
 
 // ---- partitioned estimate: geometry, workspace layout and launches ----
-// part_geo returns false when the host count or g is outside the partitioned
-// path's limits (g VATs of one host too many for one LDS sort) or the sketch
-// uses the locality-blocked H; the entry points then use the direct gather.
-static bool part_geo(const vate_sketch *s, uint64_t n, PartGeo *out)
+
+static uint64_t part_slices(const Geo &G) { return G.N >> std::min(G.c, kSliceLog2); }
+
+// Padded entries of a subgroup, and the distance between subgroups' regions.
+static uint64_t part_cap(const Geo &G, uint64_t hosts) { return (hosts * G.g + 3 * part_slices(G) + 3) & ~3ull; }
+static uint64_t part_region(const Geo &G, uint64_t hosts) { return (part_cap(G, hosts) + 63) & ~63ull; }
+
+// The scatter's LDS: counters, keys, 32-bit sort slots.
+static uint64_t part_lds(const Geo &G, uint64_t hosts)
+{
+    return 4 * (((part_slices(G) + 3) & ~3ull) + ((hosts + 3) & ~3ull)) + 4 * part_cap(G, hosts);
+}
+
+// Hosts per subgroup at most: the largest count whose VATs' pids fit the
+// scatter threads' registers (kRunPerThread each), whose padded sort of 32-bit
+// entries (+ slice counters, keys) fits its LDS, and whose histograms fit the
+// finalize's LDS.  0 where the partitioned path has no geometry for n hosts (g
+// VATs of one host too many for one LDS sort, the locality-blocked H, whose
+// direct gather already reads whole blocks, or entries past the lookup's 32-bit
+// chunk index); the entry points then use the direct gather.
+static uint32_t part_max_hosts(const vate_sketch *s, uint64_t n)
 {
     const Geo &G = s->G;
-    if (G.blog > 0) return false;   // blocked VATs: the direct gather already reads whole blocks
-    const uint32_t sl = G.c < kSliceLog2 ? G.c : kSliceLog2;
-    const uint64_t ns = G.N >> sl;
-    if (ns > kRunMaxSlices) return false;
-    PartGeo p{};
-    p.sl = sl;
-    p.n_slices = (uint32_t)ns;
-    p.bm_words = sl >= 5 ? 1u << (sl - 5) : 1u;
-    p.xcd = ns >= 8 ? 1u : 0u;
-    p.rowp = hist_row_words(G.k);
-    // Hosts per subgroup: the largest count whose VATs' pids fit the scatter
-    // threads' registers (kRunPerThread each), whose padded sort of 32-bit
-    // entries (+ slice counters, keys) fits its LDS, and whose histograms fit
-    // the finalize's LDS.
-    const uint64_t nsp = (ns + 3) & ~3ull;
-    auto lds_for = [&](uint64_t hosts) {   // counters, keys, 32-bit sort slots
-        const uint64_t cap = (hosts * G.g + 3 * ns + 3) & ~3ull;
-        return 4 * (nsp + ((hosts + 3) & ~3ull)) + 4 * cap;
-    };
+    if (G.blog > 0 || part_slices(G) > kRunMaxSlices) return 0;
     uint64_t hosts = kRunMaxHosts;
     hosts = std::min<uint64_t>(hosts, (uint64_t)kRunPerThread * kRunThreads / G.g);
-    hosts = std::min<uint64_t>(hosts, kFinHistBytes / (4ull * p.rowp));
-    while (hosts > 0 && lds_for(hosts) > s->lds_budget) --hosts;
-    if (hosts == 0) return false;
-    p.hosts = (uint32_t)hosts;
-    p.n_sub = (uint32_t)((n + hosts - 1) / hosts);
-    p.vats = (uint32_t)hosts * G.g;
-    p.cap = (uint32_t)((p.vats + 3ull * ns + 3) & ~3ull);
-    p.region = (p.cap + 63u) & ~63u;
-    // the lookup indexes the entries' 16-byte chunks with 32-bit integers
-    if ((uint64_t)p.n_sub * (p.region / 4u) >= (1ull << 32)) return false;
-    p.dq = kRunThreads / G.g;
-    p.dr = kRunThreads % G.g;
-    p.fast = G.a >= (1ull << sl) ? 1u : 0u;
-    // Subgroups per finalize workgroup: the network takes hosts in tiles of
-    // 64, so the count whose hosts leave the least of their last tile empty
-    // (the fewest on a tie), as long as the histograms fit.
-    {
-        uint32_t best = 1;
-        double waste = 1e30;
-        for (uint32_t f = 1; f <= 16; ++f) {
-            const uint64_t fh = f * hosts;
-            if (fh * 4ull * p.rowp > kFinHistBytes) break;
-            const double w = (double)(((fh + 63) / 64) * 64 - fh) / (double)fh;
-            if (w < waste - 1e-9) waste = w, best = f;
-        }
-        p.fgroup = best;
-    }
-    p.lds_scatter = (uint32_t)lds_for(hosts);
-    {   // lookup LDS: bits (whole 256-AT blocks + a sentinel word), rank tables,
-        // run counters, then as many live ATs' distances as fit
-        p.bm_words_lds = (p.bm_words + 1u + 7u) & ~7u;
-        const uint32_t nblk = p.bm_words_lds / 8u, nsup = (nblk + 7u) / 8u;
-        const uint32_t fixed = 4u * (p.bm_words_lds + nsup + (nblk + 1u) / 2u + kRunThreads);
-        p.dist16 = G.k > 256 ? 1u : 0u;
-        const uint32_t room = s->lds_budget > fixed ? s->lds_budget - fixed : 0u;
-        p.dist_cap = room >> p.dist16;
-        p.lds_lookup = (fixed + (p.dist_cap << p.dist16) + 15u) & ~15u;
-        if (p.lds_lookup > s->lds_budget) p.lds_lookup = s->lds_budget & ~15u, p.dist_cap = (p.lds_lookup - fixed) >> p.dist16;
-    }
-    p.lds_final = p.fgroup * p.hosts * p.rowp * 4u + 4u;
-    // Each slice's walk over the subgroups is cut into ranges, one workgroup
-    // each, so that the launch has at least one workgroup per CU (each builds
-    // its slice's LDS tables once); a range is a whole number of 64-subgroup
-    // windows (one per wavefront at a time) and holds at least one window
-    // per wavefront.
-    const uint32_t per_round = kRunThreads;   // 16 wavefronts x 64 subgroups
-    const uint32_t cus = std::max<uint32_t>(1u, s->n_cu);
-    const uint32_t want = std::max<uint32_t>(1u, std::min<uint32_t>((cus + p.n_slices - 1u) / p.n_slices,
-                                                                    p.n_sub / per_round));
-    p.span = ((p.n_sub + want - 1u) / want + 63u) & ~63u;
-    p.split = (p.n_sub + p.span - 1u) / p.span;
-    *out = p;
-    return true;
+    hosts = std::min<uint64_t>(hosts, kFinHistBytes / (4ull * hist_row_words(G.k)));
+    while (hosts > 0 && part_lds(G, hosts) > s->lds_budget) --hosts;
+    if (hosts == 0) return 0;
+    const uint64_t n_sub = (uint32_t)((n + hosts - 1) / hosts);
+    if (n_sub * (part_region(G, hosts) / 4u) >= (1ull << 32)) return 0;
+    return (uint32_t)hosts;
 }
 
 static size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
@@ -1162,35 +1215,143 @@ struct RunWs {
     uint32_t *hits;             // [n_sub][region] live results (host << 16 | distance), packed at the front of each run's slots
     uint32_t *table;            // [n_sub][n_slices + 1] run starts and live counts
     uint32_t *heads;            // [n_sub][n_slices][4] each run's first four live results
-    unsigned long long *cum;    // [k + 1] census prefix (several windows)
     size_t bytes;
 };
 
-static RunWs run_ws(const PartGeo &pg, uint32_t k, void *base)
+static RunWs run_ws(const Geo &G, uint64_t n, uint64_t hosts, void *base)
 {
     RunWs w;
     const uintptr_t p = reinterpret_cast<uintptr_t>(base);
-    const size_t ents = (size_t)pg.n_sub * pg.region;
+    const uint64_t ns = part_slices(G), n_sub = (n + hosts - 1) / hosts;
+    const size_t ents = (size_t)n_sub * part_region(G, hosts);
     size_t off = 0;
     w.entries = reinterpret_cast<uint32_t *>(p + off);
     off += align256(ents * 4);
     w.hits = reinterpret_cast<uint32_t *>(p + off);
     off += align256(ents * 4);
     w.table = reinterpret_cast<uint32_t *>(p + off);
-    off += align256((size_t)pg.n_sub * (pg.n_slices + 1) * 4);
+    off += align256((size_t)n_sub * (ns + 1) * 4);
     w.heads = reinterpret_cast<uint32_t *>(p + off);
-    off += align256((size_t)pg.n_sub * pg.n_slices * 16);
-    w.cum = reinterpret_cast<unsigned long long *>(p + off);
-    off += align256((size_t)(k + 1) * 8);
+    off += align256((size_t)n_sub * ns * 16);
+    off += align256((size_t)(G.k + 1) * 8);   // kept in the size, which callers may have stored
     w.bytes = off;
     return w;
 }
 
-static int set_lds_limit(vate_sketch *s, const void *fn, uint32_t bytes)
+// The workspace an estimate of n hosts has to be given: the layout with the
+// most hosts per subgroup, whichever path is taken (256 bytes where there is no
+// partitioned geometry).
+static size_t workspace_need(const vate_sketch *s, uint64_t n)
 {
-    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    if (e != hipSuccess) return fail(s, VATE_E_DEVICE, hipGetErrorString(e));
-    return VATE_OK;
+    const uint32_t hosts = part_max_hosts(s, n);
+    return hosts ? run_ws(s->G, n, hosts, nullptr).bytes : 256;
+}
+
+// Hosts per subgroup that leave no scatter workgroup without a subgroup in
+// the last round: as many rounds of n_cu subgroups as the largest subgroups
+// take, with the hosts spread over all of them.  (20,011 hosts, g = 1024: 742
+// subgroups of 27 in three rounds instead of 527 of 38, of which the third
+// round had 15.)  It takes a little more workspace (run padding), which a
+// caller who kept an older size may not have given.
+static uint32_t part_hosts(const vate_sketch *s, uint64_t n, size_t have)
+{
+    const uint32_t most = part_max_hosts(s, n);
+    if (most == 0) return 0;
+    const uint64_t n_sub = (n + most - 1) / most, rounds = (n_sub + s->n_cu - 1) / s->n_cu;
+    const uint32_t even = (uint32_t)std::max<uint64_t>(1, (n + rounds * s->n_cu - 1) / (rounds * s->n_cu));
+    return even < most && run_ws(s->G, n, even, nullptr).bytes <= have ? even : most;
+}
+
+// Whether the partitioned lookups answer n hosts.  A direct gather is a read
+// through L2 per lookup, 2.5e11 a second while an XCD's 4 MiB L2 holds the
+// bitmap (up to 2^25 ATs) and 6.5e10 on a 2^28 pool; partitioned lookups reach
+// 3.5e11 and more but take three passes and 25 us at least.  Measured (closed
+// form, byte ATs, g = 64 .. 1024) they break even at lookups x ATs of about
+// 2^49: 2M lookups on 2^28 ATs (36 us each way), 16M on 2^25 (70), 64M on 2^23
+// (240); from 2^27 to 2^26 at half of that.  Below 2^23 ATs the direct gather
+// stays ahead (512M lookups on 2^22: 0.87 of the partitioned time).  A plan's
+// runs leave out the first pass: half the lookups.
+static bool partitioned(const vate_sketch *s, uint64_t n, bool planned = false)
+{
+    return s->G.c >= kPartLog2 && n * s->G.g >= (kPartMin >> s->G.c >> (planned ? 1 : 0)) && part_max_hosts(s, n) > 0;
+}
+
+// The workspace size reported to callers: enough for the even subgroups.
+static size_t workspace_size(const vate_sketch *s, uint64_t n)
+{
+    size_t need = workspace_need(s, n);
+    if (partitioned(s, n, true)) need = std::max(need, run_ws(s->G, n, part_hosts(s, n, ~size_t(0)), nullptr).bytes);
+    return need;
+}
+
+// The workspace that several windows have to be given (without a partitioned
+// geometry, as much as full histograms).
+static size_t multi_need(const vate_sketch *s, uint64_t n)
+{
+    if (part_max_hosts(s, n) > 0) return workspace_need(s, n);
+    return align256((size_t)n * (s->p.k + 1) * 4) + align256(8ull * (s->p.k + 1));
+}
+
+// The geometry for n hosts, `hosts` per subgroup (from part_hosts).
+static PartGeo part_geo(const vate_sketch *s, uint64_t n, uint32_t hosts)
+{
+    const Geo &G = s->G;
+    const uint64_t ns = part_slices(G);
+    PartGeo p{};
+    p.n_slices = (uint32_t)ns;
+    p.xcd = ns >= 8 ? 1u : 0u;
+    p.rowp = hist_row_words(G.k);
+    p.hosts = hosts;
+    p.n_sub = (uint32_t)((n + hosts - 1) / hosts);
+    p.vats = hosts * G.g;
+    p.cap = (uint32_t)part_cap(G, hosts);
+    p.region = (uint32_t)part_region(G, hosts);
+    p.dq = kRunThreads / G.g;
+    p.dr = kRunThreads % G.g;
+    p.fast = G.a >= (1ull << kSliceLog2) ? 1u : 0u;
+    const uint32_t cus = std::max<uint32_t>(1u, s->n_cu);
+    // Subgroups per finalize workgroup: the network takes hosts in tiles of
+    // 64, so the count whose hosts leave the least of their last tile empty
+    // (the fewest on a tie), as long as the histograms fit and every CU gets a
+    // workgroup.
+    {
+        uint32_t best = 1;
+        double waste = 1e30;
+        for (uint32_t f = 1; f <= 16 && (f == 1 || f * cus <= p.n_sub); ++f) {
+            const uint64_t fh = f * hosts;
+            if (fh * 4ull * p.rowp > kFinHistBytes) break;
+            const double w = (double)(((fh + 63) / 64) * 64 - fh) / (double)fh;
+            if (w < waste - 1e-9) waste = w, best = f;
+        }
+        p.fgroup = best;
+    }
+    p.lds_scatter = (uint32_t)part_lds(G, hosts);
+    {   // lookup LDS: bits, rank tables, run counters, then as many live ATs'
+        // distances as fit
+        constexpr uint32_t nblk = kBmWordsLds / 8u, nsup = (nblk + 7u) / 8u;
+        constexpr uint32_t fixed = 4u * (kBmWordsLds + nsup + (nblk + 1u) / 2u + kRunThreads);
+        p.dist16 = G.k > 256 ? 1u : 0u;
+        const uint32_t room = s->lds_budget > fixed ? s->lds_budget - fixed : 0u;
+        p.dist_cap = room >> p.dist16;
+        p.lds_lookup = (fixed + (p.dist_cap << p.dist16) + 15u) & ~15u;
+        if (p.lds_lookup > s->lds_budget) p.lds_lookup = s->lds_budget & ~15u, p.dist_cap = (p.lds_lookup - fixed) >> p.dist16;
+    }
+    p.lds_final = p.fgroup * p.hosts * p.rowp * 4u + 4u;
+    // Each slice's walk over the subgroups is cut into ranges, one workgroup
+    // each, so that the launch has at least one workgroup per CU (each builds
+    // its slice's LDS tables once); a range holds at least one subgroup per
+    // wavefront.  The subgroups of a wavefront's window are as many as leave
+    // every wavefront of the range a window, 64 at most: with 64 always, the
+    // 742 subgroups of 20,011 hosts kept 12 of a workgroup's 16 wavefronts.
+    constexpr uint32_t waves = kRunThreads / 64u;
+    const uint32_t want = std::max<uint32_t>(1u, std::min<uint32_t>((cus + p.n_slices - 1u) / p.n_slices,
+                                                                    p.n_sub / waves));
+    const uint32_t range = (p.n_sub + want - 1u) / want;
+    p.win = 64;
+    while (p.win > 1 && (range + p.win - 1) / p.win < waves) p.win /= 2;
+    p.span = (range + p.win - 1u) & ~(p.win - 1u);
+    p.split = (p.n_sub + p.span - 1u) / p.span;
+    return p;
 }
 
 // PART_ALL: scatter, lookup, finalize; PART_PLAN: the scatter only (the
@@ -1202,22 +1363,9 @@ static int launch_part(vate_sketch *s, const PartGeo &pg, void *ws, const uint32
                        uint32_t kprime, float *est, uint32_t *live, uint32_t *hist, const Windows &win,
                        const void *weights, float *cf, hipStream_t st, int steps = PART_ALL)
 {
-    // The dynamic-LDS limits are a per-device function attribute: set once
-    // per device (bit d of the mask) and instantiation.
-    static std::atomic<uint64_t> attr_set{0};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    const uint64_t bit = 1ull << (dev & 63);
-    if (!(attr_set.load(std::memory_order_acquire) & bit)) {
-        int rc = set_lds_limit(s, reinterpret_cast<const void *>(&k_run_scatter), s->lds_budget);
-        if (rc == VATE_OK)
-            rc = set_lds_limit(s, reinterpret_cast<const void *>(&k_run_lookup<W>), s->lds_budget);
-        if (rc == VATE_OK)
-            rc = set_lds_limit(s, reinterpret_cast<const void *>(&k_run_finalize<MODE>), kFinHistBytes + 16u);
-        if (rc != VATE_OK) return rc;
-        attr_set.fetch_or(bit, std::memory_order_release);
-    }
-    const RunWs w = run_ws(pg, s->p.k, ws);
+    if (!allow_lds<k_run_scatter>(s) || !allow_lds<k_run_lookup<W>>(s) || !allow_lds<k_run_finalize<MODE>>(s))
+        return check_launch(s, "dynamic LDS");
+    const RunWs w = run_ws(s->G, n, pg.hosts, ws);
     if (steps != PART_RUN)
         k_run_scatter<<<std::min(pg.n_sub, s->n_cu), kRunThreads, pg.lds_scatter, st>>>(s->G, pg, hosts, n, w.entries,
                                                                                        w.table);
@@ -1236,7 +1384,6 @@ static int launch_part_w(vate_sketch *s, const PartGeo &pg, void *ws, const uint
                          uint32_t kprime, float *est, uint32_t *live, uint32_t *hist, const Windows &win,
                          const void *weights, float *cf, hipStream_t st, int steps = PART_ALL)
 {
-    if (steps == PART_ALL && ws == s->plan_ws) s->plan_ws = nullptr;   // the plan is overwritten
     return by_width(s->p.width, [&](auto W) {
         return launch_part<decltype(W)::value, MODE>(s, pg, ws, hosts, n, kprime, est, live, hist, win, weights, cf,
                                                      st, steps);
@@ -1369,8 +1516,7 @@ int vate_estimate_workspace_bytes(const vate_sketch *s, size_t n_hosts, size_t *
 {
     if (!s || !bytes) return VATE_E_INVAL;
     if (n_hosts > 0xFFFFFFFFull - 1024) return VATE_E_INVAL;
-    PartGeo pg;
-    *bytes = part_geo(s, n_hosts, &pg) ? run_ws(pg, s->p.k, nullptr).bytes : 256;
+    *bytes = workspace_size(s, n_hosts);
     return VATE_OK;
 }
 
@@ -1387,22 +1533,21 @@ static int estimate_ws_impl(vate_sketch *s, const uint32_t *hosts_dev, size_t n_
     if (kprime < 1 || kprime > s->p.k) return fail(s, VATE_E_INVAL, "k' must be in [1, k]");
     if (n_hosts > 0xFFFFFFFFull - 1024) return fail(s, VATE_E_INVAL, "too many hosts");
     if (n_hosts == 0) return VATE_OK;
-    size_t need = 0;
-    vate_estimate_workspace_bytes(s, n_hosts, &need);
-    if (!workspace_dev || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace_dev) & 255u))
+    if (!workspace_dev || workspace_bytes < workspace_need(s, n_hosts) || (reinterpret_cast<uintptr_t>(workspace_dev) & 255u))
         return fail(s, VATE_E_INVAL, "workspace missing, too small or not 256-byte aligned");
     if (!hosts_dev || !est_dev || (reinterpret_cast<uintptr_t>(hosts_dev) & 3u) ||
         (reinterpret_cast<uintptr_t>(est_dev) & 3u) || (reinterpret_cast<uintptr_t>(live_dev) & 3u) ||
         (reinterpret_cast<uintptr_t>(hist_dev) & 3u))
         return fail(s, VATE_E_INVAL, "hosts/est/live/hist must be non-NULL (live, hist may be NULL) and 4-byte aligned");
     const uint32_t n = (uint32_t)n_hosts;
-    PartGeo pg;
-    if (!part_geo(s, n, &pg)) {      // outside the partitioned limits: direct gather
-        if (hist_dev && s->p.k > (uint32_t)kMaxHistK)
-            return fail(s, VATE_E_UNSUPPORTED, "per-host histogram of this geometry needs k <= 256");
+    if (workspace_dev == s->plan_ws) s->plan_ws = nullptr;   // the plan is overwritten
+    if (hist_dev && s->p.k > (uint32_t)kMaxHistK && part_max_hosts(s, n) == 0)
+        return fail(s, VATE_E_UNSUPPORTED, "per-host histogram of this geometry needs k <= 256");
+    if (!partitioned(s, n)) {
         direct_estimate(s, hosts_dev, n, kprime, est_dev, live_dev, hist_dev, st);
         return check_launch(s, what);
     }
+    const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes));
     const int rc = launch_part_w<kFinClosedForm>(s, pg, workspace_dev, hosts_dev, n, kprime, est_dev, live_dev,
                                                  hist_dev, Windows{}, nullptr, nullptr, st);
     if (rc != VATE_OK) return rc;
@@ -1453,9 +1598,8 @@ int vate_estimate_noalloc(vate_sketch *s, const uint32_t *hosts_dev, size_t n_ho
 {
     if (!s) return VATE_E_INVAL;
     if (s->dead) return VATE_E_DEVICE;
-    size_t need = 0;
     if (n_hosts > 0xFFFFFFFFull - 1024) return fail(s, VATE_E_INVAL, "too many hosts");
-    vate_estimate_workspace_bytes(s, n_hosts, &need);
+    const size_t need = workspace_need(s, n_hosts);
     if (need > VATE_NOALLOC_SCRATCH_BYTES) {
         char buf[200];
         snprintf(buf, sizeof(buf), "estimate_noalloc: %zu hosts need %zu bytes of workspace, more than the %u of the "
@@ -1475,34 +1619,40 @@ int vate_estimate_plan(vate_sketch *s, const uint32_t *hosts_dev, size_t n_hosts
     if (!s) return VATE_E_INVAL;
     if (s->dead) return VATE_E_DEVICE;
     if (n_hosts == 0 || n_hosts > 0xFFFFFFFFull - 1024) return fail(s, VATE_E_INVAL, "need 1 .. 2^32-1025 hosts");
-    PartGeo pg;
-    if (!part_geo(s, n_hosts, &pg))
+    if (part_max_hosts(s, n_hosts) == 0)
         return fail(s, VATE_E_UNSUPPORTED, "no partitioned plan for this sketch (use vate_estimate)");
-    size_t need = 0;
-    vate_estimate_workspace_bytes(s, n_hosts, &need);
-    if (!workspace_dev || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace_dev) & 255u))
+    if (!workspace_dev || workspace_bytes < workspace_need(s, n_hosts) ||
+        (reinterpret_cast<uintptr_t>(workspace_dev) & 255u))
         return fail(s, VATE_E_INVAL, "workspace missing, too small or not 256-byte aligned");
     if (!hosts_dev || (reinterpret_cast<uintptr_t>(hosts_dev) & 3u))
         return fail(s, VATE_E_INVAL, "hosts must be non-NULL and 4-byte aligned");
-    const int rc = launch_part_w<kFinClosedForm>(s, pg, workspace_dev, hosts_dev, (uint32_t)n_hosts, s->p.k, nullptr,
-                                                 nullptr, nullptr, Windows{}, nullptr, nullptr,
-                                                 static_cast<hipStream_t>(stream), PART_PLAN);
-    if (rc != VATE_OK) return rc;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const uint32_t n = (uint32_t)n_hosts;
+    if (partitioned(s, n, true)) {
+        const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes));
+        const int rc = launch_part_w<kFinClosedForm>(s, pg, workspace_dev, hosts_dev, n, s->p.k, nullptr, nullptr,
+                                                     nullptr, Windows{}, nullptr, nullptr, st, PART_PLAN);
+        if (rc != VATE_OK) return rc;
+        s->plan_hosts = pg.hosts;
+    } else {
+        // the runs gather directly: they need the hosts alone (4 of the
+        // workspace's 8 g or more bytes per host)
+        k_copy_hosts<<<grid_for(n, 256, 4096), 256, 0, st>>>(hosts_dev, n, static_cast<uint32_t *>(workspace_dev));
+        s->plan_hosts = 0;
+    }
     s->plan_ws = workspace_dev;
     s->plan_n = n_hosts;
     return check_launch(s, "estimate_plan");
 }
 
 // A run needs a closed slice and the plan made for this workspace and host count.
-static int check_plan(vate_sketch *s, size_t n_hosts, const void *workspace_dev, size_t workspace_bytes, size_t need,
-                      PartGeo *pg)
+static int check_plan(vate_sketch *s, size_t n_hosts, const void *workspace_dev, size_t workspace_bytes)
 {
     if (s->dead) return VATE_E_DEVICE;
     if (!s->closed) return fail(s, VATE_E_STATE, "estimate needs a closed slice (call vate_close_slice)");
     if (!workspace_dev || workspace_dev != s->plan_ws || n_hosts != s->plan_n)
         return fail(s, VATE_E_STATE, "no plan for this workspace and host count (call vate_estimate_plan)");
-    if (workspace_bytes < need) return fail(s, VATE_E_INVAL, "workspace too small");
-    if (!part_geo(s, n_hosts, pg)) return fail(s, VATE_E_STATE, "plan geometry unavailable");
+    if (workspace_bytes < workspace_need(s, n_hosts)) return fail(s, VATE_E_INVAL, "workspace too small");
     return VATE_OK;
 }
 
@@ -1511,17 +1661,19 @@ int vate_estimate_run(vate_sketch *s, size_t n_hosts, uint32_t kprime, float *es
 {
     if (!s) return VATE_E_INVAL;
     if (kprime < 1 || kprime > s->p.k) return fail(s, VATE_E_INVAL, "k' must be in [1, k]");
-    size_t need = 0;
-    vate_estimate_workspace_bytes(s, n_hosts, &need);
-    PartGeo pg;
-    int rc = check_plan(s, n_hosts, workspace_dev, workspace_bytes, need, &pg);
+    int rc = check_plan(s, n_hosts, workspace_dev, workspace_bytes);
     if (rc != VATE_OK) return rc;
     if (!est_dev || (reinterpret_cast<uintptr_t>(est_dev) & 3u) || (reinterpret_cast<uintptr_t>(live_dev) & 3u) ||
         (reinterpret_cast<uintptr_t>(hist_dev) & 3u))
         return fail(s, VATE_E_INVAL, "est/live/hist must be 4-byte aligned, est non-NULL");
-    rc = launch_part_w<kFinClosedForm>(s, pg, workspace_dev, nullptr, (uint32_t)n_hosts, kprime, est_dev, live_dev,
-                                       hist_dev, Windows{}, nullptr, nullptr, static_cast<hipStream_t>(stream),
-                                       PART_RUN);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const uint32_t n = (uint32_t)n_hosts;
+    if (s->plan_hosts == 0) {
+        direct_estimate(s, static_cast<const uint32_t *>(workspace_dev), n, kprime, est_dev, live_dev, hist_dev, st);
+        return check_launch(s, "estimate_run");
+    }
+    rc = launch_part_w<kFinClosedForm>(s, part_geo(s, n, s->plan_hosts), workspace_dev, nullptr, n, kprime, est_dev,
+                                       live_dev, hist_dev, Windows{}, nullptr, nullptr, st, PART_RUN);
     if (rc != VATE_OK) return rc;
     return check_launch(s, "estimate_run");
 }
@@ -1531,17 +1683,19 @@ int vate_estimate_learned_run(vate_sketch *s, size_t n_hosts, const void *weight
 {
     if (!s) return VATE_E_INVAL;
     if (s->p.k > (uint32_t)kLearnMaxK) return fail(s, VATE_E_UNSUPPORTED, "learned estimator needs k + 3 <= 64");
-    size_t need = 0;
-    vate_estimate_learned_workspace_bytes(s, n_hosts, &need);
-    PartGeo pg;
-    int rc = check_plan(s, n_hosts, workspace_dev, workspace_bytes, need, &pg);
+    int rc = check_plan(s, n_hosts, workspace_dev, workspace_bytes);
     if (rc != VATE_OK) return rc;
     if (!est_dev || !est_cf_dev || !weights_dev || (reinterpret_cast<uintptr_t>(est_dev) & 3u) ||
         (reinterpret_cast<uintptr_t>(est_cf_dev) & 3u) || (reinterpret_cast<uintptr_t>(weights_dev) & 255u))
         return fail(s, VATE_E_INVAL, "est/est_cf must be 4-byte and weights 256-byte aligned, non-NULL");
-    rc = launch_part_w<kFinLearned>(s, pg, workspace_dev, nullptr, (uint32_t)n_hosts, s->p.k, est_dev, nullptr,
-                                    nullptr, Windows{}, weights_dev, est_cf_dev, static_cast<hipStream_t>(stream),
-                                    PART_RUN);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const uint32_t n = (uint32_t)n_hosts;
+    if (s->plan_hosts == 0) {
+        direct_learned(s, static_cast<const uint32_t *>(workspace_dev), n, weights_dev, est_dev, est_cf_dev, st);
+        return check_launch(s, "estimate_learned_run");
+    }
+    rc = launch_part_w<kFinLearned>(s, part_geo(s, n, s->plan_hosts), workspace_dev, nullptr, n, s->p.k, est_dev,
+                                    nullptr, nullptr, Windows{}, weights_dev, est_cf_dev, st, PART_RUN);
     if (rc != VATE_OK) return rc;
     return check_launch(s, "estimate_learned_run");
 }
@@ -1556,9 +1710,7 @@ int vate_estimate_learned_ws(vate_sketch *s, const uint32_t *hosts_dev, size_t n
     if (s->p.k > (uint32_t)kLearnMaxK) return fail(s, VATE_E_UNSUPPORTED, "learned estimator needs k + 3 <= 64");
     if (n_hosts > 0xFFFFFFFFull - 1024) return fail(s, VATE_E_INVAL, "too many hosts");
     if (n_hosts == 0) return VATE_OK;
-    size_t need = 0;
-    vate_estimate_learned_workspace_bytes(s, n_hosts, &need);
-    if (!workspace_dev || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace_dev) & 255u))
+    if (!workspace_dev || workspace_bytes < workspace_need(s, n_hosts) || (reinterpret_cast<uintptr_t>(workspace_dev) & 255u))
         return fail(s, VATE_E_INVAL, "workspace missing, too small or not 256-byte aligned");
     if (!hosts_dev || !est_dev || !est_cf_dev || !weights_dev || (reinterpret_cast<uintptr_t>(hosts_dev) & 3u) ||
         (reinterpret_cast<uintptr_t>(est_dev) & 3u) || (reinterpret_cast<uintptr_t>(est_cf_dev) & 3u) ||
@@ -1566,11 +1718,12 @@ int vate_estimate_learned_ws(vate_sketch *s, const uint32_t *hosts_dev, size_t n
         return fail(s, VATE_E_INVAL, "hosts/est/est_cf must be 4-byte and weights 256-byte aligned, non-NULL");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const uint32_t n = (uint32_t)n_hosts;
-    PartGeo pg;
-    if (!part_geo(s, n, &pg)) {      // outside the partitioned limits: fused direct gather
+    if (workspace_dev == s->plan_ws) s->plan_ws = nullptr;   // the plan is overwritten
+    if (!partitioned(s, n)) {
         direct_learned(s, hosts_dev, n, weights_dev, est_dev, est_cf_dev, st);
         return check_launch(s, "estimate_learned_ws");
     }
+    const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes));
     const int rc = launch_part_w<kFinLearned>(s, pg, workspace_dev, hosts_dev, n, s->p.k, est_dev, nullptr, nullptr,
                                               Windows{}, weights_dev, est_cf_dev, st);
     if (rc != VATE_OK) return rc;
@@ -1581,11 +1734,8 @@ int vate_estimate_multi_workspace_bytes(const vate_sketch *s, size_t n_hosts, si
 {
     if (!s || !bytes) return VATE_E_INVAL;
     if (n_hosts > 0xFFFFFFFFull - 1024) return VATE_E_INVAL;
-    PartGeo pg;
-    if (part_geo(s, n_hosts, &pg))
-        *bytes = run_ws(pg, s->p.k, nullptr).bytes;
-    else    // direct gather into full histograms, then the windows
-        *bytes = align256((size_t)n_hosts * (s->p.k + 1) * 4) + align256(8ull * (s->p.k + 1));
+    *bytes = multi_need(s, n_hosts);
+    if (partitioned(s, n_hosts, true)) *bytes = std::max(*bytes, workspace_size(s, n_hosts));
     return VATE_OK;
 }
 
@@ -1605,24 +1755,23 @@ int vate_estimate_multi_ws(vate_sketch *s, const uint32_t *hosts_dev, size_t n_h
     }
     if (n_hosts > 0xFFFFFFFFull - 1024) return fail(s, VATE_E_INVAL, "too many hosts");
     if (n_hosts == 0) return VATE_OK;
-    size_t need = 0;
-    vate_estimate_multi_workspace_bytes(s, n_hosts, &need);
-    if (!workspace_dev || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace_dev) & 255u))
+    if (!workspace_dev || workspace_bytes < multi_need(s, n_hosts) || (reinterpret_cast<uintptr_t>(workspace_dev) & 255u))
         return fail(s, VATE_E_INVAL, "workspace missing, too small or not 256-byte aligned");
     if (!hosts_dev || !est_dev || (reinterpret_cast<uintptr_t>(hosts_dev) & 3u) ||
         (reinterpret_cast<uintptr_t>(est_dev) & 3u))
         return fail(s, VATE_E_INVAL, "hosts/est must be non-NULL and 4-byte aligned");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const uint32_t n = (uint32_t)n_hosts;
-    PartGeo pg;
-    if (part_geo(s, n, &pg)) {
+    if (workspace_dev == s->plan_ws) s->plan_ws = nullptr;   // the plan is overwritten
+    if (s->p.k > (uint32_t)kMaxHistK && part_max_hosts(s, n) == 0)
+        return fail(s, VATE_E_UNSUPPORTED, "several windows for this geometry need k <= 256");
+    if (partitioned(s, n)) {
+        const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes));
         const int rc = launch_part_w<kFinMulti>(s, pg, workspace_dev, hosts_dev, n, s->p.k, est_dev, nullptr,
                                                 nullptr, win, nullptr, nullptr, st);
         if (rc != VATE_OK) return rc;
         return check_launch(s, "estimate_multi_ws");
     }
-    if (s->p.k > (uint32_t)kMaxHistK)
-        return fail(s, VATE_E_UNSUPPORTED, "several windows for this geometry need k <= 256");
     by_width(s->p.width, [&](auto W) {
         launch_gather<decltype(W)::value, kFinMulti>(s, hosts_dev, n, s->p.k, est_dev, nullptr, nullptr, win, nullptr,
                                                      nullptr, st);
@@ -1634,8 +1783,7 @@ int vate_estimate_learned_workspace_bytes(const vate_sketch *s, size_t n_hosts, 
 {
     if (!s || !bytes) return VATE_E_INVAL;
     if (n_hosts > 0xFFFFFFFFull - 1024) return VATE_E_INVAL;
-    PartGeo pg;
-    *bytes = part_geo(s, n_hosts, &pg) ? run_ws(pg, s->p.k, nullptr).bytes : 256;
+    *bytes = workspace_size(s, n_hosts);
     return VATE_OK;
 }
 

@@ -256,7 +256,7 @@ template <int W, int L>
 __device__ __forceinline__ uint32_t batch_host_live(const BatchItem &it, uint32_t key, bool valid, uint32_t bact0,
                                                     uint32_t sub)
 {
-    return sum_lanes<L>(lane_live<W, L, 16>(it.G, it.pool, it.bitmap, it.kprime, key, valid, bact0, sub));
+    return sum_lanes<L>(lane_live<W, L, 16, false>(it.G, it.pool, it.bitmap, it.kprime, key, valid, bact0, sub));
 }
 
 template <int L>

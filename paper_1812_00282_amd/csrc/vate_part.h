@@ -48,6 +48,8 @@ constexpr uint32_t kRunPerThread = 40;                          // VATs hashed p
 constexpr uint32_t kRunLdsMax = 160u * 1024u;                   // gfx950 LDS per workgroup
 constexpr uint32_t kRunLdsStatic = 64u;                         // k_run_scatter's static LDS (wsum)
 constexpr uint32_t kSliceLog2 = 20;                             // ATs per slice: 2^20, 128 KiB of activity bits
+constexpr uint32_t kBmWords = 1u << (kSliceLog2 - 5);           // 32-bit bitmap words per slice
+constexpr uint32_t kBmWordsLds = (kBmWords + 1u + 7u) & ~7u;    // and in LDS: whole 256-AT blocks, a zero sentinel word after
 constexpr uint32_t kRunMaxSlices = 4096;                        // any pool up to 2^32 ATs
 constexpr uint32_t kRunMaxHosts = 1024;                         // hosts per subgroup
 constexpr uint32_t kFinThreads = 256;
@@ -55,10 +57,7 @@ constexpr uint32_t kLookU = 8;                                  // 16-byte entry
 constexpr uint32_t kFinHistBytes = 64u * 1024u;                 // per-subgroup histogram ceiling
 
 struct PartGeo {
-    uint32_t sl;          // ATs per slice = 2^sl
-    uint32_t n_slices;    // N >> sl
-    uint32_t bm_words;    // 32-bit bitmap words per slice (at least one)
-    uint32_t bm_words_lds;// the lookup's LDS words for them: whole 256-AT blocks and a zero sentinel word after
+    uint32_t n_slices;    // N >> kSliceLog2
     uint32_t dist_cap;    // live ATs of a slice whose distances the lookup keeps in LDS
     uint32_t dist16;      // distances take 16 bits (k > 256)
     uint32_t hosts;       // hosts per subgroup
@@ -67,11 +66,12 @@ struct PartGeo {
     uint32_t cap;         // padded entries per subgroup at most: vats + 3 n_slices, rounded up to 4
     uint32_t region;      // entries between subgroup regions (cap rounded up to 64)
     uint32_t dq, dr;      // kRunThreads = dq * g + dr
-    uint32_t fast;        // every block holds >= 2^sl ATs: a slice meets at most two blocks
+    uint32_t fast;        // every block holds a whole slice's ATs: a slice meets at most two blocks
     uint32_t rowp;        // u32 words per packed 16-bit histogram row: ceil((k + 1) / 2), made odd
     uint32_t xcd;         // give the workgroups of one slice to one XCD
     uint32_t split;       // lookup workgroups per slice, each over a range of subgroups
-    uint32_t span;        // subgroups per range (a multiple of kGroupRuns)
+    uint32_t span;        // subgroups per range (a multiple of win)
+    uint32_t win;         // subgroups per wavefront and window of the lookup (a power of two, at most 64)
     uint32_t fgroup;      // subgroups per finalize workgroup
     uint32_t lds_scatter, lds_lookup, lds_final;
 };
@@ -96,7 +96,7 @@ __global__ void __launch_bounds__(kRunThreads) k_run_scatter(Geo G, PartGeo PG, 
     uint32_t *keys = lds + nsp;           // host keys
     uint32_t *sorted = keys + nkp;        // entries by slice, runs padded to 4 (16-byte aligned)
     const uint32_t t = threadIdx.x;
-    const uint32_t sl = PG.sl, mask = (1u << sl) - 1u;
+    constexpr uint32_t sl = kSliceLog2, mask = (1u << sl) - 1u;
     const uint32_t host_t0 = t / G.g, i_t0 = t - host_t0 * G.g;
     const uint32_t d_ik = PG.dr * kPhi, g_ik = G.g * kPhi;
 
@@ -271,7 +271,8 @@ __device__ __forceinline__ uint32_t comp4(const uint4 &v, uint32_t m)
     return m == 0 ? v.x : m == 1 ? v.y : m == 2 ? v.z : v.w;
 }
 
-constexpr uint32_t kBmLoads = 8;      // 16-byte bitmap loads in flight per thread
+constexpr uint32_t kBmLoads = kBmWords / 4u / kRunThreads;   // 16-byte bitmap loads per thread
+static_assert(kBmLoads * 4u * kRunThreads == kBmWords, "a slice's bits are whole rounds of 16-byte loads");
 constexpr uint32_t kDistWords = 8;    // bitmap words whose first live AT is loaded together
 
 // Rank support for the slice's activity bits in the lookup's LDS: the live
@@ -303,9 +304,9 @@ __global__ void __launch_bounds__(kRunThreads) k_run_lookup(Geo G, PartGeo PG, c
     // slice's live ATs in slice order (when they fit).
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     __shared__ uint32_t wsum[kRunThreads / 64];
-    const uint32_t sl = PG.sl, mask = (1u << sl) - 1u, omask = (2u << sl) - 1u;
-    const uint32_t nw = PG.bm_words, nwp = PG.bm_words_lds;
-    const uint32_t nblk = nwp / 8u, nsup = (nblk + 7u) / 8u;
+    constexpr uint32_t sl = kSliceLog2, mask = (1u << sl) - 1u, omask = (2u << sl) - 1u;
+    constexpr uint32_t nw = kBmWords, nwp = kBmWordsLds;
+    constexpr uint32_t nblk = nwp / 8u, nsup = (nblk + 7u) / 8u;
     uint32_t *bm = lds;
     uint32_t *sup = bm + nwp;
     uint16_t *blk = reinterpret_cast<uint16_t *>(sup + nsup);
@@ -326,34 +327,16 @@ __global__ void __launch_bounds__(kRunThreads) k_run_lookup(Geo G, PartGeo PG, c
     const uint32_t s_lo = part * PG.span, s_hi = min(PG.n_sub, s_lo + PG.span);
     const uint32_t t = threadIdx.x, lane = t & 63u, wv = t >> 6;
     {
-        // From 2^7 ATs a slice's words are whole 16-byte groups (16-byte
-        // aligned): a thread issues all its group loads before it stores any,
-        // so the slice's bits take one round trip rather than one per word.
-        const uint32_t *src = bitmap + (size_t)b * nw;
-        const uint32_t nv = sl >= 7 ? nw / 4u : 0u;
-        const uint4 *src4 = reinterpret_cast<const uint4 *>(src);
+        // A thread issues all its 16-byte group loads before it stores any, so
+        // the slice's bits take one round trip rather than one per word.
+        const uint4 *src4 = reinterpret_cast<const uint4 *>(bitmap + (size_t)b * nw);
         uint4 *bm4 = reinterpret_cast<uint4 *>(bm);
-        for (uint32_t q0 = t; q0 < nv; q0 += kBmLoads * kRunThreads) {
-            uint4 v[kBmLoads];
+        uint4 v[kBmLoads];
 #pragma unroll
-            for (uint32_t u = 0; u < kBmLoads; ++u) {
-                const uint32_t q = q0 + u * kRunThreads;
-                v[u] = src4[q < nv ? q : q0];     // a group past the end reloads q0 and is not stored
-            }
-            // every load is used here, so none is sunk into its store's branch
+        for (uint32_t u = 0; u < kBmLoads; ++u) v[u] = src4[t + u * kRunThreads];
 #pragma unroll
-            for (uint32_t u = 0; u < kBmLoads; ++u) asm volatile("" ::"v"(v[u].x), "v"(v[u].y), "v"(v[u].z), "v"(v[u].w));
-#pragma unroll
-            for (uint32_t u = 0; u < kBmLoads; ++u) {
-                const uint32_t q = q0 + u * kRunThreads;
-                if (q < nv) bm4[q] = v[u];
-            }
-        }
-        for (uint32_t q = 4u * nv + t; q < nwp; q += kRunThreads) {
-            uint32_t v = q < nw ? src[q] : 0u;
-            if (sl < 5 && q == 0) v &= (1u << (1u << sl)) - 1u;   // bits past the pool: the sentinel among them
-            bm[q] = v;
-        }
+        for (uint32_t u = 0; u < kBmLoads; ++u) bm4[t + u * kRunThreads] = v[u];
+        if (t < nwp - nw) bm[nw + t] = 0;
     }
     __syncthreads();
     // rank tables: thread x < nsup sums its superblock's blocks
@@ -419,18 +402,14 @@ __global__ void __launch_bounds__(kRunThreads) k_run_lookup(Geo G, PartGeo PG, c
     const bool in_lds = live <= PG.dist_cap;
     __syncthreads();
     if (in_lds) {
-        const uint32_t per = (nw + kRunThreads - 1u) / kRunThreads;
-        const uint32_t q_lo = min(nw, t * per), q_hi = min(nw, q_lo + per);
-        uint32_t r = q_lo < q_hi ? live_rank(bm, sup, blk, 32u * q_lo) : 0u;
+        constexpr uint32_t per = nw / kRunThreads;
+        static_assert(per % kDistWords == 0, "whole batches of words");
+        const uint32_t q_lo = t * per, q_hi = q_lo + per;
+        uint32_t r = live_rank(bm, sup, blk, 32u * q_lo);
         for (uint32_t q0 = q_lo; q0 < q_hi; q0 += kDistWords) {
             uint32_t bits[kDistWords], v[kDistWords], rb[kDistWords];
 #pragma unroll
-            for (uint32_t u = 0; u < kDistWords; ++u) {
-                // q < q_hi + 7 <= nw + 7 stays inside the LDS block (the
-                // rank tables follow the bits); words past q_hi count as empty
-                const uint32_t q = q0 + u, w = bm[q];
-                bits[u] = q < q_hi ? w : 0u;
-            }
+            for (uint32_t u = 0; u < kDistWords; ++u) bits[u] = bm[q0 + u];
 #pragma unroll
             for (uint32_t u = 0; u < kDistWords; ++u) {
                 const uint32_t o = bits[u] ? 32u * (q0 + u) + (uint32_t)__builtin_ctz(bits[u]) : 0u;
@@ -476,15 +455,17 @@ __global__ void __launch_bounds__(kRunThreads) k_run_lookup(Geo G, PartGeo PG, c
         e4[q] = make_uint4(pad, pad, pad, pad);
         jr[q] = 0;
     }
-    // A wavefront takes windows of 64 subgroups (lane r: run r of the
-    // window), kRunThreads subgroups apart.  The window's runs in this slice
+    // A wavefront takes windows of PG.win subgroups (lane r: run r of the
+    // window), 16 windows apart.  The window's runs in this slice
     // are one flat list of chunks (run after run), read in passes of kLookU
     // chunks per lane.  A live entry takes the next slot of its run from an
     // LDS counter (the order within a run is immaterial: the finalize only
     // counts), and its distance from LDS.
-    for (uint32_t s0 = s_lo + wv * 64u; s0 < s_hi; s0 += kRunThreads) {
+    const uint32_t win = PG.win;
+    for (uint32_t s0 = s_lo + wv * win; s0 < s_hi; s0 += (kRunThreads / 64u) * win) {
         uint32_t Sv = 0, len = 0;      // lane r: start (chunks) and length of run r
-        if (lane < s_hi - s0) {
+        const uint32_t nrun = min(win, s_hi - s0);
+        if (lane < nrun) {
             const size_t cell = (size_t)(s0 + lane) * row + b;
             Sv = tab16[2 * cell];
             len = (uint32_t)tab16[2 * cell + 2] - Sv;
@@ -569,7 +550,7 @@ __global__ void __launch_bounds__(kRunThreads) k_run_lookup(Geo G, PartGeo PG, c
             }
         }
         // live count of each run beside its start
-        if (lane < s_hi - s0) tab16[2 * ((size_t)(s0 + lane) * row + b) + 1] = (uint16_t)cnt[lane];
+        if (lane < nrun) tab16[2 * ((size_t)(s0 + lane) * row + b) + 1] = (uint16_t)cnt[lane];
     }
 }
 
@@ -690,12 +671,12 @@ __device__ __forceinline__ void window_counts(const Geo &G, const DevState *__re
 __host__ __device__ __forceinline__ uint32_t hist_row_words(uint32_t k) { return ((k + 2u) / 2u) | 1u; }
 
 // The outputs of hosts h0 .. h0 + nh - 1 from their histogram rows in LDS
-// (bins 0 .. k - 1 counted, bin k zero), by a workgroup of kFinThreads: the
+// (bins 0 .. k - 1 counted, bin k zero), by a workgroup of NT threads: the
 // closed form (and histograms), several windows, or the learned estimate.
 // Four threads share a host's row; a row's 16-bit halves are summed packed,
 // which cannot carry because all bins of a host add up to at most g < 2^16.
 // act: kFinMulti's window counts.  Starts after a barrier.
-template <int MODE>
+template <int MODE, uint32_t NT>
 __device__ __forceinline__ void finish_hosts(const Geo &G, const DevState *__restrict__ st, uint32_t *hist,
                                              uint32_t rowp, uint32_t nh, uint32_t h0, uint32_t kprime,
                                              float *__restrict__ est, uint32_t *__restrict__ live_out,
@@ -715,7 +696,7 @@ __device__ __forceinline__ void finish_hosts(const Geo &G, const DevState *__res
     };
     if constexpr (MODE == kFinClosedForm) {
         const uint64_t active_pool = pool_active(st, kprime);
-        for (uint32_t base = 0; base < nh; base += kFinThreads / 4) {
+        for (uint32_t base = 0; base < nh; base += NT / 4) {
             const bool valid = base + hh < nh;
             uint32_t *row = hist + (valid ? base + hh : 0u) * rowp;
             uint32_t acc = 0, j = qq;
@@ -735,13 +716,13 @@ __device__ __forceinline__ void finish_hosts(const Geo &G, const DevState *__res
             __syncthreads();
             const uint32_t kp1 = G.k + 1;
             uint32_t *out = hist_out + (size_t)h0 * kp1;
-            for (uint32_t q = t; q < nh * kp1; q += kFinThreads) {
+            for (uint32_t q = t; q < nh * kp1; q += NT) {
                 const uint32_t h = q / kp1, d = q - h * kp1;
                 out[q] = hist_bin(hist + h * rowp, d);
             }
         }
     } else if constexpr (MODE == kFinMulti) {
-        for (uint32_t base = 0; base < nh; base += kFinThreads / 4) {
+        for (uint32_t base = 0; base < nh; base += NT / 4) {
             const bool valid = base + hh < nh;
             const uint32_t *row = hist + (valid ? base + hh : 0u) * rowp;
             float *e = est + (size_t)(h0 + base + hh) * win.m;
@@ -758,14 +739,14 @@ __device__ __forceinline__ void finish_hosts(const Geo &G, const DevState *__res
             }
         }
     } else {
-        // Learned estimate, in groups of 64 hosts (16 per wavefront): the
-        // closed form for window k, then the network fed from the LDS rows.
+        // Learned estimate, 16 hosts per wavefront at a time: the closed form
+        // for window k, then the network fed from the LDS rows.
         // One 16-row staging tile per wavefront holds its features and then
         // its first layer's activations: the layer's inputs are in registers
         // (its products depend on them) before its outputs are written.
-        __shared__ __attribute__((aligned(16))) uint16_t xs_all[kFinThreads / 64][16 * mlp::LDS_STRIDE];
-        __shared__ float cf_s[kFinThreads / 4];
-        __shared__ uint32_t live_s[kFinThreads / 4];
+        __shared__ __attribute__((aligned(16))) uint16_t xs_all[NT / 64][16 * mlp::LDS_STRIDE];
+        __shared__ float cf_s[NT / 4];
+        __shared__ uint32_t live_s[NT / 4];
         const uint64_t active_pool = pool_active(st, G.k);
         const float occupancy = (float)active_pool / (float)G.N;
         const uint32_t w = t >> 6;
@@ -774,7 +755,7 @@ __device__ __forceinline__ void finish_hosts(const Geo &G, const DevState *__res
         if (t == 0) fell_wg = 0;
         __syncthreads();                  // (the loop below synchronizes wavefronts only with themselves)
         uint32_t fell_wave = 0;
-        for (uint32_t base = 0; base < nh; base += kFinThreads / 4) {
+        for (uint32_t base = 0; base < nh; base += NT / 4) {
             {   // live count and closed form of host base + hh, four threads a host
                 uint32_t live = 0;
                 if (base + hh < nh) {
@@ -804,7 +785,7 @@ __device__ __forceinline__ void finish_hosts(const Geo &G, const DevState *__res
             uint32_t zero = 0;
             asm volatile("" : "+s"(zero));
             const mlp::Packed *Pg = P + zero;
-            fell_wave += learned16(G, occupancy, hist + m0 * rowp, rowp, n16, cf_s + 16 * w, live_s + 16 * w,
+            fell_wave += learned16(G, occupancy, hist + (n16 ? m0 : 0u) * rowp, rowp, n16, cf_s + 16 * w, live_s + 16 * w,
                                        xs_all[w], xs_all[w], Pg, est + h0 + m0, geo_off);
             mlp::wave_sync();
         }
@@ -896,7 +877,13 @@ __global__ void __launch_bounds__(kFinThreads, 5) k_run_finalize(Geo G, PartGeo 
         }
     }
     __syncthreads();
-    finish_hosts<MODE>(G, st, hist, rowp, nh, h0, kprime, est, live_out, hist_out, win, act, P, cf_out);
+    finish_hosts<MODE, kFinThreads>(G, st, hist, rowp, nh, h0, kprime, est, live_out, hist_out, win, act, P, cf_out);
+}
+
+__global__ void __launch_bounds__(256) k_copy_hosts(const uint32_t *__restrict__ hosts, uint32_t n,
+                                                    uint32_t *__restrict__ out)
+{
+    for (uint64_t h = (uint64_t)blockIdx.x * 256 + threadIdx.x; h < n; h += (uint64_t)gridDim.x * 256) out[h] = hosts[h];
 }
 
 // ---------------------------------------------------------------------------
@@ -908,12 +895,18 @@ __global__ void __launch_bounds__(kFinThreads, 5) k_run_finalize(Geo G, PartGeo 
 // latency of those two gathers while there are few hosts: one host per
 // workgroup then (a wavefront per 64 hosts and a lane per host, as before,
 // took 64 serial rounds of bitmap gathers at g = 1024 and up to 1024 of
-// values: 509 us for 331 hosts on a 2^28 pool).
+// values: 509 us for 331 hosts on a 2^28 pool).  LOCAL as in k_estimate.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kGatherU = 8;
+// Lookups from which they are local.  8-bit pool of 2^20 ATs, g = 1024: 2M
+// lookups take 12 us either way (launch and latency), 8M 22 us direct and 16
+// local, 100M 309 and 106; on a 2^16 pool 16M take 22 and 14 us.
+constexpr uint64_t kLocalMin = 1u << 21;
+constexpr uint32_t kPartLog2 = 23;         // smallest pool (log2) whose lookups are partitioned
+constexpr uint64_t kPartMin = 3ull << 47;  // lookups times pool size from which they are
 
-template <int W, int MODE>
-__global__ void __launch_bounds__(kFinThreads) k_gather(Geo G, const uint8_t *__restrict__ pool,
+template <int W, int MODE, bool LOCAL>
+__global__ void __launch_bounds__(LOCAL ? kLocalThreads : kFinThreads) k_gather(Geo G, const uint8_t *__restrict__ pool,
                                                        const DevState *__restrict__ st,
                                                        const uint8_t *__restrict__ bitmap,
                                                        const uint32_t *__restrict__ hosts, uint32_t n, uint32_t lg,
@@ -922,37 +915,44 @@ __global__ void __launch_bounds__(kFinThreads) k_gather(Geo G, const uint8_t *__
                                                        Windows win, const mlp::Packed *__restrict__ P,
                                                        float *__restrict__ cf_out)
 {
-    extern __shared__ __attribute__((aligned(16))) uint32_t hist[];   // [2^lg][rowp] packed 16-bit bins
+    // LOCAL: the bitmap; then [2^lg][rowp] packed 16-bit bins
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     __shared__ unsigned long long act[MODE == kFinMulti ? kMaxWindows : 1u];
+    constexpr uint32_t NT = LOCAL ? kLocalThreads : kFinThreads;
+    uint32_t *hist = lds + (LOCAL ? (G.c > 7 ? 1u << (G.c - 5) : 4u) : 0u);
+    const void *bm = LOCAL ? static_cast<const void *>(lds) : bitmap;
     const uint32_t t = threadIdx.x;
-    const uint32_t h0 = blockIdx.x << lg, nh = min(1u << lg, n - h0);
-    for (uint32_t q = t; q < nh * rowp; q += kFinThreads) hist[q] = 0;
+    if constexpr (LOCAL) copy_bitmap(G, bitmap, lds);
     if constexpr (MODE == kFinMulti)
         if (t < 64) window_counts(G, st, win, act);
-    const uint32_t lanes = kFinThreads >> lg, sub = t & (lanes - 1u), h = t / lanes;
+    const uint32_t lanes = NT >> lg, sub = t & (lanes - 1u), h = t / lanes;
     const uint32_t bact0 = st->bact0;
-    const uint32_t key = host_key(G, hosts[h0 + min(h, nh - 1u)]);
     uint32_t *row = hist + h * rowp;
-    __syncthreads();
-    if (h < nh)
-        for (uint32_t i0 = sub; i0 < G.g; i0 += kGatherU * lanes) {
-            uint32_t pid[kGatherU], bit[kGatherU], val[kGatherU];
+    for (uint64_t h0 = (uint64_t)blockIdx.x << lg; h0 < n; h0 += (uint64_t)gridDim.x << lg) {
+        const uint32_t nh = (uint32_t)min((uint64_t)1u << lg, n - h0);
+        for (uint32_t q = t; q < nh * rowp; q += NT) hist[q] = 0;
+        const uint32_t key = host_key(G, hosts[h0 + min(h, nh - 1u)]);
+        __syncthreads();
+        if (h < nh)
+            for (uint32_t i0 = sub; i0 < G.g; i0 += kGatherU * lanes) {
+                uint32_t pid[kGatherU], bit[kGatherU], val[kGatherU];
 #pragma unroll
-            for (uint32_t u = 0; u < kGatherU; ++u) pid[u] = vat_pid(G, key, i0 + u * lanes);
+                for (uint32_t u = 0; u < kGatherU; ++u) pid[u] = vat_pid(G, key, i0 + u * lanes);
 #pragma unroll
-            for (uint32_t u = 0; u < kGatherU; ++u) bit[u] = i0 + u * lanes < G.g ? bitmap[pid[u] >> 3] : 0u;
+                for (uint32_t u = 0; u < kGatherU; ++u)
+                    bit[u] = i0 + u * lanes < G.g ? active_bit<LOCAL>(bm, pid[u]) : 0u;
 #pragma unroll
-            for (uint32_t u = 0; u < kGatherU; ++u) {
-                bit[u] = (bit[u] >> (pid[u] & 7u)) & 1u;
-                val[u] = bit[u] ? load_at<W>(pool, pid[u], G.wb) : 0u;
+                for (uint32_t u = 0; u < kGatherU; ++u) val[u] = bit[u] ? load_at<W>(pool, pid[u], G.wb) : 0u;
+#pragma unroll
+                for (uint32_t u = 0; u < kGatherU; ++u)
+                    if (bit[u]) {
+                        const uint32_t d = value_dist(G, bact0, pid[u], val[u]);
+                        if (d < G.k) atomicAdd(&row[d >> 1], 1u << ((d & 1u) << 4));
+                    }
             }
-#pragma unroll
-            for (uint32_t u = 0; u < kGatherU; ++u)
-                if (bit[u]) {
-                    const uint32_t d = value_dist(G, bact0, pid[u], val[u]);
-                    if (d < G.k) atomicAdd(&row[d >> 1], 1u << ((d & 1u) << 4));
-                }
-        }
-    __syncthreads();
-    finish_hosts<MODE>(G, st, hist, rowp, nh, h0, kprime, est, live_out, hist_out, win, act, P, cf_out);
+        __syncthreads();
+        finish_hosts<MODE, NT>(G, st, hist, rowp, nh, (uint32_t)h0, kprime, est, live_out, hist_out, win, act, P,
+                               cf_out);
+        __syncthreads();
+    }
 }

@@ -62,3 +62,46 @@ def test_direct_gather_shapes(c, w, k, g, n_hosts, b):
         for j, kp in enumerate(kps):
             one, _, _ = gpu.estimate(hosts, kprime=kp)
             np.testing.assert_array_equal(est[:, j], one.cpu().numpy().astype(np.float64))
+
+
+# Which path answers depends on lookups and pool size: bitmaps copied to LDS
+# (up to 2^20 ATs, from 2M lookups), partitioned lookups (from 2^23 ATs), both
+# sides of the rules; subgroups of even size, windows of few subgroups.
+@pytest.mark.parametrize("c,w,k,g,n_hosts", [
+    (5, 7, 9, 1024, 2100), (20, 8, 60, 1024, 2048), (16, 10, 300, 2048, 1500), (18, 4, 7, 100, 30_001),
+    (20, 16, 256, 33, 70_000), (19, 8, 61, 1000, 2500), (23, 8, 60, 1024, 48_000), (23, 8, 60, 2048, 24_577),
+    (26, 8, 61, 1024, 6_200), (27, 4, 7, 64, 49_153), (28, 8, 60, 1024, 1_537), (28, 10, 300, 100, 20_000)])
+def test_estimate_routes(c, w, k, g, n_hosts):
+    from paper_1812_00282_amd import _lib, learned as L
+
+    rng = np.random.default_rng(c * 1000 + g)
+    cfg = Config(c, w, k, g, seed_a=5, seed_b=6)
+    gpu, ref = _pair(cfg)
+    hosts = rng.integers(0, 2**32, n_hosts, dtype=np.uint64).astype(np.uint32)
+    some = hosts[rng.permutation(n_hosts)[:200]]
+    for t in range(4):
+        p = _stream(rng, 60_000 if c > 10 else 50, some if c > 20 else hosts, 2**32)
+        gpu.ingest(p)
+        ref.ingest(p)
+        gpu.close_slice()
+        ref.close_slice()
+    gpu.plan(hosts)
+    for kp in sorted({1, 3, k}):
+        want = kp == k
+        _, r_live, r_hist = ref.estimate(hosts, kprime=kp, want_hist=want)
+        one, live, hist = gpu.estimate(hosts, kprime=kp, want_hist=want, partitioned=True)
+        est, plive, phist = gpu.estimate_run(kp, want_hist=want)
+        np.testing.assert_array_equal(_u32(live), r_live)
+        np.testing.assert_array_equal(_u32(plive), r_live)
+        assert torch.equal(one, est)
+        if want:
+            np.testing.assert_array_equal(_u32(hist), r_hist)
+            assert torch.equal(hist, phist)
+        dlive = gpu.estimate(hosts, kprime=kp)[1]
+        assert torch.equal(live, dlive)
+    if k + 3 <= _lib.MLP_FEATURES:
+        gen = torch.Generator().manual_seed(k)
+        wts = L.pack((torch.randn(_lib.MLP_PARAMS, generator=gen) * 0.05).cuda(), L.new_weights())
+        d, dcf = L.estimate_learned(gpu, hosts, wts)
+        for e, cf in (L.estimate_learned(gpu, hosts, wts, partitioned=True), L.estimate_learned_run(gpu, wts)):
+            assert torch.equal(d, e) and torch.equal(dcf, cf)
