@@ -64,10 +64,12 @@ static size_t bitmap_bytes(uint64_t N)
     return bm < 16 ? 16 : bm;
 }
 
-// After the bitmap: kCensusCopies partial censuses (k counters each) that
-// k_census8's workgroups add into, so that no counter takes an atomic from
-// every workgroup; k_census_fold then adds them to the census and clears
-// them (they are zero between censuses).
+// After the bitmap: kCensusCopies partial censuses (k counters each) that the
+// census workgroups add into, so that no counter takes an atomic from every
+// workgroup (they run one after the other, about 12 ns each: 2048 workgroups
+// on the two counters of a 2^26 nibble pool with k = 2 took 23 us);
+// k_census_fold then adds them to the census and clears them (they are zero
+// between censuses).
 constexpr uint32_t kCensusCopies = 16;
 
 static size_t copies_offset(uint32_t k, uint64_t N)
@@ -147,6 +149,15 @@ int make_geo(const vate_params *p, Geo *G, const char **why)
 // ---------------------------------------------------------------------------
 // Container access.  AT p sits at bits [p*W, p*W+W) of the pool, little-endian.
 // ---------------------------------------------------------------------------
+// Adds a census workgroup's LDS histogram to copy blockIdx mod kCensusCopies
+// (k_census_fold adds the copies to the census).
+__device__ __forceinline__ void census_flush(const Geo &G, const uint32_t *hist, unsigned long long *__restrict__ copies)
+{
+    unsigned long long *mine = copies + (size_t)(blockIdx.x % kCensusCopies) * G.k;
+    for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x)
+        if (hist[d]) atomicAdd(&mine[d], (unsigned long long)hist[d]);
+}
+
 #include "vate_exact.h"
 
 // W = 0: the exact width wb (counters packed back to back in 32-bit words).
@@ -438,9 +449,11 @@ __device__ __forceinline__ uint32_t census_chunk_fast(const Geo &G, const uint4 
     return census_chunk<W>(G, v, ch, bact0, hist, census);
 }
 
+// Nibbles and 16-bit counters; byte counters take k_census8.
 template <int W>
 __global__ void __launch_bounds__(256) k_census(Geo G, const uint4 *__restrict__ pool4, uint64_t nchunks,
-                                                DevState *__restrict__ st, uint8_t *__restrict__ bitmap)
+                                                DevState *__restrict__ st, uint8_t *__restrict__ bitmap,
+                                                unsigned long long *__restrict__ copies)
 {
     __shared__ uint32_t hist[kCensusLdsBins];
     const bool lds = G.k <= kCensusLdsBins;
@@ -467,12 +480,10 @@ __global__ void __launch_bounds__(256) k_census(Geo G, const uint4 *__restrict__
         }
     }
     __syncthreads();
-    if (lds)
-        for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x)
-            if (hist[d]) atomicAdd(&census_of(st)[d], (unsigned long long)hist[d]);
+    if (lds) census_flush(G, hist, copies);
 }
 
-// k_census8: the census of byte counters with k <= kCensus8Bins.  In steady
+// k_census8: the census of byte counters (k <= 255).  In steady
 // state only a few per cent of the chunks hold an active AT, but nearly every
 // wavefront has one among its 64, so a per-lane test would run the packed
 // activity test on all of them.  Here each wavefront stages the busy chunks
@@ -583,11 +594,7 @@ __global__ void __launch_bounds__(256) k_census8(Geo G, const uint4 *__restrict_
             if (c0 + u < nchunks) bm16[c0 + u] = (uint16_t)bits[u];
     }
     __syncthreads();
-    // Flush into copy blockIdx mod kCensusCopies (k_census_fold adds the
-    // copies to the census).
-    unsigned long long *mine = copies + (size_t)(blockIdx.x % kCensusCopies) * G.k;
-    for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x)
-        if (L.hist[d]) atomicAdd(&mine[d], (unsigned long long)L.hist[d]);
+    census_flush(G, L.hist, copies);
 }
 
 __global__ void __launch_bounds__(256) k_census_fold(Geo G, DevState *__restrict__ st,
@@ -830,6 +837,8 @@ __device__ __forceinline__ void preserve_chunk(const Geo &G, uint4 *__restrict__
     if (ch >= (second ? c1hi : c0hi)) return;
     if (second && ch >= c0lo && ch < c0hi) return;
     uint4 v = pool4[ch];
+    const uint32_t pat = replicate<W>(G.twok);       // inactive ATs stay as they are (most chunks)
+    if (v.x == pat && v.y == pat && v.z == pat && v.w == pat) return;
     bool changed = false;
     for (uint32_t e = 0; e < E; ++e) {
         const uint64_t p = ch * E + e;
@@ -853,7 +862,10 @@ template <int W>
 __global__ void __launch_bounds__(256) k_preserve(Geo G, uint4 *__restrict__ pool4,
                                                   const DevState *__restrict__ st, uint64_t max_chunks)
 {
-    preserve_chunk<W>(G, pool4, st->bact0, (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, max_chunks);
+    const uint32_t bact0 = st->bact0;
+    for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < 2 * max_chunks;
+         j += (uint64_t)gridDim.x * blockDim.x)
+        preserve_chunk<W>(G, pool4, bact0, j, max_chunks);
 }
 
 // ---------------------------------------------------------------------------
@@ -953,12 +965,35 @@ static auto by_width(uint32_t w, F &&f)
     return f(std::integral_constant<int, 0>{});
 }
 
+// Exact widths as a compile-time constant for the streaming kernels.
+template <class F>
+static void by_exact_width(uint32_t w, F &&f)
+{
+    using std::integral_constant;
+    switch (w) {
+    case 1: return f(integral_constant<int, 1>{});
+    case 2: return f(integral_constant<int, 2>{});
+    case 3: return f(integral_constant<int, 3>{});
+    case 5: return f(integral_constant<int, 5>{});
+    case 6: return f(integral_constant<int, 6>{});
+    case 7: return f(integral_constant<int, 7>{});
+    case 9: return f(integral_constant<int, 9>{});
+    case 10: return f(integral_constant<int, 10>{});
+    case 11: return f(integral_constant<int, 11>{});
+    case 12: return f(integral_constant<int, 12>{});
+    case 13: return f(integral_constant<int, 13>{});
+    case 14: return f(integral_constant<int, 14>{});
+    default: return f(integral_constant<int, 15>{});
+    }
+}
+
 template <int W>
 static void launch_init(vate_sketch *s, hipStream_t st)
 {
     if constexpr (W == 0) {
         const uint64_t ng = s->G.N / 32;
-        k_init_x<<<grid_for(ng, 256, 8192), 256, 0, st>>>(s->G, reinterpret_cast<uint32_t *>(s->pool), ng, s->st);
+        k_init_x<<<grid_for(ng, 256, 8192), 256, 0, st>>>(s->G, reinterpret_cast<uint32_t *>(s->pool), ng, s->st,
+                                                            s->copies);
     } else {
         uint64_t nch = s->pool_bytes / 16;
         k_init<W><<<grid_for(nch, 256, 8192), 256, 0, st>>>(s->G, reinterpret_cast<uint4 *>(s->pool), nch, s->st,
@@ -971,19 +1006,21 @@ static void launch_census(vate_sketch *s, hipStream_t st)
 {
     if constexpr (W == 0) {
         const uint64_t ng = s->G.N / 32;
-        k_census_x<<<grid_for(ng, 256, 4096), 256, 0, st>>>(s->G, reinterpret_cast<const uint32_t *>(s->pool), ng,
-                                                             s->st, s->bitmap);
+        by_exact_width(s->p.width, [&](auto WB) {
+            k_census_x<decltype(WB)::value><<<grid_for(ng, 256, 8u * s->n_cu), 256, 0, st>>>(
+                s->G, reinterpret_cast<const uint32_t *>(s->pool), ng, s->st, s->bitmap, s->copies);
+        });
     } else {
         uint64_t nch = s->pool_bytes / 16;
-        if (W == 8 && s->G.k <= kCensus8Bins) {
+        if constexpr (W == 8)         // k <= 255 (2^8 >= k + 1)
             k_census8<<<grid_for(nch, 256 * kCensus8U, 4096), 256, 0, st>>>(
                 s->G, reinterpret_cast<const uint4 *>(s->pool), nch, s->st, s->bitmap, s->copies);
-            k_census_fold<<<1, 256, 0, st>>>(s->G, s->st, s->copies);
-        } else {
+        else
             k_census<W><<<grid_for(nch, 256 * 4, 2048), 256, 0, st>>>(s->G, reinterpret_cast<const uint4 *>(s->pool),
-                                                                       nch, s->st, s->bitmap);
-        }
+                                                                       nch, s->st, s->bitmap, s->copies);
     }
+    if (s->G.k <= kCensusLdsBins)      // longer windows are counted straight into the census
+        k_census_fold<<<(s->G.k + 255) / 256, 256, 0, st>>>(s->G, s->st, s->copies);
 }
 
 template <int W>
@@ -991,10 +1028,12 @@ static void launch_preserve(vate_sketch *s, hipStream_t st)
 {
     uint64_t threads = 2 * s->max_block_chunks;
     if constexpr (W == 0)
-        k_preserve_x<<<grid_for(threads, 256, 1u << 30), 256, 0, st>>>(s->G, reinterpret_cast<uint32_t *>(s->pool),
-                                                                        s->st, s->max_block_chunks);
+        by_exact_width(s->p.width, [&](auto WB) {
+            k_preserve_x<decltype(WB)::value><<<grid_for(threads, 256, 8u * s->n_cu), 256, 0, st>>>(
+                s->G, reinterpret_cast<uint32_t *>(s->pool), s->st, s->max_block_chunks);
+        });
     else
-        k_preserve<W><<<grid_for(threads, 256, 1u << 30), 256, 0, st>>>(s->G, reinterpret_cast<uint4 *>(s->pool),
+        k_preserve<W><<<grid_for(threads, 256, 8u * s->n_cu), 256, 0, st>>>(s->G, reinterpret_cast<uint4 *>(s->pool),
                                                                          s->st, s->max_block_chunks);
 }
 
@@ -1003,7 +1042,10 @@ static void launch_dr_maintain(vate_sketch *s, hipStream_t st)
 {
     if constexpr (W == 0) {
         const uint64_t ng = s->G.N / 32;
-        k_dr_maintain_x<<<grid_for(ng, 256, 8192), 256, 0, st>>>(s->G, reinterpret_cast<uint32_t *>(s->pool), ng);
+        by_exact_width(s->p.width, [&](auto WB) {
+            k_dr_maintain_x<decltype(WB)::value><<<grid_for(ng, 256, 8192), 256, 0, st>>>(
+                s->G, reinterpret_cast<uint32_t *>(s->pool), ng);
+        });
     } else {
         const uint64_t nch = s->pool_bytes / 16;
         k_dr_maintain<W><<<grid_for(nch, 256, 8192), 256, 0, st>>>(s->G, reinterpret_cast<uint4 *>(s->pool), nch);

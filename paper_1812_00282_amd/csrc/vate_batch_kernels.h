@@ -129,14 +129,14 @@ __global__ void __launch_bounds__(256) k_batch_preserve(const BatchItem *__restr
         const uint32_t bact0 = it.st->bact0;
         if (it.G.dr) {
             if (j < it.nchunks) {
-                if (it.width == 0) dr_maintain_group_x(it.G, pool32, j);
+                if (it.width == 0) dr_maintain_group_x<0>(it.G, pool32, j);
                 else if (it.width == 4) dr_maintain_chunk<4>(it.G, pool4, j);
                 else if (it.width == 8) dr_maintain_chunk<8>(it.G, pool4, j);
                 else dr_maintain_chunk<16>(it.G, pool4, j);
             }
             continue;
         }
-        if (it.width == 0) preserve_group_x(it.G, pool32, bact0, j, it.max_block_chunks);
+        if (it.width == 0) preserve_group_x<0>(it.G, pool32, bact0, j, it.max_block_chunks);
         else if (it.width == 4) preserve_chunk<4>(it.G, pool4, bact0, j, it.max_block_chunks);
         else if (it.width == 8) preserve_chunk<8>(it.G, pool4, bact0, j, it.max_block_chunks);
         else preserve_chunk<16>(it.G, pool4, bact0, j, it.max_block_chunks);
@@ -214,7 +214,7 @@ __device__ __forceinline__ void batch_census_groups(const BatchItem &it, uint64_
     const uint32_t *pool32 = reinterpret_cast<const uint32_t *>(it.pool);
     uint32_t *h = it.G.k <= kBatchCensusBins ? hist : nullptr;
     for (uint64_t gi = c0 + threadIdx.x; gi < c1; gi += blockDim.x)
-        census_group_x(it.G, pool32, gi, bact0, h, census_of(it.st), it.bitmap);
+        census_group_x<0>(it.G, pool32, gi, bact0, h, census_of(it.st), it.bitmap);
 }
 
 // The LDS histogram belongs to one sketch at a time: it is flushed into that

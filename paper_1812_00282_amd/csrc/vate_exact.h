@@ -3,12 +3,13 @@
 // (Sec. 3: 2k+1 values per AT; Sec. 5: 10-bit ATs at k = 300).  Counter p
 // sits at bits [p w, (p+1) w) of the pool read as little-endian 32-bit words,
 // so a group of 32 counters fills exactly w words and starts on a word.
-// Included into vate.hip inside namespace vate; the width w = G.wb is a
-// run-time value (template width 0 selects these paths).
+// Included into vate.hip inside namespace vate; single counters are read and
+// set with the width w = G.wb at run time (template width 0 of the lookups).
 //
-// Streaming kernels (init, census, preservation, DR maintenance) give each
-// thread whole groups: the group's w words are read in order through a
-// 64-bit bit buffer and, where counters change, written back the same way.
+// Streaming kernels (census, preservation, DR maintenance) give each thread
+// whole groups, read and where counters change written back by kernels with
+// the width at compile time; init and the batched kernels, which meet any mix
+// of widths, go through a 64-bit bit buffer (template width 0).
 // SetAT writes the w bits of one counter, which may straddle two words, with
 // a compare-and-swap on each word that does not hold them yet: the bits of
 // neighbouring counters are never changed, and every writer of a counter
@@ -57,104 +58,154 @@ __device__ __forceinline__ void set_x(uint32_t *__restrict__ words, uint64_t pid
     if (n0 < wb) set_bits(p + 1, low_mask(wb - n0), val >> n0);
 }
 
-// The 32 counters of group gi (its wb words in order).
+// The 32 counters of a group (its wb words in order).  WB: the width at
+// compile time, so that every shift is a constant and the words are loaded up
+// to 16 bytes at a time (4-byte aligned); WB = 0: any width, through a bit
+// buffer.
+template <int WB>
 __device__ __forceinline__ void read_group(const uint32_t *__restrict__ src, uint32_t wb, uint32_t vals[32])
 {
-    uint64_t buf = 0;
-    uint32_t have = 0;
-    const uint32_t m = low_mask(wb);
+    if constexpr (WB > 0) {
+        uint32_t w[WB];
+        __builtin_memcpy(w, src, sizeof w);
+        constexpr uint32_t m = (1u << WB) - 1u;
 #pragma unroll
-    for (int e = 0; e < 32; ++e) {
-        if (have < wb) {
-            buf |= (uint64_t)(*src++) << have;
-            have += 32;
+        for (int e = 0; e < 32; ++e) {
+            const int o = e * WB, i = o >> 5, sh = o & 31;
+            vals[e] = (sh + WB <= 32 ? w[i] >> sh : __builtin_amdgcn_alignbit(w[(i + 1) % WB], w[i], sh)) & m;
         }
-        vals[e] = (uint32_t)buf & m;
-        buf >>= wb;
-        have -= wb;
+    } else {
+        uint64_t buf = 0;
+        uint32_t have = 0;
+        const uint32_t m = low_mask(wb);
+#pragma unroll
+        for (int e = 0; e < 32; ++e) {
+            if (have < wb) {
+                buf |= (uint64_t)(*src++) << have;
+                have += 32;
+            }
+            vals[e] = (uint32_t)buf & m;
+            buf >>= wb;
+            have -= wb;
+        }
     }
 }
 
+template <int WB>
 __device__ __forceinline__ void write_group(uint32_t *__restrict__ dst, uint32_t wb, const uint32_t vals[32])
 {
-    uint64_t buf = 0;
-    uint32_t have = 0;
+    if constexpr (WB > 0) {
+        uint32_t w[WB] = {};
 #pragma unroll
-    for (int e = 0; e < 32; ++e) {
-        buf |= (uint64_t)vals[e] << have;
-        have += wb;
-        if (have >= 32) {
-            *dst++ = (uint32_t)buf;
-            buf >>= 32;
-            have -= 32;
+        for (int e = 0; e < 32; ++e) {
+            const int o = e * WB, i = o >> 5, sh = o & 31;
+            w[i] |= vals[e] << sh;
+            if (sh + WB > 32) w[(i + 1) % WB] |= vals[e] >> ((32 - sh) & 31);
+        }
+        __builtin_memcpy(dst, w, sizeof w);
+    } else {
+        uint64_t buf = 0;
+        uint32_t have = 0;
+#pragma unroll
+        for (int e = 0; e < 32; ++e) {
+            buf |= (uint64_t)vals[e] << have;
+            have += wb;
+            if (have >= 32) {
+                *dst++ = (uint32_t)buf;
+                buf >>= 32;
+                have -= 32;
+            }
         }
     }
 }
 
 // InitAT on every counter, clock and census reset.
 __global__ void __launch_bounds__(256) k_init_x(Geo G, uint32_t *__restrict__ pool32, uint64_t ngroups,
-                                                DevState *__restrict__ st)
+                                                DevState *__restrict__ st, unsigned long long *__restrict__ copies)
 {
     uint32_t vals[32];
 #pragma unroll
     for (int e = 0; e < 32; ++e) vals[e] = inactive_value(G);
     for (uint64_t gi = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; gi < ngroups;
          gi += (uint64_t)gridDim.x * blockDim.x)
-        write_group(pool32 + gi * G.wb, G.wb, vals);
+        write_group<0>(pool32 + gi * G.wb, G.wb, vals);
     if (blockIdx.x == 0) {
         if (threadIdx.x == 0) {
             st->t = 0;
             st->bact0 = 0;
         }
         for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x) census_of(st)[d] = 0;
+        for (uint32_t d = threadIdx.x; d < kCensusCopies * G.k; d += blockDim.x) copies[d] = 0;
     }
 }
 
 // Census of group gi and its activity bitmap word: distances below k are
-// counted into hist (LDS) when given, else into the census.
+// counted into hist (LDS) when given, else into the census.  A group inside
+// one block (nearly all of them) has one ACT: its counters are tested without
+// a branch, and only the active ones take the histogram's LDS atomic.
+template <int WB>
 __device__ __forceinline__ void census_group_x(const Geo &G, const uint32_t *__restrict__ pool32, uint64_t gi,
                                                uint32_t bact0, uint32_t *hist, unsigned long long *census,
                                                uint8_t *__restrict__ bitmap)
 {
     const uint32_t inact = inactive_value(G);
     uint32_t vals[32];
-    read_group(pool32 + gi * G.wb, G.wb, vals);
+    read_group<WB>(pool32 + gi * G.wb, G.wb, vals);
     const uint64_t p0 = gi * 32;
     uint32_t bid0 = 0, act0 = 0;
     uint64_t next = 0;
+    bool one = G.dr != 0;
     if (G.fast_blocks && !G.dr) {
         bid0 = block_of(G, (uint32_t)p0);
         act0 = block_act(G, bact0, bid0);
         next = block_start(G, bid0 + 1);
+        one = p0 + 32 <= next;
     }
     uint32_t bits = 0;
+    if (one && hist) {
+        const uint32_t top = act0 + G.twok;
 #pragma unroll
-    for (int e = 0; e < 32; ++e) {
-        const uint32_t val = vals[e];
-        if (val == inact) continue;
-        uint32_t d;
-        if (G.dr) {
-            d = val;
-        } else {
-            uint32_t act;
-            if (G.fast_blocks)
-                act = p0 + e < next ? act0 : block_act(G, bact0, bid0 + 1);
-            else
-                act = block_act(G, bact0, block_of(G, (uint32_t)(p0 + e)));
-            d = at_dist(G, act, val);
+        for (int e = 0; e < 32; ++e) {
+            const uint32_t u = top - vals[e];                       // ACT + 2k - value
+            const uint32_t d = G.dr ? vals[e] : min(u, u - G.twok); // the second wraps when u < 2k
+            if (vals[e] != inact && d < G.k) {
+                bits |= 1u << e;
+                atomicAdd(&hist[d], 1u);
+            }
         }
-        if (d < G.k) {
-            bits |= 1u << e;
-            if (hist) atomicAdd(&hist[d], 1u);
-            else atomicAdd(&census[d], 1ull);
+    } else {
+        for (int e = 0; e < 32; ++e) {
+            const uint32_t val = vals[e];
+            if (val == inact) continue;
+            uint32_t d;
+            if (G.dr) {
+                d = val;
+            } else {
+                uint32_t act;
+                if (G.fast_blocks)
+                    act = p0 + e < next ? act0 : block_act(G, bact0, bid0 + 1);
+                else
+                    act = block_act(G, bact0, block_of(G, (uint32_t)(p0 + e)));
+                d = at_dist(G, act, val);
+            }
+            if (d < G.k) {
+                bits |= 1u << e;
+                if (hist) atomicAdd(&hist[d], 1u);
+                else atomicAdd(&census[d], 1ull);
+            }
         }
     }
     reinterpret_cast<uint32_t *>(bitmap)[gi] = bits;
 }
 
-// Census and activity bitmap (one bitmap word per group).
+// Census and activity bitmap (one bitmap word per group).  Bound by its
+// instructions: with a group's shifts and word indexes known at compile time
+// 2^27 10-bit ATs of steady traffic (k = 300, 168 MB) take 44 us instead of
+// 158, 2^28 9-bit DRs (302 MB) 81 instead of 196.
+template <int WB>
 __global__ void __launch_bounds__(256) k_census_x(Geo G, const uint32_t *__restrict__ pool32, uint64_t ngroups,
-                                                  DevState *__restrict__ st, uint8_t *__restrict__ bitmap)
+                                                  DevState *__restrict__ st, uint8_t *__restrict__ bitmap,
+                                                  unsigned long long *__restrict__ copies)
 {
     __shared__ uint32_t hist[kCensusLdsBins];
     const bool lds = G.k <= kCensusLdsBins;
@@ -164,16 +215,15 @@ __global__ void __launch_bounds__(256) k_census_x(Geo G, const uint32_t *__restr
     const uint32_t bact0 = st->bact0;
     for (uint64_t gi = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; gi < ngroups;
          gi += (uint64_t)gridDim.x * blockDim.x)
-        census_group_x(G, pool32, gi, bact0, lds ? hist : nullptr, census_of(st), bitmap);
+        census_group_x<WB>(G, pool32, gi, bact0, lds ? hist : nullptr, census_of(st), bitmap);
     __syncthreads();
-    if (lds)
-        for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x)
-            if (hist[d]) atomicAdd(&census_of(st)[d], (unsigned long long)hist[d]);
+    if (lds) census_flush(G, hist, copies);
 }
 
 // Alg. 3 on the two blocks whose ACT is 0 or k; thread j < max_groups takes
 // a group of the first block, the rest groups of the second (a group in both
 // ranges is handled once, by the first).
+template <int WB>
 __device__ __forceinline__ void preserve_group_x(const Geo &G, uint32_t *__restrict__ pool32, uint32_t bact0,
                                                  uint64_t j, uint64_t max_groups)
 {
@@ -190,7 +240,7 @@ __device__ __forceinline__ void preserve_group_x(const Geo &G, uint32_t *__restr
     if (second && gi >= g0lo && gi < g0hi) return;
     uint32_t *words = pool32 + gi * G.wb;
     uint32_t vals[32];
-    read_group(words, G.wb, vals);
+    read_group<WB>(words, G.wb, vals);
     bool changed = false;
 #pragma unroll
     for (int e = 0; e < 32; ++e) {
@@ -208,34 +258,42 @@ __device__ __forceinline__ void preserve_group_x(const Geo &G, uint32_t *__restr
             changed = true;
         }
     }
-    if (changed) write_group(words, G.wb, vals);
+    if (changed) write_group<WB>(words, G.wb, vals);
 }
 
+template <int WB>
 __global__ void __launch_bounds__(256) k_preserve_x(Geo G, uint32_t *__restrict__ pool32,
                                                     const DevState *__restrict__ st, uint64_t max_groups)
 {
-    preserve_group_x(G, pool32, st->bact0, (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, max_groups);
+    const uint32_t bact0 = st->bact0;
+    for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < 2 * max_groups;
+         j += (uint64_t)gridDim.x * blockDim.x)
+        preserve_group_x<WB>(G, pool32, bact0, j, max_groups);
 }
 
-// DR maintenance: every counter of group gi grows by one, saturating at k.
+// DR maintenance: every counter of group gi grows by one, saturating at k
+// (2^28 9-bit DRs, 302 MB read and what changed written: 87 us, with run-time
+// shifts 187).
+template <int WB>
 __device__ __forceinline__ void dr_maintain_group_x(const Geo &G, uint32_t *__restrict__ pool32, uint64_t gi)
 {
     uint32_t *words = pool32 + gi * G.wb;
     uint32_t vals[32];
-    read_group(words, G.wb, vals);
-    bool changed = false;
+    read_group<WB>(words, G.wb, vals);
+    uint32_t changed = 0;
 #pragma unroll
-    for (int e = 0; e < 32; ++e)
-        if (vals[e] < G.k) {
-            ++vals[e];
-            changed = true;
-        }
-    if (changed) write_group(words, G.wb, vals);
+    for (int e = 0; e < 32; ++e) {
+        const uint32_t up = vals[e] < G.k ? 1u : 0u;
+        vals[e] += up;
+        changed |= up;
+    }
+    if (changed) write_group<WB>(words, G.wb, vals);
 }
 
+template <int WB>
 __global__ void __launch_bounds__(256) k_dr_maintain_x(Geo G, uint32_t *__restrict__ pool32, uint64_t ngroups)
 {
     for (uint64_t gi = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; gi < ngroups;
          gi += (uint64_t)gridDim.x * blockDim.x)
-        dr_maintain_group_x(G, pool32, gi);
+        dr_maintain_group_x<WB>(G, pool32, gi);
 }

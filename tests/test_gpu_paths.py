@@ -105,3 +105,28 @@ def test_estimate_routes(c, w, k, g, n_hosts):
         d, dcf = L.estimate_learned(gpu, hosts, wts)
         for e, cf in (L.estimate_learned(gpu, hosts, wts, partitioned=True), L.estimate_learned_run(gpu, wts)):
             assert torch.equal(d, e) and torch.equal(dcf, cf)
+
+
+# Streaming kernels with the exact width at compile time: every width, a pool
+# of one group and one with a ragged last round, blocks shorter than a group
+# and blocks that cut groups, both counters, census and bitmap (live counts).
+@pytest.mark.parametrize("w", [1, 2, 3, 5, 6, 7, 9, 10, 11, 12, 13, 14, 15])
+@pytest.mark.parametrize("counter,c", [(0, 5), (0, 14), (1, 5), (1, 14)])
+def test_exact_width_streams(w, counter, c):
+    k = (1 << w) - 1 if counter else ((1 << w) - 1) // 2
+    if k < 1:
+        pytest.skip("a 1-bit AT has no window")
+    k = min(k, 16 if c == 5 else 5000)
+    rng = np.random.default_rng(w * 10 + counter)
+    gpu, ref = _pair(Config(c, w, k, 64, seed_a=1, seed_b=2, counter=counter, partition=w & 1))
+    hosts = rng.integers(0, 2**32, 300, dtype=np.uint64).astype(np.uint32)
+    for t in range(min(2 * k + 3, 40)):
+        p = _stream(rng, 40 if c == 5 else 2000, hosts, 5000)
+        gpu.ingest(p)
+        ref.ingest(p)
+        gpu.close_slice()
+        ref.close_slice()
+        if t % 4 == 3 or t < 3:
+            _check_state(gpu, ref, f"slice {t}")
+            np.testing.assert_array_equal(gpu.census(), ref.census())
+            np.testing.assert_array_equal(_u32(gpu.estimate(hosts)[1]), ref.estimate(hosts)[1])
