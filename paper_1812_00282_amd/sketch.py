@@ -16,8 +16,11 @@ from ._lib import VateParams, check, lib
 
 
 def _stream_handle(stream: torch.cuda.Stream | None) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # the current stream's handle itself (0.4 us): torch.cuda.current_stream()
+    # builds a Stream object around it first, 2.8 us of a call's 10
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def as_u32_tensor(x, device) -> torch.Tensor:
