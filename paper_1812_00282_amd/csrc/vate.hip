@@ -33,7 +33,8 @@ struct DevState {
     unsigned long long t;        // current slice
     uint32_t bact0;              // ACT of block 0 (Eq. 7)
     uint32_t pad0;
-    unsigned long long pad1[2];
+    uint32_t ticket[2];          // workgroups done (k_preserve, census), zero between kernels
+    uint32_t pad1[2];
 };
 constexpr size_t kStateHeader = sizeof(DevState);
 static_assert(kStateHeader == 32, "state header layout");
@@ -149,14 +150,71 @@ int make_geo(const vate_params *p, Geo *G, const char **why)
 // ---------------------------------------------------------------------------
 // Container access.  AT p sits at bits [p*W, p*W+W) of the pool, little-endian.
 // ---------------------------------------------------------------------------
-// Adds a census workgroup's LDS histogram to copy blockIdx mod kCensusCopies
-// (k_census_fold adds the copies to the census).
-__device__ __forceinline__ void census_flush(const Geo &G, const uint32_t *hist, unsigned long long *__restrict__ copies)
+// Kernels of at most this many workgroups end a step themselves (the clock,
+// the census's sum) in the workgroup that finishes last, instead of in a
+// kernel of their own: a launch costs the host 3 us and the GPU 2 to 5, a
+// ticket about 12 ns per workgroup, one after the other.
+constexpr uint32_t kTicketMax = 64;
+
+// Whether this workgroup is the last of the launch to get here (every thread
+// of it calls).  What the others have done before is only seen where it was
+// done by atomics that had returned.
+__device__ __forceinline__ bool last_workgroup(uint32_t *ticket)
+{
+    __shared__ uint32_t last;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        last = atomicAdd(ticket, 1u) == gridDim.x - 1u;
+        if (last) atomicExch(ticket, 0u);
+    }
+    __syncthreads();
+    return last != 0;
+}
+
+// Adds a census workgroup's LDS histogram to copy blockIdx mod kCensusCopies.
+// The copies are added to the census by k_census_fold, or (`ends`) by the last
+// workgroup, which takes them with atomics as they were put there.
+__device__ __forceinline__ void census_flush(const Geo &G, DevState *__restrict__ st, const uint32_t *hist,
+                                             unsigned long long *__restrict__ copies, bool ends)
 {
     unsigned long long *mine = copies + (size_t)(blockIdx.x % kCensusCopies) * G.k;
+    if (!ends) {
+        for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x)
+            if (hist[d]) atomicAdd(&mine[d], (unsigned long long)hist[d]);
+        return;
+    }
     for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x)
-        if (hist[d]) atomicAdd(&mine[d], (unsigned long long)hist[d]);
+        if (hist[d]) {
+            const unsigned long long was = atomicAdd(&mine[d], (unsigned long long)hist[d]);
+            asm volatile("" ::"v"(was));      // returned, so performed before the ticket is taken
+        }
+    if (!last_workgroup(&st->ticket[1])) return;
+    const uint32_t used = min(gridDim.x, kCensusCopies);
+    for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x) {
+        unsigned long long sum = 0;
+        for (uint32_t c = 0; c < used; ++c) sum += atomicExch(&copies[(size_t)c * G.k + d], 0ull);
+        census_of(st)[d] += sum;
+    }
 }
+
+// ---------------------------------------------------------------------------
+// Slice advance: BACT^0 = (BACT^0 + 1) mod 2k, t = t + 1 (Alg. 4 end of loop),
+// census cleared for the new slice, by one workgroup: k_advance, the last one
+// of a small k_preserve, or the first one of DR maintenance (whose kernels do
+// not read the clock).
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t next_bact0(const Geo &G, uint32_t bact0) { return bact0 + 1 == G.twok ? 0 : bact0 + 1; }
+
+__device__ __forceinline__ void advance_clock(const Geo &G, DevState *__restrict__ st)
+{
+    if (threadIdx.x == 0) {
+        st->bact0 = next_bact0(G, st->bact0);
+        st->t = st->t + 1;
+    }
+    for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x) census_of(st)[d] = 0;
+}
+
+__global__ void k_advance(Geo G, DevState *__restrict__ st) { advance_clock(G, st); }
 
 #include "vate_exact.h"
 
@@ -218,6 +276,7 @@ __global__ void __launch_bounds__(256) k_init(Geo G, uint4 *__restrict__ pool4, 
         if (threadIdx.x == 0) {
             st->t = 0;
             st->bact0 = 0;
+            st->ticket[0] = st->ticket[1] = 0;
         }
         for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x) census_of(st)[d] = 0;
         for (uint32_t d = threadIdx.x; d < kCensusCopies * G.k; d += blockDim.x) copies[d] = 0;
@@ -453,7 +512,7 @@ __device__ __forceinline__ uint32_t census_chunk_fast(const Geo &G, const uint4 
 template <int W>
 __global__ void __launch_bounds__(256) k_census(Geo G, const uint4 *__restrict__ pool4, uint64_t nchunks,
                                                 DevState *__restrict__ st, uint8_t *__restrict__ bitmap,
-                                                unsigned long long *__restrict__ copies)
+                                                unsigned long long *__restrict__ copies, bool ends)
 {
     __shared__ uint32_t hist[kCensusLdsBins];
     const bool lds = G.k <= kCensusLdsBins;
@@ -480,7 +539,7 @@ __global__ void __launch_bounds__(256) k_census(Geo G, const uint4 *__restrict__
         }
     }
     __syncthreads();
-    if (lds) census_flush(G, hist, copies);
+    if (lds) census_flush(G, st, hist, copies, ends);
 }
 
 // k_census8: the census of byte counters (k <= 255).  In steady
@@ -548,7 +607,7 @@ __device__ __forceinline__ void census8_round(const Geo &G, const uint4 (&v)[kCe
 
 __global__ void __launch_bounds__(256) k_census8(Geo G, const uint4 *__restrict__ pool4, uint64_t nchunks,
                                                  DevState *__restrict__ st, uint8_t *__restrict__ bitmap,
-                                                 unsigned long long *__restrict__ copies)
+                                                 unsigned long long *__restrict__ copies, bool ends)
 {
     constexpr int U = kCensus8U;
     static_assert(U == 4, "one 8-byte bitmap store per lane and round");
@@ -594,7 +653,7 @@ __global__ void __launch_bounds__(256) k_census8(Geo G, const uint4 *__restrict_
             if (c0 + u < nchunks) bm16[c0 + u] = (uint16_t)bits[u];
     }
     __syncthreads();
-    census_flush(G, L.hist, copies);
+    census_flush(G, st, L.hist, copies, ends);
 }
 
 __global__ void __launch_bounds__(256) k_census_fold(Geo G, DevState *__restrict__ st,
@@ -791,19 +850,6 @@ constexpr int kLearnMaxK = VATE_MLP_FEATURES - 3;
 
 #include "vate_part.h"
 
-// ---------------------------------------------------------------------------
-// Slice advance: BACT^0 = (BACT^0 + 1) mod 2k, t = t + 1 (Alg. 4 end of loop),
-// census cleared for the new slice.
-// ---------------------------------------------------------------------------
-__global__ void k_advance(Geo G, DevState *__restrict__ st)
-{
-    if (threadIdx.x == 0) {
-        st->bact0 = st->bact0 + 1 == G.twok ? 0 : st->bact0 + 1;
-        st->t = st->t + 1;
-    }
-    for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x) census_of(st)[d] = 0;
-}
-
 __global__ void k_set_clock(Geo G, DevState *__restrict__ st, unsigned long long t, uint32_t bact0)
 {
     if (threadIdx.x == 0) {
@@ -858,14 +904,17 @@ __device__ __forceinline__ void preserve_chunk(const Geo &G, uint4 *__restrict__
     if (changed) pool4[ch] = v;
 }
 
+// `ends`: the clock is still the old slice's, and the last workgroup moves it
+// (each has read it by then).
 template <int W>
-__global__ void __launch_bounds__(256) k_preserve(Geo G, uint4 *__restrict__ pool4,
-                                                  const DevState *__restrict__ st, uint64_t max_chunks)
+__global__ void __launch_bounds__(256) k_preserve(Geo G, uint4 *__restrict__ pool4, DevState *st, uint64_t max_chunks,
+                                                  bool ends)
 {
-    const uint32_t bact0 = st->bact0;
+    const uint32_t bact0 = ends ? next_bact0(G, st->bact0) : st->bact0;
     for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < 2 * max_chunks;
          j += (uint64_t)gridDim.x * blockDim.x)
         preserve_chunk<W>(G, pool4, bact0, j, max_chunks);
+    if (ends && last_workgroup(&st->ticket[0])) advance_clock(G, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -892,8 +941,10 @@ __device__ __forceinline__ void dr_maintain_chunk(const Geo &G, uint4 *__restric
 }
 
 template <int W>
-__global__ void __launch_bounds__(256) k_dr_maintain(Geo G, uint4 *__restrict__ pool4, uint64_t nchunks)
+__global__ void __launch_bounds__(256) k_dr_maintain(Geo G, uint4 *__restrict__ pool4, uint64_t nchunks,
+                                                     DevState *__restrict__ st)
 {
+    if (blockIdx.x == 0) advance_clock(G, st);
     for (uint64_t ch = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; ch < nchunks;
          ch += (uint64_t)gridDim.x * blockDim.x)
         dr_maintain_chunk<W>(G, pool4, ch);
@@ -1004,37 +1055,44 @@ static void launch_init(vate_sketch *s, hipStream_t st)
 template <int W>
 static void launch_census(vate_sketch *s, hipStream_t st)
 {
+    unsigned blocks;
+    const bool lds = s->G.k <= kCensusLdsBins;      // longer windows are counted straight into the census
     if constexpr (W == 0) {
         const uint64_t ng = s->G.N / 32;
+        blocks = grid_for(ng, 256, 8u * s->n_cu);
         by_exact_width(s->p.width, [&](auto WB) {
-            k_census_x<decltype(WB)::value><<<grid_for(ng, 256, 8u * s->n_cu), 256, 0, st>>>(
-                s->G, reinterpret_cast<const uint32_t *>(s->pool), ng, s->st, s->bitmap, s->copies);
+            k_census_x<decltype(WB)::value><<<blocks, 256, 0, st>>>(s->G, reinterpret_cast<const uint32_t *>(s->pool),
+                                                                    ng, s->st, s->bitmap, s->copies,
+                                                                    blocks <= kTicketMax);
         });
     } else {
-        uint64_t nch = s->pool_bytes / 16;
-        if constexpr (W == 8)         // k <= 255 (2^8 >= k + 1)
-            k_census8<<<grid_for(nch, 256 * kCensus8U, 4096), 256, 0, st>>>(
-                s->G, reinterpret_cast<const uint4 *>(s->pool), nch, s->st, s->bitmap, s->copies);
-        else
-            k_census<W><<<grid_for(nch, 256 * 4, 2048), 256, 0, st>>>(s->G, reinterpret_cast<const uint4 *>(s->pool),
-                                                                       nch, s->st, s->bitmap, s->copies);
+        const uint64_t nch = s->pool_bytes / 16;
+        const uint4 *pool4 = reinterpret_cast<const uint4 *>(s->pool);
+        if constexpr (W == 8) {         // k <= 255 (2^8 >= k + 1)
+            blocks = grid_for(nch, 256 * kCensus8U, 4096);
+            k_census8<<<blocks, 256, 0, st>>>(s->G, pool4, nch, s->st, s->bitmap, s->copies, blocks <= kTicketMax);
+        } else {
+            blocks = grid_for(nch, 256 * 4, 2048);
+            k_census<W><<<blocks, 256, 0, st>>>(s->G, pool4, nch, s->st, s->bitmap, s->copies, blocks <= kTicketMax);
+        }
     }
-    if (s->G.k <= kCensusLdsBins)      // longer windows are counted straight into the census
-        k_census_fold<<<(s->G.k + 255) / 256, 256, 0, st>>>(s->G, s->st, s->copies);
+    if (lds && blocks > kTicketMax) k_census_fold<<<(s->G.k + 255) / 256, 256, 0, st>>>(s->G, s->st, s->copies);
 }
 
+// The slide of the window: the clock and Alg. 3.
 template <int W>
 static void launch_preserve(vate_sketch *s, hipStream_t st)
 {
-    uint64_t threads = 2 * s->max_block_chunks;
+    const unsigned blocks = grid_for(2 * s->max_block_chunks, 256, 8u * s->n_cu);
+    const bool ends = blocks <= kTicketMax;
+    if (!ends) k_advance<<<1, 256, 0, st>>>(s->G, s->st);
     if constexpr (W == 0)
         by_exact_width(s->p.width, [&](auto WB) {
-            k_preserve_x<decltype(WB)::value><<<grid_for(threads, 256, 8u * s->n_cu), 256, 0, st>>>(
-                s->G, reinterpret_cast<uint32_t *>(s->pool), s->st, s->max_block_chunks);
+            k_preserve_x<decltype(WB)::value><<<blocks, 256, 0, st>>>(s->G, reinterpret_cast<uint32_t *>(s->pool), s->st,
+                                                                      s->max_block_chunks, ends);
         });
     else
-        k_preserve<W><<<grid_for(threads, 256, 8u * s->n_cu), 256, 0, st>>>(s->G, reinterpret_cast<uint4 *>(s->pool),
-                                                                         s->st, s->max_block_chunks);
+        k_preserve<W><<<blocks, 256, 0, st>>>(s->G, reinterpret_cast<uint4 *>(s->pool), s->st, s->max_block_chunks, ends);
 }
 
 template <int W>
@@ -1044,11 +1102,11 @@ static void launch_dr_maintain(vate_sketch *s, hipStream_t st)
         const uint64_t ng = s->G.N / 32;
         by_exact_width(s->p.width, [&](auto WB) {
             k_dr_maintain_x<decltype(WB)::value><<<grid_for(ng, 256, 8192), 256, 0, st>>>(
-                s->G, reinterpret_cast<uint32_t *>(s->pool), ng);
+                s->G, reinterpret_cast<uint32_t *>(s->pool), ng, s->st);
         });
     } else {
         const uint64_t nch = s->pool_bytes / 16;
-        k_dr_maintain<W><<<grid_for(nch, 256, 8192), 256, 0, st>>>(s->G, reinterpret_cast<uint4 *>(s->pool), nch);
+        k_dr_maintain<W><<<grid_for(nch, 256, 8192), 256, 0, st>>>(s->G, reinterpret_cast<uint4 *>(s->pool), nch, s->st);
     }
 }
 
@@ -1076,7 +1134,6 @@ static void dispatch_census(vate_sketch *s, hipStream_t st)
 
 static int advance(vate_sketch *s, hipStream_t st)
 {
-    k_advance<<<1, 256, 0, st>>>(s->G, s->st);
     if (s->G.dr)
         by_width(s->p.width, [&](auto W) { launch_dr_maintain<decltype(W)::value>(s, st); });
     else

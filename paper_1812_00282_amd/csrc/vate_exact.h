@@ -133,6 +133,7 @@ __global__ void __launch_bounds__(256) k_init_x(Geo G, uint32_t *__restrict__ po
         if (threadIdx.x == 0) {
             st->t = 0;
             st->bact0 = 0;
+            st->ticket[0] = st->ticket[1] = 0;
         }
         for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x) census_of(st)[d] = 0;
         for (uint32_t d = threadIdx.x; d < kCensusCopies * G.k; d += blockDim.x) copies[d] = 0;
@@ -205,7 +206,7 @@ __device__ __forceinline__ void census_group_x(const Geo &G, const uint32_t *__r
 template <int WB>
 __global__ void __launch_bounds__(256) k_census_x(Geo G, const uint32_t *__restrict__ pool32, uint64_t ngroups,
                                                   DevState *__restrict__ st, uint8_t *__restrict__ bitmap,
-                                                  unsigned long long *__restrict__ copies)
+                                                  unsigned long long *__restrict__ copies, bool ends)
 {
     __shared__ uint32_t hist[kCensusLdsBins];
     const bool lds = G.k <= kCensusLdsBins;
@@ -217,7 +218,7 @@ __global__ void __launch_bounds__(256) k_census_x(Geo G, const uint32_t *__restr
          gi += (uint64_t)gridDim.x * blockDim.x)
         census_group_x<WB>(G, pool32, gi, bact0, lds ? hist : nullptr, census_of(st), bitmap);
     __syncthreads();
-    if (lds) census_flush(G, hist, copies);
+    if (lds) census_flush(G, st, hist, copies, ends);
 }
 
 // Alg. 3 on the two blocks whose ACT is 0 or k; thread j < max_groups takes
@@ -262,13 +263,14 @@ __device__ __forceinline__ void preserve_group_x(const Geo &G, uint32_t *__restr
 }
 
 template <int WB>
-__global__ void __launch_bounds__(256) k_preserve_x(Geo G, uint32_t *__restrict__ pool32,
-                                                    const DevState *__restrict__ st, uint64_t max_groups)
+__global__ void __launch_bounds__(256) k_preserve_x(Geo G, uint32_t *__restrict__ pool32, DevState *st,
+                                                    uint64_t max_groups, bool ends)
 {
-    const uint32_t bact0 = st->bact0;
+    const uint32_t bact0 = ends ? next_bact0(G, st->bact0) : st->bact0;
     for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < 2 * max_groups;
          j += (uint64_t)gridDim.x * blockDim.x)
         preserve_group_x<WB>(G, pool32, bact0, j, max_groups);
+    if (ends && last_workgroup(&st->ticket[0])) advance_clock(G, st);
 }
 
 // DR maintenance: every counter of group gi grows by one, saturating at k
@@ -291,8 +293,10 @@ __device__ __forceinline__ void dr_maintain_group_x(const Geo &G, uint32_t *__re
 }
 
 template <int WB>
-__global__ void __launch_bounds__(256) k_dr_maintain_x(Geo G, uint32_t *__restrict__ pool32, uint64_t ngroups)
+__global__ void __launch_bounds__(256) k_dr_maintain_x(Geo G, uint32_t *__restrict__ pool32, uint64_t ngroups,
+                                                       DevState *__restrict__ st)
 {
+    if (blockIdx.x == 0) advance_clock(G, st);
     for (uint64_t gi = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; gi < ngroups;
          gi += (uint64_t)gridDim.x * blockDim.x)
         dr_maintain_group_x<WB>(G, pool32, gi);
