@@ -674,10 +674,8 @@ __global__ void __launch_bounds__(256) k_census_fold(Geo G, DevState *__restrict
 // VATs of a host are gathered in batches of U independent reads per lane,
 // decoded with CheckAT (Alg. 1), counted and summed over the host's lanes, and
 // the estimate of Eq. 11 is formed in FP32 from exact integer counts.  (With
-// the distance histogram: k_gather.)  LOCAL: the whole activity bitmap of a
-// pool of at most 2^20 ATs is copied to the workgroup's LDS first and the bits
-// are read there, so a lookup costs its hash and an LDS read; else each is a
-// read through L2, which serves about 2.5e11 of them a second.
+// the distance histogram: k_gather.)  Bound by L2 once the chip is full: it
+// serves about 2.5e11 of these reads a second.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float estimate_from_counts(uint64_t u_v, uint64_t u_p, uint32_t g, uint32_t c)
 {
@@ -703,45 +701,13 @@ __device__ __forceinline__ uint64_t pool_active(const DevState *__restrict__ st,
     return s;
 }
 
-constexpr uint32_t kLocalLog2 = 20;       // largest pool whose bitmap a workgroup keeps in LDS (128 KiB)
-constexpr uint32_t kLocalThreads = 512;   // LOCAL workgroups; others 256
-
-// Activity bit of AT pid (CheckAT for window k), from the bitmap in memory or
-// from its copy in LDS.
-template <bool LOCAL>
-__device__ __forceinline__ uint32_t active_bit(const void *bitmap, uint32_t pid)
-{
-    if constexpr (LOCAL)
-        return __builtin_amdgcn_ubfe(static_cast<const uint32_t *>(bitmap)[pid >> 5], pid, 1u);   // bit pid mod 32
-    else
-        return ((uint32_t)static_cast<const uint8_t *>(bitmap)[pid >> 3] >> (pid & 7u)) & 1u;
-}
-
-// Copies the bitmap of a pool of N <= 2^20 ATs to LDS, a thread's 16-byte
-// groups all in flight (a bitmap has at least 16 bytes).
-__device__ __forceinline__ void copy_bitmap(const Geo &G, const uint8_t *__restrict__ bitmap, uint32_t *bits)
-{
-    const uint32_t nv = G.c > 7 ? 1u << (G.c - 7) : 1u;
-    const uint4 *src = reinterpret_cast<const uint4 *>(bitmap);
-    uint4 *dst = reinterpret_cast<uint4 *>(bits);
-    constexpr uint32_t B = 8;
-    for (uint32_t q0 = threadIdx.x; q0 < nv; q0 += B * kLocalThreads) {
-        uint4 v[B];
-#pragma unroll
-        for (uint32_t u = 0; u < B; ++u) v[u] = src[min(q0 + u * kLocalThreads, nv - 1u)];
-#pragma unroll
-        for (uint32_t u = 0; u < B; ++u)
-            if (q0 + u * kLocalThreads < nv) dst[q0 + u * kLocalThreads] = v[u];
-    }
-}
-
 // VATs sub, sub + L, ... of one host that are active for k', by U gathers in
 // flight.  The activity bitmap answers CheckAT(., k) directly; the AT value
 // (for its distance) is only read for VATs that are active at all, and only
 // when a shorter window needs it, again with all of a batch in flight.
-template <int W, int L, int U, bool LOCAL>
-__device__ __forceinline__ uint32_t lane_live(const Geo &G, const uint8_t *__restrict__ pool, const void *bitmap,
-                                              uint32_t kprime, uint32_t key, bool valid, uint32_t bact0, uint32_t sub)
+template <int W, int L, int U>
+__device__ __forceinline__ uint32_t lane_live(const Geo &G, const uint8_t *__restrict__ pool,
+                                              const uint8_t *__restrict__ bitmap, uint32_t kprime, uint32_t key, bool valid, uint32_t bact0, uint32_t sub)
 {
     const bool need_dist = kprime < G.k;
     uint32_t live = 0;
@@ -750,7 +716,9 @@ __device__ __forceinline__ uint32_t lane_live(const Geo &G, const uint8_t *__res
 #pragma unroll
         for (int u = 0; u < U; ++u) pid[u] = vat_pid(G, key, i0 + u * L);
 #pragma unroll
-        for (int u = 0; u < U; ++u) bit[u] = (valid && i0 + u * L < G.g) ? active_bit<LOCAL>(bitmap, pid[u]) : 0u;
+        for (int u = 0; u < U; ++u) bit[u] = (valid && i0 + u * L < G.g) ? (uint32_t)bitmap[pid[u] >> 3] : 0u;
+#pragma unroll
+        for (int u = 0; u < U; ++u) bit[u] = (bit[u] >> (pid[u] & 7u)) & 1u;
         if (!need_dist) {
 #pragma unroll
             for (int u = 0; u < U; ++u) live += bit[u];
@@ -774,27 +742,23 @@ __device__ __forceinline__ uint32_t sum_lanes(uint32_t x)
     return x;
 }
 
-template <int W, int L, int U, bool LOCAL>
-__global__ void __launch_bounds__(LOCAL ? kLocalThreads : 256) k_estimate(Geo G, const uint8_t *__restrict__ pool,
+template <int W, int L, int U>
+__global__ void __launch_bounds__(256) k_estimate(Geo G, const uint8_t *__restrict__ pool,
                                                   const DevState *__restrict__ st,
                                                   const uint8_t *__restrict__ bitmap,
                                                   const uint32_t *__restrict__ hosts, uint32_t n,
                                                   uint32_t kprime, float *__restrict__ est,
                                                   uint32_t *__restrict__ live_out)
 {
-    extern __shared__ __attribute__((aligned(16))) uint32_t bits[];   // LOCAL
-    if constexpr (LOCAL) copy_bitmap(G, bitmap, bits);
-    const void *bm = LOCAL ? static_cast<const void *>(bits) : bitmap;
-    constexpr uint32_t per = (LOCAL ? kLocalThreads : 256) / L;
+    constexpr uint32_t per = 256 / L;
     const uint32_t sub = threadIdx.x % L;
     const uint32_t bact0 = st->bact0;
     const uint64_t active_pool = pool_active(st, kprime);
-    if constexpr (LOCAL) __syncthreads();
     for (uint64_t h0 = (uint64_t)blockIdx.x * per; h0 < n; h0 += (uint64_t)gridDim.x * per) {
         const uint64_t h = h0 + threadIdx.x / L;
         const bool valid = h < n;
         const uint32_t key = host_key(G, valid ? hosts[h] : 0u);
-        const uint32_t live = sum_lanes<L>(lane_live<W, L, U, LOCAL>(G, pool, bm, kprime, key, valid, bact0, sub));
+        const uint32_t live = sum_lanes<L>(lane_live<W, L, U>(G, pool, bitmap, kprime, key, valid, bact0, sub));
         if (valid && sub == 0) {
             est[h] = estimate_from_counts(G.g - live, G.N - active_pool, G.g, G.c);
             if (live_out) live_out[h] = live;
@@ -849,6 +813,7 @@ static bool blocked_gather_ok(const Geo &G, uint32_t kprime) { return G.blog >= 
 constexpr int kLearnMaxK = VATE_MLP_FEATURES - 3;
 
 #include "vate_part.h"
+#include "vate_sliced.h"
 
 __global__ void k_set_clock(Geo G, DevState *__restrict__ st, unsigned long long t, uint32_t bact0)
 {
@@ -1162,15 +1127,44 @@ static bool allow_lds(const vate_sketch *s)
     return true;
 }
 
-static uint32_t local_bits_bytes(const Geo &G) { return G.c > 7 ? 1u << (G.c - 3) : 16u; }
-
-// Whether the lookups of n hosts read the activity bits from LDS: the pool's
-// bitmap has to fit, and there have to be enough lookups to pay for one copy
-// of it per workgroup.
-static bool local_lookups(const vate_sketch *s, uint32_t n)
+// Whether the lookups of n hosts go through LDS slice by slice (k_sliced).  The
+// closed form takes pools up to 2^23, histograms (which read the live VATs'
+// values as well) up to 2^22: at 64,000 hosts, g = 1024, 2^23 ATs the closed
+// form takes 204 us (gathered 240, partitioned 238), histograms 272 (gathered
+// 248).  Fewer lookups than kSlicedMin do not pay for the copies.
+static bool sliced(const vate_sketch *s, uint32_t n, bool hist)
 {
-    return s->G.c <= kLocalLog2 && (uint64_t)n * s->G.g >= kLocalMin;
+    const Geo &G = s->G;
+    if (G.blog > 0 || G.c > kSlicedLog2 - (hist ? 1u : 0u)) return false;
+    return (uint64_t)n * G.g >= (kSlicedMin << (G.c > kSliceLog2 ? G.c - kSliceLog2 - 1u : 0u));
 }
+
+// log2 of the lanes per host.  As many as hold a host's VATs, P each; with one
+// slice, where going round again costs no copy, 16 at most (64 hosts per
+// workgroup) while every CU has a workgroup.
+static uint32_t sliced_lanes(const vate_sketch *s, uint32_t n, uint32_t P)
+{
+    uint32_t lg = 0;
+    while (lg < 6 && (P << lg) < s->G.g) ++lg;
+    if (s->G.c <= kSliceLog2)
+        while (lg > 4 && (uint64_t)n << (lg - 1) >= (uint64_t)kSlicedThreads * s->n_cu) --lg;
+    return lg;
+}
+
+// Calls f with the kernel's VATs per thread and whether there is one slice.
+// Several slices: 32 VATs, or 16 while 32 would leave CUs without hosts.
+template <class F>
+static void by_slices(const vate_sketch *s, uint32_t n, bool small, F &&f)
+{
+    using std::integral_constant;
+    if (s->G.c <= kSliceLog2) f(integral_constant<uint32_t, 16>{}, std::true_type{});
+    else if (!small && (uint64_t)n * s->G.g >= 32ull * kSlicedThreads * s->n_cu)
+        f(integral_constant<uint32_t, 32>{}, std::false_type{});
+    else f(integral_constant<uint32_t, 16>{}, std::false_type{});
+}
+
+// Workgroups of `lds` bytes that a CU holds.
+static unsigned sliced_cap(const vate_sketch *s, uint32_t lds) { return s->n_cu * (s->G.c <= kSliceLog2 && lds <= s->lds_budget / 2 ? 2u : 1u); }
 
 // The closed form without histograms.  Lanes per host: as many as keep the
 // chip's 2048 threads per CU busy, so that few hosts take few serial rounds.
@@ -1188,24 +1182,21 @@ static void launch_estimate(vate_sketch *s, const uint32_t *hosts, uint32_t n, u
     }
     const uint64_t lanes = (uint64_t)s->n_cu * 2048u / n;       // lanes a host may take (n >= 1)
     using std::integral_constant;
-    if (local_lookups(s, n)) {
-        const uint32_t lds = local_bits_bytes(s->G);
-        const unsigned cap = s->n_cu * std::min<uint32_t>(2048u / kLocalThreads, s->lds_budget / lds);
-        auto go = [&](auto L) {
-            constexpr int l = decltype(L)::value;
-            if (!allow_lds<k_estimate<W, l, 16, true>>(s)) return;
-            k_estimate<W, l, 16, true><<<grid_for(n, kLocalThreads / l, cap), kLocalThreads, lds, st>>>(
-                s->G, s->pool, s->st, s->bitmap, hosts, n, kprime, est, live);
-        };
-        if (lanes >= 64 && s->G.g >= 512) go(integral_constant<int, 64>{});
-        else if (s->G.g >= 128) go(integral_constant<int, 16>{});
-        else go(integral_constant<int, 4>{});
+    if (sliced(s, n, false)) {
+        by_slices(s, n, false, [&](auto Pv, auto One) {
+            constexpr uint32_t P = decltype(Pv)::value;
+            constexpr bool one = decltype(One)::value;
+            if (!allow_lds<k_sliced<W, P, one>>(s)) return;
+            const uint32_t lg = sliced_lanes(s, n, P), lds = 4u * sliced_words(s->G);
+            k_sliced<W, P, one><<<grid_for(n, kSlicedThreads >> lg, sliced_cap(s, lds)), kSlicedThreads, lds, st>>>(
+                s->G, s->pool, s->st, s->bitmap, hosts, n, lg, kprime, est, live);
+        });
         return;
     }
     const unsigned cap = 16u * s->n_cu;
     auto go = [&](auto L, auto U) {
         constexpr int l = decltype(L)::value, u = decltype(U)::value;
-        k_estimate<W, l, u, false><<<grid_for(n, 256 / l, cap), 256, 0, st>>>(s->G, s->pool, s->st, s->bitmap, hosts,
+        k_estimate<W, l, u><<<grid_for(n, 256 / l, cap), 256, 0, st>>>(s->G, s->pool, s->st, s->bitmap, hosts,
                                                                               n, kprime, est, live);
     };
     if (lanes >= 64 && s->G.g <= 256) go(integral_constant<int, 64>{}, integral_constant<int, 4>{});
@@ -1216,28 +1207,44 @@ static void launch_estimate(vate_sketch *s, const uint32_t *hosts, uint32_t n, u
 
 // The direct gather with per-host distance histograms (MODE as in
 // finish_hosts).  Hosts per workgroup: 1 while the chip has room for a
-// workgroup per host, up to 16, or 64 for the network and where the lookups are
-// local and the rows fit beside the bitmap.
+// workgroup per host, up to 16, or 64 for the network.  Many lookups on a small
+// pool: k_sliced_hist, where the rows fit beside the bits.
 template <int W, int MODE>
 static void launch_gather(vate_sketch *s, const uint32_t *hosts, uint32_t n, uint32_t kprime, float *est,
                           uint32_t *live, uint32_t *hist, const Windows &win, const void *weights, float *cf,
                           hipStream_t st)
 {
     const uint32_t rowp = hist_row_words(s->G.k), row_bytes = rowp * 4u;
-    const auto *P = static_cast<const mlp::Packed *>(weights);
-    if (local_lookups(s, n)) {
-        // static LDS of the LOCAL kernels: the network's tiles, windows
-        constexpr uint32_t fixed = (MODE == kFinLearned ? 20u : 1u) * 1024u;
-        const uint32_t bits = local_bits_bytes(s->G);
-        const uint32_t room = s->lds_budget > bits + fixed ? s->lds_budget - bits - fixed : 0u;
-        if (room >= row_bytes) {
-            if (!allow_lds<k_gather<W, MODE, true>>(s)) return;
-            uint32_t lg = 0;
-            while (lg < 6 && (row_bytes << (lg + 1)) <= room && ((uint64_t)n >> lg) > 2u * s->n_cu) ++lg;
-            const uint32_t lds = bits + (row_bytes << lg);
-            const unsigned cap = s->n_cu * std::min<uint32_t>(2048u / kLocalThreads, s->lds_budget / (lds + fixed));
-            k_gather<W, MODE, true><<<grid_for(n, 1u << lg, cap), kLocalThreads, lds, st>>>(
-                s->G, s->pool, s->st, s->bitmap, hosts, n, lg, rowp, kprime, est, live, hist, win, P, cf);
+    const auto *net = static_cast<const mlp::Packed *>(weights);
+    using std::integral_constant;
+    // The network runs on 64 hosts of a workgroup's 1024 threads, so it goes
+    // through LDS only where lookups outweigh it (500,000 hosts, 2^21 ATs:
+    // g = 128 gathered 317 us, through LDS 400 to 640; g = 1024 1862 and 1367).
+    if (sliced(s, n, true) && (MODE != kFinLearned || s->G.g >= 512)) {
+        constexpr uint32_t fixed = (MODE == kFinLearned ? 10u : 1u) * 1024u;
+        const uint32_t bits = 4u * sliced_words(s->G), room = s->lds_budget - bits - fixed;
+        auto rows = [&](uint32_t P) {
+            uint32_t lg = sliced_lanes(s, n, P);
+            if (MODE == kFinLearned && lg < 4) lg = 4;      // the network takes 64 hosts at a time
+            while (lg < 6 && (row_bytes * kSlicedThreads >> lg) > room) ++lg;
+            return lg;
+        };
+        // rows that fit without leaving half of the threads' VATs empty
+        auto fits = [&](uint32_t P) {
+            const uint32_t lg = rows(P);
+            return (row_bytes * kSlicedThreads >> lg) <= room && (s->G.c <= kSliceLog2 || (P << lg) < 2u * s->G.g);
+        };
+        if (fits(16)) {
+            by_slices(s, n, !fits(32), [&](auto Pv, auto One) {
+                constexpr uint32_t P = decltype(Pv)::value;
+                constexpr bool one = decltype(One)::value;
+                if (!allow_lds<k_sliced_hist<W, MODE, P, one>>(s)) return;
+                const uint32_t lg = rows(P), lds = bits + (row_bytes * kSlicedThreads >> lg);
+                k_sliced_hist<W, MODE, P, one><<<grid_for(n, kSlicedThreads >> lg, sliced_cap(s, lds + fixed)),
+                                                 kSlicedThreads, lds, st>>>(s->G, s->pool, s->st, s->bitmap, hosts, n,
+                                                                            lg, rowp, kprime, est, live, hist, win,
+                                                                            net, cf);
+            });
             return;
         }
     }
@@ -1245,9 +1252,9 @@ static void launch_gather(vate_sketch *s, const uint32_t *hosts, uint32_t n, uin
     constexpr uint32_t most = MODE == kFinLearned ? 6u : 4u, room = (MODE == kFinLearned ? 2u : 8u);
     uint32_t lg = 0;
     while (lg < most && (row_bytes << (lg + 1)) <= 32u * 1024u && ((uint64_t)n >> lg) > room * s->n_cu) ++lg;
-    if (!allow_lds<k_gather<W, MODE, false>>(s)) return;
-    k_gather<W, MODE, false><<<grid_for(n, 1u << lg, 1u << 30), 256, row_bytes << lg, st>>>(
-        s->G, s->pool, s->st, s->bitmap, hosts, n, lg, rowp, kprime, est, live, hist, win, P, cf);
+    if (!allow_lds<k_gather<W, MODE>>(s)) return;
+    k_gather<W, MODE><<<grid_for(n, 1u << lg, 1u << 30), 256, row_bytes << lg, st>>>(
+        s->G, s->pool, s->st, s->bitmap, hosts, n, lg, rowp, kprime, est, live, hist, win, net, cf);
 }
 
 // vate_estimate's gather, with or without histograms.
@@ -1364,22 +1371,25 @@ static uint32_t part_hosts(const vate_sketch *s, uint64_t n, size_t have)
 // Whether the partitioned lookups answer n hosts.  A direct gather is a read
 // through L2 per lookup, 2.5e11 a second while an XCD's 4 MiB L2 holds the
 // bitmap (up to 2^25 ATs) and 6.5e10 on a 2^28 pool; partitioned lookups reach
-// 3.5e11 and more but take three passes and 25 us at least.  Measured (closed
-// form, byte ATs, g = 64 .. 1024) they break even at lookups x ATs of about
-// 2^49: 2M lookups on 2^28 ATs (36 us each way), 16M on 2^25 (70), 64M on 2^23
-// (240); from 2^27 to 2^26 at half of that.  Below 2^23 ATs the direct gather
-// stays ahead (512M lookups on 2^22: 0.87 of the partitioned time).  A plan's
-// runs leave out the first pass: half the lookups.
-static bool partitioned(const vate_sketch *s, uint64_t n, bool planned = false)
+// 3.5e11 and more but take three passes and 25 us at least.  Measured (byte
+// ATs, g = 64 .. 1024) they break even at lookups x ATs of about 2^49: 2M
+// lookups on 2^28 ATs (36 us each way), 16M on 2^25 (70), 64M on 2^23 (240);
+// from 2^27 to 2^26 at half of that.  A plan's runs leave out the first pass:
+// half the lookups.  On 2^23 ATs the closed form stays with k_sliced, below
+// everything does (512M lookups on 2^22: 0.87 of the partitioned time by
+// gathers).
+enum PartUse { PART_FORM, PART_HIST, PART_PLANNED };   // the closed form; histograms, windows, learned; a plan
+static bool partitioned(const vate_sketch *s, uint64_t n, PartUse use)
 {
-    return s->G.c >= kPartLog2 && n * s->G.g >= (kPartMin >> s->G.c >> (planned ? 1 : 0)) && part_max_hosts(s, n) > 0;
+    return s->G.c >= (use == PART_FORM ? kPartLog2 + 1u : kPartLog2) &&
+           n * s->G.g >= (kPartMin >> s->G.c >> (use == PART_PLANNED ? 1 : 0)) && part_max_hosts(s, n) > 0;
 }
 
 // The workspace size reported to callers: enough for the even subgroups.
 static size_t workspace_size(const vate_sketch *s, uint64_t n)
 {
     size_t need = workspace_need(s, n);
-    if (partitioned(s, n, true)) need = std::max(need, run_ws(s->G, n, part_hosts(s, n, ~size_t(0)), nullptr).bytes);
+    if (partitioned(s, n, PART_PLANNED)) need = std::max(need, run_ws(s->G, n, part_hosts(s, n, ~size_t(0)), nullptr).bytes);
     return need;
 }
 
@@ -1642,7 +1652,7 @@ static int estimate_ws_impl(vate_sketch *s, const uint32_t *hosts_dev, size_t n_
     if (workspace_dev == s->plan_ws) s->plan_ws = nullptr;   // the plan is overwritten
     if (hist_dev && s->p.k > (uint32_t)kMaxHistK && part_max_hosts(s, n) == 0)
         return fail(s, VATE_E_UNSUPPORTED, "per-host histogram of this geometry needs k <= 256");
-    if (!partitioned(s, n)) {
+    if (!partitioned(s, n, hist_dev ? PART_HIST : PART_FORM)) {
         direct_estimate(s, hosts_dev, n, kprime, est_dev, live_dev, hist_dev, st);
         return check_launch(s, what);
     }
@@ -1727,7 +1737,7 @@ int vate_estimate_plan(vate_sketch *s, const uint32_t *hosts_dev, size_t n_hosts
         return fail(s, VATE_E_INVAL, "hosts must be non-NULL and 4-byte aligned");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const uint32_t n = (uint32_t)n_hosts;
-    if (partitioned(s, n, true)) {
+    if (partitioned(s, n, PART_PLANNED)) {
         const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes));
         const int rc = launch_part_w<kFinClosedForm>(s, pg, workspace_dev, hosts_dev, n, s->p.k, nullptr, nullptr,
                                                      nullptr, Windows{}, nullptr, nullptr, st, PART_PLAN);
@@ -1818,7 +1828,7 @@ int vate_estimate_learned_ws(vate_sketch *s, const uint32_t *hosts_dev, size_t n
     hipStream_t st = static_cast<hipStream_t>(stream);
     const uint32_t n = (uint32_t)n_hosts;
     if (workspace_dev == s->plan_ws) s->plan_ws = nullptr;   // the plan is overwritten
-    if (!partitioned(s, n)) {
+    if (!partitioned(s, n, PART_HIST)) {
         direct_learned(s, hosts_dev, n, weights_dev, est_dev, est_cf_dev, st);
         return check_launch(s, "estimate_learned_ws");
     }
@@ -1834,7 +1844,7 @@ int vate_estimate_multi_workspace_bytes(const vate_sketch *s, size_t n_hosts, si
     if (!s || !bytes) return VATE_E_INVAL;
     if (n_hosts > 0xFFFFFFFFull - 1024) return VATE_E_INVAL;
     *bytes = multi_need(s, n_hosts);
-    if (partitioned(s, n_hosts, true)) *bytes = std::max(*bytes, workspace_size(s, n_hosts));
+    if (partitioned(s, n_hosts, PART_PLANNED)) *bytes = std::max(*bytes, workspace_size(s, n_hosts));
     return VATE_OK;
 }
 
@@ -1864,7 +1874,7 @@ int vate_estimate_multi_ws(vate_sketch *s, const uint32_t *hosts_dev, size_t n_h
     if (workspace_dev == s->plan_ws) s->plan_ws = nullptr;   // the plan is overwritten
     if (s->p.k > (uint32_t)kMaxHistK && part_max_hosts(s, n) == 0)
         return fail(s, VATE_E_UNSUPPORTED, "several windows for this geometry need k <= 256");
-    if (partitioned(s, n)) {
+    if (partitioned(s, n, PART_HIST)) {
         const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes));
         const int rc = launch_part_w<kFinMulti>(s, pg, workspace_dev, hosts_dev, n, s->p.k, est_dev, nullptr,
                                                 nullptr, win, nullptr, nullptr, st);

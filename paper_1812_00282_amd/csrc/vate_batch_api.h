@@ -10,6 +10,7 @@ struct vate_batch {
     const unsigned long long *n_pairs;   // device packet counts, one per sketch
     BatchTune tune;
     uint32_t cus;
+    uint32_t graph_sliced;                // the captured graph has k_batch_sliced
     hipGraph_t graph;
     hipGraphExec_t exec;
     int has_graph;
@@ -54,6 +55,23 @@ static BatchTune default_tune(uint32_t cus)
     return t;
 }
 
+// log2 of the lanes per host of a sliced member.
+static uint32_t batch_lanes(uint32_t g)
+{
+    uint32_t lg = 0;
+    while (lg < 6 && (kBatchSlicedVats << lg) < g) ++lg;
+    return lg;
+}
+
+// Whether some member's lookups go through LDS (a launch of their own, whose
+// shape is not tuned).
+static bool batch_sliced(const vate_batch *b)
+{
+    for (uint32_t i = 0; i < b->S; ++i)
+        if (b->host_items[i].sliced) return true;
+    return false;
+}
+
 static void batch_phase(vate_batch *b, int ph, hipStream_t st)
 {
     const BatchTune &t = b->tune;
@@ -66,6 +84,8 @@ static void batch_phase(vate_batch *b, int ph, hipStream_t st)
         else k_batch_census<1><<<t.grid_census, 256, 0, st>>>(b->items, b->S, t, b->tab);
         break;
     default:
+        if (batch_sliced(b) && allow_lds<k_batch_sliced>(b->sk[0]))
+            k_batch_sliced<<<b->cus, kSlicedThreads, 16u * (kBmWords / 4u + 1u), st>>>(b->items, b->S, b->tab);
         if (t.estimate_lanes == 16)
             k_batch_estimate<16><<<t.grid_estimate, t.estimate_block, 0, st>>>(b->items, b->S, t, b->tab);
         else if (t.estimate_lanes == 4)
@@ -79,7 +99,7 @@ static void batch_phase(vate_batch *b, int ph, hipStream_t st)
 static void batch_enqueue(vate_batch *b, unsigned long long adv_mask, hipStream_t st)
 {
     k_batch_begin<<<1, 64, 0, st>>>(b->items, b->S, b->n_pairs, adv_mask, b->tune, b->tab);
-    for (int ph = 0; ph < PH_COUNT; ++ph) batch_phase(b, ph, st);
+    for (int ph = 0; ph <= PH_ESTIMATE; ++ph) batch_phase(b, ph, st);
 }
 
 static bool batch_tune_valid(const BatchTune &t)
@@ -170,6 +190,10 @@ int vate_batch_set_io(vate_batch *b, uint32_t i, const uint32_t *pairs_dev, uint
     it.kprime = kprime;
     it.est = est_dev;
     it.live = live_dev;
+    // (a captured graph without k_batch_sliced keeps gathering)
+    it.sliced = n_hosts > 0 && sliced(b->sk[i], n_hosts, false) && (!b->has_graph || b->graph_sliced)
+                    ? 1u + batch_lanes(it.G.g)
+                    : 0u;
     hipError_t e = hipMemcpy(b->items + i, &it, sizeof(BatchItem), hipMemcpyHostToDevice);
     if (e != hipSuccess) return bfail(b, VATE_E_DEVICE, hipGetErrorString(e));
     return VATE_OK;
@@ -218,6 +242,7 @@ int vate_batch_capture(vate_batch *b, void *stream)
     b->graph = g;
     b->exec = x;
     b->has_graph = 1;
+    b->graph_sliced = batch_sliced(b);
     return VATE_OK;
 }
 
@@ -307,8 +332,8 @@ int vate_batch_autotune(vate_batch *b, void *stream, char *report, size_t report
         *ms = bestms;
         return VATE_OK;
     };
-    const char *names[PH_COUNT] = {"preserve", "ingest", "census", "estimate"};
-    float best_ms[PH_COUNT] = {0.f, 1e30f, 1e30f, 1e30f};
+    const char *names[PH_ESTIMATE + 1] = {"preserve", "ingest", "census", "estimate"};
+    float best_ms[PH_ESTIMATE + 1] = {0.f, 1e30f, 1e30f, 1e30f};
     // Per phase: tile size x a second axis x grid size (workgroups per CU).
     // The second axis is the census's chunks in flight per thread and the
     // estimate's lanes per host (how many lanes share one host's g gathers);

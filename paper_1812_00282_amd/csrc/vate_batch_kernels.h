@@ -24,7 +24,8 @@ struct BatchItem {
     uint64_t pairs_cap;          // capacity of the pair buffer (packets)
     uint64_t nchunks;            // streaming units: 16-byte pool chunks (exact widths: 32-counter groups)
     uint64_t max_block_chunks;   // units one due block can overlap
-    uint32_t width, n_hosts, kprime, pad;   // width 0: an exact-width pool (G.wb bits per counter)
+    uint32_t width, n_hosts, kprime;   // width 0: an exact-width pool (G.wb bits per counter)
+    uint32_t sliced;             // 0: gathered lookups; else 1 + log2 of the lanes per host of k_batch_sliced
 };
 
 // Launch shape of each phase (chosen by the autotuner).
@@ -37,7 +38,9 @@ struct BatchTune {
     uint32_t census_unroll;      // pool chunks in flight per census thread (1, 2 or 4)
 };
 
-enum { PH_PRESERVE = 0, PH_INGEST = 1, PH_CENSUS = 2, PH_ESTIMATE = 3, PH_COUNT = 4 };
+// PH_ESTIMATE: the estimates of the gathered members, PH_SLICED of those whose
+// lookups go through LDS.
+enum { PH_PRESERVE = 0, PH_INGEST = 1, PH_CENSUS = 2, PH_ESTIMATE = 3, PH_SLICED = 4, PH_COUNT = 5 };
 
 struct BatchTables {
     unsigned long long prefix[PH_COUNT][kBatchMax + 1];
@@ -88,7 +91,9 @@ __global__ void k_batch_begin(BatchItem *__restrict__ items, uint32_t S, const u
         tiles[PH_INGEST][s] = (np + tune.ingest_tile - 1) / tune.ingest_tile;
         tiles[PH_CENSUS][s] = (it.nchunks + tune.census_tile - 1) / tune.census_tile;
         const uint32_t per_tile = tune.estimate_block / tune.estimate_lanes;
-        tiles[PH_ESTIMATE][s] = ((unsigned long long)it.n_hosts + per_tile - 1) / per_tile;
+        const uint32_t sliced_tile = kSlicedThreads >> (it.sliced ? it.sliced - 1u : 0u);
+        tiles[PH_ESTIMATE][s] = it.sliced ? 0ull : ((unsigned long long)it.n_hosts + per_tile - 1) / per_tile;
+        tiles[PH_SLICED][s] = it.sliced ? ((unsigned long long)it.n_hosts + sliced_tile - 1) / sliced_tile : 0ull;
     }
     __syncthreads();
     if (threadIdx.x < PH_COUNT) {
@@ -256,7 +261,7 @@ template <int W, int L>
 __device__ __forceinline__ uint32_t batch_host_live(const BatchItem &it, uint32_t key, bool valid, uint32_t bact0,
                                                     uint32_t sub)
 {
-    return sum_lanes<L>(lane_live<W, L, 16, false>(it.G, it.pool, it.bitmap, it.kprime, key, valid, bact0, sub));
+    return sum_lanes<L>(lane_live<W, L, 16>(it.G, it.pool, it.bitmap, it.kprime, key, valid, bact0, sub));
 }
 
 template <int L>
@@ -282,6 +287,54 @@ __global__ void __launch_bounds__(256) k_batch_estimate(const BatchItem *__restr
         else live = batch_host_live<16, L>(it, key, valid, bact0, sub);
         if (valid && sub == 0) {
             it.est[h] = estimate_from_counts(it.G.g - live, it.G.N - active_pool, it.G.g, it.G.c);
+            if (it.live) it.live[h] = live;
+        }
+    }
+}
+
+// The closed form of the members whose bitmaps go through LDS slice by slice
+// (k_sliced): one workgroup per CU, which claims groups of hosts.  16 sketches
+// of 2^20 to 2^25 ATs, 299k hosts, g = 1024: the estimates take 928 us with 15
+// of them here (399 us) and one gathered (528), 1162 with all of them gathered.
+// (One kernel for both kinds, a quarter of the workgroups starting with the
+// gathers, took 1001: a CU gathers a lookup every 2.3 clocks whatever the
+// others do, so there is nothing to overlap.)
+constexpr uint32_t kBatchSlicedVats = 32;
+
+__global__ void __launch_bounds__(kSlicedThreads, kSlicedWaves<false>)
+    k_batch_sliced(const BatchItem *__restrict__ items, uint32_t S, BatchTables *__restrict__ tab)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t bits[];
+    constexpr uint32_t P = kBatchSlicedVats;
+    const unsigned long long total = tab->prefix[PH_SLICED][S];
+    for (;;) {
+        const unsigned long long tile = claim_tile(&tab->claim[PH_SLICED]);
+        if (tile >= total) break;
+        const uint32_t s = find_item(tab->prefix[PH_SLICED], S, tile);
+        const BatchItem &it = items[s];
+        const Geo &G = it.G;
+        const uint32_t lg = it.sliced - 1u, sub = threadIdx.x & ((1u << lg) - 1u);
+        const uint32_t bact0 = it.st->bact0;
+        const uint64_t h = (tile - tab->prefix[PH_SLICED][s]) * (kSlicedThreads >> lg) + (threadIdx.x >> lg);
+        const bool valid = h < it.n_hosts;
+        const uint32_t key = host_key(G, valid ? it.hosts[h] : 0u);
+        uint32_t live = 0;
+        for (uint32_t i0 = 0; i0 < G.g; i0 += P << lg) {
+            u32x4 v[kSlicedLoads];
+            sliced_load(reinterpret_cast<const u32x4 *>(it.bitmap), sliced_groups(G), v);
+            uint32_t pid[P], mask;
+            sliced_pids<P>(G, key, valid, i0 + sub, 1u << lg, pid);
+            sliced_masks<P, false>(G, it.bitmap, bits, v, pid, mask);
+            if (it.kprime >= G.k) live += __popc(mask);
+            else if (it.width == 0) live += sliced_live<0, P>(G, it.pool, it.kprime, bact0, pid, mask);
+            else if (it.width == 4) live += sliced_live<4, P>(G, it.pool, it.kprime, bact0, pid, mask);
+            else if (it.width == 8) live += sliced_live<8, P>(G, it.pool, it.kprime, bact0, pid, mask);
+            else live += sliced_live<16, P>(G, it.pool, it.kprime, bact0, pid, mask);
+        }
+        live = sum_lanes_log2(live, lg);
+        const uint64_t active_pool = pool_active(it.st, it.kprime);
+        if (valid && sub == 0) {
+            it.est[h] = estimate_from_counts(G.g - live, G.N - active_pool, G.g, G.c);
             if (it.live) it.live[h] = live;
         }
     }

@@ -163,7 +163,7 @@ __device__ __forceinline__ void census_group_x(const Geo &G, const uint32_t *__r
         one = p0 + 32 <= next;
     }
     uint32_t bits = 0;
-    if (one && hist) {
+    if (WB > 0 && one && hist) {     // (the batched kernels keep their registers for the container widths)
         const uint32_t top = act0 + G.twok;
 #pragma unroll
         for (int e = 0; e < 32; ++e) {
@@ -175,6 +175,7 @@ __device__ __forceinline__ void census_group_x(const Geo &G, const uint32_t *__r
             }
         }
     } else {
+#pragma unroll
         for (int e = 0; e < 32; ++e) {
             const uint32_t val = vals[e];
             if (val == inact) continue;

@@ -739,14 +739,15 @@ __device__ __forceinline__ void finish_hosts(const Geo &G, const DevState *__res
             }
         }
     } else {
-        // Learned estimate, 16 hosts per wavefront at a time: the closed form
-        // for window k, then the network fed from the LDS rows.
+        // Learned estimate by the first 256 threads, in groups of 64 hosts (16
+        // per wavefront): the closed form for window k, then the network fed
+        // from the LDS rows.
         // One 16-row staging tile per wavefront holds its features and then
         // its first layer's activations: the layer's inputs are in registers
         // (its products depend on them) before its outputs are written.
-        __shared__ __attribute__((aligned(16))) uint16_t xs_all[NT / 64][16 * mlp::LDS_STRIDE];
-        __shared__ float cf_s[NT / 4];
-        __shared__ uint32_t live_s[NT / 4];
+        __shared__ __attribute__((aligned(16))) uint16_t xs_all[4][16 * mlp::LDS_STRIDE];
+        __shared__ float cf_s[64];
+        __shared__ uint32_t live_s[64];
         const uint64_t active_pool = pool_active(st, G.k);
         const float occupancy = (float)active_pool / (float)G.N;
         const uint32_t w = t >> 6;
@@ -755,7 +756,7 @@ __device__ __forceinline__ void finish_hosts(const Geo &G, const DevState *__res
         if (t == 0) fell_wg = 0;
         __syncthreads();                  // (the loop below synchronizes wavefronts only with themselves)
         uint32_t fell_wave = 0;
-        for (uint32_t base = 0; base < nh; base += NT / 4) {
+        if (NT == 256 || t < 256) for (uint32_t base = 0; base < nh; base += 64) {
             {   // live count and closed form of host base + hh, four threads a host
                 uint32_t live = 0;
                 if (base + hh < nh) {
@@ -895,18 +896,18 @@ __global__ void __launch_bounds__(256) k_copy_hosts(const uint32_t *__restrict__
 // latency of those two gathers while there are few hosts: one host per
 // workgroup then (a wavefront per 64 hosts and a lane per host, as before,
 // took 64 serial rounds of bitmap gathers at g = 1024 and up to 1024 of
-// values: 509 us for 331 hosts on a 2^28 pool).  LOCAL as in k_estimate.
+// values: 509 us for 331 hosts on a 2^28 pool).
 // ---------------------------------------------------------------------------
 constexpr uint32_t kGatherU = 8;
-// Lookups from which they are local.  8-bit pool of 2^20 ATs, g = 1024: 2M
-// lookups take 12 us either way (launch and latency), 8M 22 us direct and 16
-// local, 100M 309 and 106; on a 2^16 pool 16M take 22 and 14 us.
-constexpr uint64_t kLocalMin = 1u << 21;
+// Lookups from which they go slice by slice (doubling from 2^21 ATs on, with
+// the slices).  8-bit pool of 2^20 ATs, g = 1024: 2M lookups take 12 us either
+// way (launch and latency), 16M 55 us gathered and 20 through LDS.
+constexpr uint64_t kSlicedMin = 1u << 21;
 constexpr uint32_t kPartLog2 = 23;         // smallest pool (log2) whose lookups are partitioned
 constexpr uint64_t kPartMin = 3ull << 47;  // lookups times pool size from which they are
 
-template <int W, int MODE, bool LOCAL>
-__global__ void __launch_bounds__(LOCAL ? kLocalThreads : kFinThreads) k_gather(Geo G, const uint8_t *__restrict__ pool,
+template <int W, int MODE>
+__global__ void __launch_bounds__(kFinThreads) k_gather(Geo G, const uint8_t *__restrict__ pool,
                                                        const DevState *__restrict__ st,
                                                        const uint8_t *__restrict__ bitmap,
                                                        const uint32_t *__restrict__ hosts, uint32_t n, uint32_t lg,
@@ -915,14 +916,10 @@ __global__ void __launch_bounds__(LOCAL ? kLocalThreads : kFinThreads) k_gather(
                                                        Windows win, const mlp::Packed *__restrict__ P,
                                                        float *__restrict__ cf_out)
 {
-    // LOCAL: the bitmap; then [2^lg][rowp] packed 16-bit bins
-    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+    extern __shared__ __attribute__((aligned(16))) uint32_t hist[];   // [2^lg][rowp] packed 16-bit bins
     __shared__ unsigned long long act[MODE == kFinMulti ? kMaxWindows : 1u];
-    constexpr uint32_t NT = LOCAL ? kLocalThreads : kFinThreads;
-    uint32_t *hist = lds + (LOCAL ? (G.c > 7 ? 1u << (G.c - 5) : 4u) : 0u);
-    const void *bm = LOCAL ? static_cast<const void *>(lds) : bitmap;
+    constexpr uint32_t NT = kFinThreads;
     const uint32_t t = threadIdx.x;
-    if constexpr (LOCAL) copy_bitmap(G, bitmap, lds);
     if constexpr (MODE == kFinMulti)
         if (t < 64) window_counts(G, st, win, act);
     const uint32_t lanes = NT >> lg, sub = t & (lanes - 1u), h = t / lanes;
@@ -940,7 +937,9 @@ __global__ void __launch_bounds__(LOCAL ? kLocalThreads : kFinThreads) k_gather(
                 for (uint32_t u = 0; u < kGatherU; ++u) pid[u] = vat_pid(G, key, i0 + u * lanes);
 #pragma unroll
                 for (uint32_t u = 0; u < kGatherU; ++u)
-                    bit[u] = i0 + u * lanes < G.g ? active_bit<LOCAL>(bm, pid[u]) : 0u;
+                    bit[u] = i0 + u * lanes < G.g ? (uint32_t)bitmap[pid[u] >> 3] : 0u;
+#pragma unroll
+                for (uint32_t u = 0; u < kGatherU; ++u) bit[u] = (bit[u] >> (pid[u] & 7u)) & 1u;
 #pragma unroll
                 for (uint32_t u = 0; u < kGatherU; ++u) val[u] = bit[u] ? load_at<W>(pool, pid[u], G.wb) : 0u;
 #pragma unroll

@@ -130,3 +130,35 @@ def test_exact_width_streams(w, counter, c):
             _check_state(gpu, ref, f"slice {t}")
             np.testing.assert_array_equal(gpu.census(), ref.census())
             np.testing.assert_array_equal(_u32(gpu.estimate(hosts)[1]), ref.estimate(hosts)[1])
+
+
+# Batch members on both sides of the rule that sends lookups through LDS, with
+# windows of all kinds, against the single-sketch calls; eager and replayed, and
+# with hosts set again after the capture.
+def test_batch_sliced_members():
+    from paper_1812_00282_amd.batch import Batch
+    from paper_1812_00282_amd.sketch import Sketch
+
+    geo = [(16, 8, 60, 1024, 3000), (20, 7, 60, 1000, 4001), (21, 16, 200, 2048, 1500), (23, 8, 9, 300, 30_011),
+           (12, 4, 7, 33, 70_000), (24, 8, 60, 1024, 2500), (18, 8, 60, 100, 50)]
+    cfgs = [Config(c, w, k, g, seed_a=c, seed_b=w) for c, w, k, g, _ in geo]
+    rng = np.random.default_rng(8)
+    hosts = [rng.integers(0, 2**32, x[4], dtype=np.uint64).astype(np.uint32) for x in geo]
+    kp = [60, 13, 200, 4, 3, 60, 60]
+    b = Batch([Sketch(c) for c in cfgs], [20_000] * len(geo), hosts, kprime=kp)
+    solo = [Sketch(c) for c in cfgs]
+    for t in range(5):
+        sl = [_stream(rng, int(rng.integers(1, 20_000)), h, 4000) for h in hosts]
+        b.load(sl)
+        if t < 2:
+            b.slice()
+        else:
+            if t == 2:
+                b.capture()
+            b.replay()
+        b.synchronize()
+        for i, sk in enumerate(solo):
+            sk.ingest(sl[i])
+            sk.close_slice()
+            est, live, _ = sk.estimate(hosts[i], kprime=kp[i])
+            assert torch.equal(b.live[i], live) and torch.equal(b.est[i], est), (t, i)
