@@ -10,11 +10,10 @@
 // gradients dz2, dz1 before the products that consume them; every sum, bias,
 // GELU, the output layer and Adam in FP32.
 //
-// Tile organisation: a workgroup of 4 wavefronts owns 64 samples, each
-// wavefront 16 of them.  Forward layers are (16 x 64) x (64 x 64) products per
-// wavefront; the weight gradients are (64 x 64 samples) x (64 samples x 64)
-// products per workgroup, one 16-row slab per wavefront, accumulated across
-// workgroups with FP32 atomics.
+// Tile organisation: inference gives a wavefront 16 samples, whose layers are
+// (16 x 64) x (64 x 64) products; training gives a workgroup 64 samples and
+// each of its 16 wavefronts one 16 x 16 tile of every product (k_train), the
+// weight gradients accumulated across workgroups with FP32 atomics.
 
 #include <hip/hip_runtime.h>
 
@@ -93,131 +92,192 @@ __global__ void __launch_bounds__(256) k_forward(const Packed *__restrict__ P, c
 // One training pass over a minibatch: forward, loss gradient, backward; the
 // parameter gradient (FP32, VATE_MLP_PARAMS entries, caller-zeroed) and the
 // loss sum are accumulated with atomics.  Loss = mean |exp(o - y) - 1|.
+//
+// A workgroup of 4 S wavefronts takes 16 S samples at a time, each wavefront
+// one 16 x 16 tile of every product (sample slab w / 4, unit tile w mod 4; of
+// the weight gradients 4 / S tiles, column tile w mod 4), with the weights of
+// its tiles loaded at the start together with the samples.  Its time is one
+// workgroup's chain of steps (8 us with 32 samples, 10 with 64; the GELUs and
+// their derivatives most of it) plus about 48 ns per workgroup for the 8385
+// gradient atomics of each: so 32 samples a workgroup up to 2048, else 64 (at
+// 4096 samples 13.7 us against 14.1 with 32, at 8192 16.7 against 20.8; four
+// wavefronts with whole 16-sample slabs took 20 us at 4096 and 76 at 65,536,
+// which now take 13.7 and 43).  Beyond 256 workgroups each goes on with the
+// next samples and keeps its sums in registers.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_train(const Packed *__restrict__ P, const uint16_t *__restrict__ X,
-                                               const float *__restrict__ R, const float *__restrict__ Y,
-                                               uint64_t n, float inv_batch, float *__restrict__ grad,
-                                               float *__restrict__ loss)
-{
-    __shared__ __attribute__((aligned(16))) uint16_t xs[64 * LDS_STRIDE];    // [sample][feature]
-    __shared__ __attribute__((aligned(16))) uint16_t xT[64 * LDS_STRIDE];    // [feature][sample]
-    __shared__ __attribute__((aligned(16))) uint16_t a1s[64 * LDS_STRIDE];   // [sample][unit]
-    __shared__ __attribute__((aligned(16))) uint16_t a1T[64 * LDS_STRIDE];   // [unit][sample]
-    __shared__ __attribute__((aligned(16))) uint16_t dz2s[64 * LDS_STRIDE];  // [sample][unit]
-    __shared__ __attribute__((aligned(16))) uint16_t dz2T[64 * LDS_STRIDE];  // [unit][sample]
-    __shared__ __attribute__((aligned(16))) uint16_t dz1T[64 * LDS_STRIDE];  // [unit][sample]
-    __shared__ float gsmall[3 * HD + 1];                                      // db1, db2, dw3, db3
-    __shared__ float lsum;
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, q = l >> 4, c = l & 15;
-    const uint64_t blk0 = (uint64_t)blockIdx.x * 64, row0 = blk0 + 16 * w;
-    for (int i = threadIdx.x; i < 3 * HD + 1; i += blockDim.x) gsmall[i] = 0.f;
-    if (threadIdx.x == 0) lsum = 0.f;
-    uint16_t *xw = xs + 16 * w * LDS_STRIDE;
-    stage_rows(X, row0, n, xw);
-    __syncthreads();
-    // transposed copy of the features for the W1 gradient
-    for (int i = threadIdx.x; i < 64 * 64; i += blockDim.x) {
-        const int m = i >> 6, f = i & 63;
-        xT[f * LDS_STRIDE + m] = xs[m * LDS_STRIDE + f];
-    }
-    float r4[4], y4[4];
-    bool v4[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const uint64_t row = row0 + 4 * q + r;
-        v4[r] = row < n;
-        r4[r] = v4[r] ? R[row] : 0.f;
-        y4[r] = v4[r] ? Y[row] : 0.f;
-    }
-    f32x4 z1[4], z2[4];
-    float a2v[4][4], o4[4];
-    forward16(P, xw, a1s + 16 * w * LDS_STRIDE, r4, z1, z2, a2v, o4);
+constexpr unsigned kTrainBlocks = 256;       // the CUs of an MI355X
 
-    // loss gradient
-    float do4[4];
+// One 16 x 16 tile, K = 64: rows of A from arow, rows of B already in registers.
+__device__ __forceinline__ f32x4 tile64(const uint16_t *arow, const bf16x8 b0, const bf16x8 b1, int q)
+{
+    f32x4 d = {0.f, 0.f, 0.f, 0.f};
+    d = mfma(frag(arow, 0, q), b0, d);
+    return mfma(frag(arow, 1, q), b1, d);
+}
+
+// A tile of a weight gradient over K = 16 S samples, both operands from LDS.
+template <int S>
+__device__ __forceinline__ f32x4 grad_tile(const uint16_t *arow, const uint16_t *brow, int q)
+{
+    f32x4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const float e = expf(o4[r] - y4[r]);
-        const float d = e - 1.0f;
-        do4[r] = v4[r] ? (d > 0.f ? e : (d < 0.f ? -e : 0.f)) * inv_batch : 0.f;
-        if (v4[r] && c == 0) atomicAdd(&lsum, fabsf(d));
-    }
-    // output layer gradients, dz2
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        const int n = 16 * nt + c;
-        float gw3 = 0.f, gb2 = 0.f;
+    for (int s = 0; s < S / 2; ++s) d = mfma(frag(arow, s, q), frag(brow, s, q), d);
+    return d;
+}
+
+template <int S>
+__global__ void __launch_bounds__(256 * S) k_train(const Packed *__restrict__ P, const uint16_t *__restrict__ X,
+                                                   const float *__restrict__ R, const float *__restrict__ Y,
+                                                   uint64_t n, float inv_batch, float *__restrict__ grad,
+                                                   float *__restrict__ loss)
+{
+    static_assert(S == 2 || S == 4, "weight gradients in steps of 32 samples");
+    constexpr int NT = 256 * S, ROWS = 16 * S, TILES = 4 / S;
+    __shared__ __attribute__((aligned(16))) uint16_t xs[ROWS * LDS_STRIDE];    // [sample][feature]
+    __shared__ __attribute__((aligned(16))) uint16_t xT[64 * LDS_STRIDE];      // [feature][sample]
+    __shared__ __attribute__((aligned(16))) uint16_t a1s[ROWS * LDS_STRIDE];   // [sample][unit]
+    __shared__ __attribute__((aligned(16))) uint16_t a1T[64 * LDS_STRIDE];     // [unit][sample]
+    __shared__ __attribute__((aligned(16))) uint16_t dz2s[ROWS * LDS_STRIDE];  // [sample][unit]
+    __shared__ __attribute__((aligned(16))) uint16_t dz2T[64 * LDS_STRIDE];    // [unit][sample]
+    __shared__ __attribute__((aligned(16))) uint16_t dz1T[64 * LDS_STRIDE];    // [unit][sample]
+    __shared__ float opart[4][ROWS];                                            // output layer, per unit tile
+    __shared__ float gsmall[3 * HD + 1];                                        // db1, db2, dw3, db3
+    __shared__ float lsum;
+    const int t = threadIdx.x, w = t >> 6, l = t & 63, q = l >> 4, c = l & 15;
+    const int sw = w >> 2, nt = w & 3, u = 16 * nt + c, m0 = 16 * sw + 4 * q;   // this lane's unit, first sample
+    for (int i = t; i < 3 * HD + 1; i += NT) gsmall[i] = 0.f;
+    if (t == 0) lsum = 0.f;
+    const bf16x8 w1a = frag(P->W1b + u * F, 0, q), w1b = frag(P->W1b + u * F, 1, q);
+    const bf16x8 w2a = frag(P->W2b + u * HD, 0, q), w2b = frag(P->W2b + u * HD, 1, q);
+    const bf16x8 w2ta = frag(P->W2bT + u * HD, 0, q), w2tb = frag(P->W2bT + u * HD, 1, q);
+    const float b1 = P->b1[u], b2 = P->b2[u], w3 = P->w3[u], b3 = P->b3;
+    f32x4 gW1[TILES] = {}, gW2[TILES] = {};
+    float gw3 = 0.f, gb2 = 0.f, gb1 = 0.f, gb3 = 0.f, ls = 0.f;
+
+    for (uint64_t row0 = (uint64_t)blockIdx.x * ROWS; row0 < n; row0 += (uint64_t)gridDim.x * ROWS) {
+        float r4[4], y4[4];
+        bool v4[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            gw3 += do4[r] * a2v[nt][r];
-            const float dz = do4[r] * P->w3[n] * gelu_grad(z2[nt][r]);
-            gb2 += dz;
-            const uint16_t b = bf16_bits(dz);
-            const int m = 16 * w + 4 * q + r;
-            dz2s[m * LDS_STRIDE + n] = b;
-            dz2T[n * LDS_STRIDE + m] = b;
+            const uint64_t row = row0 + m0 + r;
+            v4[r] = row < n;
+            r4[r] = v4[r] ? R[row] : 0.f;
+            y4[r] = v4[r] ? Y[row] : 0.f;
         }
-        atomicAdd(&gsmall[2 * HD + n], gw3);
-        atomicAdd(&gsmall[HD + n], gb2);
-    }
-    if (c == 0) {
-        float s = do4[0] + do4[1] + do4[2] + do4[3];
-        atomicAdd(&gsmall[3 * HD], s);
-    }
-    // a1 transposed for the W2 gradient
-    for (int i = threadIdx.x; i < 64 * 64; i += blockDim.x) {
-        const int m = i >> 6, k = i & 63;
-        a1T[k * LDS_STRIDE + m] = a1s[m * LDS_STRIDE + k];
-    }
-    __syncthreads();
-    // dW2[n][k] = sum_m dz2[m][n] a1[m][k]: rows n of this wavefront's slab
-    {
-        f32x4 acc[4];
-        gemm16x64([&](int i) { return dz2T + (16 * w + i) * LDS_STRIDE; },
-                  [&](int j) { return a1T + j * LDS_STRIDE; }, acc);
+        if (t < 8 * ROWS) {      // rows of 8 16-byte parts (zero beyond n), and the transposed copy
+            const int m = t >> 3, part = t & 7;
+            uint4 v = make_uint4(0, 0, 0, 0);
+            if (row0 + m < n) v = reinterpret_cast<const uint4 *>(X + (row0 + m) * F)[part];
+            *reinterpret_cast<uint4 *>(xs + m * LDS_STRIDE + part * 8) = v;
+            const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-        for (int jt = 0; jt < 4; ++jt)
+            for (int j = 0; j < 4; ++j) {
+                xT[(8 * part + 2 * j) * LDS_STRIDE + m] = (uint16_t)w4[j];
+                xT[(8 * part + 2 * j + 1) * LDS_STRIDE + m] = (uint16_t)(w4[j] >> 16);
+            }
+        }
+        __syncthreads();
+        // layer 1: this wavefront's 16 samples, 16 units
+        f32x4 z1 = tile64(xs + (16 * sw + c) * LDS_STRIDE, w1a, w1b, q);
+        uint32_t pk[2];
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                atomicAdd(&grad[OFF_W2 + (16 * w + 4 * q + r) * HD + 16 * jt + c], acc[jt][r]);
-    }
-    // da1 = dz2 W2 (this wavefront's 16 samples), dz1 = da1 * gelu'(z1)
-    {
-        f32x4 acc[4];
-        gemm16x64([&](int m) { return dz2s + (16 * w + m) * LDS_STRIDE; },
-                  [&](int k) { return P->W2bT + k * HD; }, acc);
+        for (int r = 0; r < 4; ++r) {
+            z1[r] += b1;
+            const uint32_t b = bf16_bits(gelu(z1[r]));
+            a1s[(m0 + r) * LDS_STRIDE + u] = (uint16_t)b;
+            pk[r >> 1] = (r & 1) ? pk[r >> 1] | b << 16 : b;
+        }
+        *reinterpret_cast<uint2 *>(a1T + u * LDS_STRIDE + m0) = make_uint2(pk[0], pk[1]);
+        __syncthreads();
+        // layer 2 and the output layer's sum over this tile's units
+        f32x4 z2 = tile64(a1s + (16 * sw + c) * LDS_STRIDE, w2a, w2b, q);
+        float a2[4];
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt) {
-            const int k = 16 * kt + c;
-            float gb1 = 0.f;
+        for (int r = 0; r < 4; ++r) {
+            z2[r] += b2;
+            a2[r] = bf16_float(bf16_bits(gelu(z2[r])));
+            float part = a2[r] * w3;
+#pragma unroll
+            for (int off = 1; off < 16; off <<= 1) part += __shfl_xor(part, off, 64);
+            if (c == 0) opart[nt][m0 + r] = part;
+        }
+        __syncthreads();
+        // loss gradient, output layer gradients, dz2
+        uint32_t pd[2];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float o = opart[0][m0 + r] + opart[1][m0 + r] + opart[2][m0 + r] + opart[3][m0 + r] + b3 + r4[r];
+            const float e = expf(o - y4[r]), d = e - 1.0f;
+            const float dor = v4[r] ? (d > 0.f ? e : (d < 0.f ? -e : 0.f)) * inv_batch : 0.f;
+            if (nt == 0 && c == 0) {       // once per sample
+                gb3 += dor;
+                if (v4[r]) ls += fabsf(d);
+            }
+            gw3 += dor * a2[r];
+            const float dz = dor * w3 * gelu_grad(z2[r]);
+            gb2 += dz;
+            const uint32_t b = bf16_bits(dz);
+            dz2s[(m0 + r) * LDS_STRIDE + u] = (uint16_t)b;
+            pd[r >> 1] = (r & 1) ? pd[r >> 1] | b << 16 : b;
+        }
+        *reinterpret_cast<uint2 *>(dz2T + u * LDS_STRIDE + m0) = make_uint2(pd[0], pd[1]);
+        __syncthreads();
+        // dW2[i][k] += sum_m dz2[m][i] a1[m][k]: row tiles sw + S j, column tile nt
+#pragma unroll
+        for (int j = 0; j < TILES; ++j)
+            gW2[j] += grad_tile<S>(dz2T + (16 * (sw + S * j) + c) * LDS_STRIDE, a1T + u * LDS_STRIDE, q);
+        // da1 = dz2 W2, dz1 = da1 * gelu'(z1)
+        {
+            const f32x4 da = tile64(dz2s + (16 * sw + c) * LDS_STRIDE, w2ta, w2tb, q);
+            uint32_t p1[2];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float dz = acc[kt][r] * gelu_grad(z1[kt][r]);
+                const float dz = da[r] * gelu_grad(z1[r]);
                 gb1 += dz;
-                dz1T[k * LDS_STRIDE + 16 * w + 4 * q + r] = bf16_bits(dz);
+                const uint32_t b = bf16_bits(dz);
+                p1[r >> 1] = (r & 1) ? p1[r >> 1] | b << 16 : b;
             }
-            atomicAdd(&gsmall[k], gb1);
+            *reinterpret_cast<uint2 *>(dz1T + u * LDS_STRIDE + m0) = make_uint2(p1[0], p1[1]);
         }
+        __syncthreads();
+        // dW1[j][f] += sum_m dz1[m][j] x[m][f]
+#pragma unroll
+        for (int j = 0; j < TILES; ++j)
+            gW1[j] += grad_tile<S>(dz1T + (16 * (sw + S * j) + c) * LDS_STRIDE, xT + u * LDS_STRIDE, q);
+        __syncthreads();       // xs and xT are free for the next samples
+    }
+
+#pragma unroll
+    for (int j = 0; j < TILES; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 16 * (sw + S * j) + 4 * q + r;
+            atomicAdd(&grad[OFF_W2 + row * HD + u], gW2[j][r]);
+            atomicAdd(&grad[OFF_W1 + row * F + u], gW1[j][r]);
+        }
+    // the four row groups of a unit's lanes, then the sample slabs
+#pragma unroll
+    for (int off = 16; off < 64; off <<= 1) {
+        gw3 += __shfl_xor(gw3, off, 64);
+        gb2 += __shfl_xor(gb2, off, 64);
+        gb1 += __shfl_xor(gb1, off, 64);
+    }
+    if (q == 0) {
+        atomicAdd(&gsmall[u], gb1);
+        atomicAdd(&gsmall[HD + u], gb2);
+        atomicAdd(&gsmall[2 * HD + u], gw3);
+    }
+    if (nt == 0 && c == 0) {
+        atomicAdd(&gsmall[3 * HD], gb3);
+        atomicAdd(&lsum, ls);
     }
     __syncthreads();
-    // dW1[j][f] = sum_m dz1[m][j] x[m][f]
-    {
-        f32x4 acc[4];
-        gemm16x64([&](int i) { return dz1T + (16 * w + i) * LDS_STRIDE; },
-                  [&](int f) { return xT + f * LDS_STRIDE; }, acc);
-#pragma unroll
-        for (int ft = 0; ft < 4; ++ft)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                atomicAdd(&grad[OFF_W1 + (16 * w + 4 * q + r) * F + 16 * ft + c], acc[ft][r]);
+    if (t < HD) {
+        atomicAdd(&grad[OFF_B1 + t], gsmall[t]);
+        atomicAdd(&grad[OFF_B2 + t], gsmall[HD + t]);
+        atomicAdd(&grad[OFF_W3 + t], gsmall[2 * HD + t]);
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < HD; i += blockDim.x) {
-        atomicAdd(&grad[OFF_B1 + i], gsmall[i]);
-        atomicAdd(&grad[OFF_B2 + i], gsmall[HD + i]);
-        atomicAdd(&grad[OFF_W3 + i], gsmall[2 * HD + i]);
-    }
-    if (threadIdx.x == 0) {
+    if (t == 0) {
         atomicAdd(&grad[OFF_B3], gsmall[3 * HD]);
         atomicAdd(loss, lsum * inv_batch);
     }
@@ -240,33 +300,25 @@ __global__ void k_adam(float *__restrict__ theta, const float *__restrict__ grad
     theta[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
-// Features of one host per thread from vate_estimate's histogram output.
-__global__ void k_features(const uint32_t *__restrict__ hist, const float *__restrict__ est, uint64_t n,
-                           uint32_t k, uint32_t g, float occupancy, uint16_t *__restrict__ X,
-                           float *__restrict__ R)
+// Features of hosts from vate_estimate's histogram output, a wavefront per
+// host: lane f builds feature f, so a row is read and written in one piece.
+// (A thread per host took 20 us for 331 hosts, row by row through scratch.)
+__global__ void __launch_bounds__(256) k_features(const uint32_t *__restrict__ hist, const float *__restrict__ est,
+                                                  uint64_t n, uint32_t k, uint32_t g, float occupancy,
+                                                  uint16_t *__restrict__ X, float *__restrict__ R)
 {
-    const uint64_t h = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (h >= n) return;
-    const uint32_t *row = hist + h * (k + 1);
+    const uint32_t f = threadIdx.x & 63u;
     const float fg = (float)g;
-    uint32_t live = 0;
-    uint16_t out[F];
-    for (int f = 0; f < F; ++f) out[f] = 0;
-    for (uint32_t d = 0; d < k; ++d) {
-        live += row[d];
-        out[d] = bf16_bits((float)row[d] / fg);
+    for (uint64_t h = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6); h < n; h += (uint64_t)gridDim.x * 4) {
+        const uint32_t bin = f < k ? hist[h * (k + 1) + f] : 0u;      // k < 64
+        const float r = logf(fmaxf(est[h], 1.0f));
+        uint32_t live = bin;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) live += __shfl_xor(live, off, 64);
+        const float x = f <= k ? (float)(f < k ? bin : live) / fg : f == k + 1 ? occupancy : f == k + 2 ? r * 0.0625f : 0.f;
+        X[h * F + f] = bf16_bits(x);
+        if (f == 0) R[h] = r;
     }
-    out[k] = bf16_bits((float)live / fg);
-    out[k + 1] = bf16_bits(occupancy);
-    const float r = logf(fmaxf(est[h], 1.0f));
-    out[k + 2] = bf16_bits(r * 0.0625f);
-    uint4 *dst = reinterpret_cast<uint4 *>(X + h * F);
-    for (int j = 0; j < F / 8; ++j) {
-        uint32_t wv[4];
-        for (int t = 0; t < 4; ++t) wv[t] = (uint32_t)out[8 * j + 2 * t] | ((uint32_t)out[8 * j + 2 * t + 1] << 16);
-        dst[j] = make_uint4(wv[0], wv[1], wv[2], wv[3]);
-    }
-    R[h] = r;
 }
 
 __global__ void k_fill(float *__restrict__ p, int count, float value)
@@ -373,8 +425,14 @@ int vate_mlp_train_step(const void *weights_dev, const uint16_t *x_dev, const fl
         return VATE_E_INVAL;
     const uint64_t blocks = (n + 63) / 64;
     if (blocks > 0x7FFFFFFFull) return VATE_E_INVAL;
-    k_train<<<(unsigned)blocks, 256, 0, static_cast<hipStream_t>(stream)>>>(
-        static_cast<const Packed *>(weights_dev), x_dev, r_dev, y_dev, n, 1.0f / (float)n, grad_dev, loss_dev);
+    const Packed *P = static_cast<const Packed *>(weights_dev);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const float inv = 1.0f / (float)n;
+    if (n <= 2048)
+        k_train<2><<<(unsigned)((n + 31) / 32), 512, 0, st>>>(P, x_dev, r_dev, y_dev, n, inv, grad_dev, loss_dev);
+    else
+        k_train<4><<<(unsigned)(blocks < kTrainBlocks ? blocks : kTrainBlocks), 1024, 0, st>>>(
+            P, x_dev, r_dev, y_dev, n, inv, grad_dev, loss_dev);
     return mlp_check("train");
 }
 
@@ -404,9 +462,9 @@ int vate_mlp_features(const uint32_t *hist_dev, const float *est_dev, size_t n, 
     if (k < 1 || k + 3 > (uint32_t)F) return VATE_E_UNSUPPORTED;
     if (!hist_dev || !est_dev || !x_dev || !r_dev || g < 1 || (reinterpret_cast<uintptr_t>(x_dev) & 15u))
         return VATE_E_INVAL;
-    const uint64_t blocks = (n + 255) / 256;
-    if (blocks > 0x7FFFFFFFull) return VATE_E_INVAL;
-    k_features<<<(unsigned)blocks, 256, 0, static_cast<hipStream_t>(stream)>>>(
+    if ((n + 255) / 256 > 0x7FFFFFFFull) return VATE_E_INVAL;
+    const uint64_t blocks = (n + 3) / 4;
+    k_features<<<(unsigned)(blocks < 16384 ? blocks : 16384), 256, 0, static_cast<hipStream_t>(stream)>>>(
         hist_dev, est_dev, n, k, g, pool_active_fraction, x_dev, r_dev);
     return mlp_check("features");
 }

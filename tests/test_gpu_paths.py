@@ -6,6 +6,7 @@ import pytest
 torch = pytest.importorskip("torch")
 
 from paper_1812_00282_amd.sketch import Config  # noqa: E402
+from test_gpu_learned import test_gradient_parity as gradient_parity  # noqa: E402
 from test_gpu_parity import _check_estimates, _check_state, _pair, _u32  # noqa: E402
 
 pytestmark = pytest.mark.gpu
@@ -162,3 +163,10 @@ def test_batch_sliced_members():
             sk.close_slice()
             est, live, _ = sk.estimate(hosts[i], kprime=kp[i])
             assert torch.equal(b.live[i], live) and torch.equal(b.est[i], est), (t, i)
+
+
+# Training takes 32 or 64 samples per workgroup, and beyond 256 workgroups
+# several times over: gradients and loss against the FP64 network.
+@pytest.mark.parametrize("n", [1, 33, 2048, 2049, 16_385])
+def test_training_sample_tiles(n):
+    gradient_parity(n)
