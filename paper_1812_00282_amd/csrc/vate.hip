@@ -1472,16 +1472,21 @@ static int launch_part(vate_sketch *s, const PartGeo &pg, void *ws, const uint32
                        uint32_t kprime, float *est, uint32_t *live, uint32_t *hist, const Windows &win,
                        const void *weights, float *cf, hipStream_t st, int steps = PART_ALL)
 {
-    if (!allow_lds<k_run_scatter>(s) || !allow_lds<k_run_lookup<W>>(s) || !allow_lds<k_run_finalize<MODE>>(s))
+    if (!allow_lds<k_run_scatter>(s) || !allow_lds<k_run_lookup<W, true>>(s) || !allow_lds<k_run_lookup<W, false>>(s) ||
+         !allow_lds<k_run_finalize<MODE>>(s))
         return check_launch(s, "dynamic LDS");
     const RunWs w = run_ws(s->G, n, pg.hosts, ws);
     if (steps != PART_RUN)
         k_run_scatter<<<std::min(pg.n_sub, s->n_cu), kRunThreads, pg.lds_scatter, st>>>(s->G, pg, hosts, n, w.entries,
                                                                                        w.table);
     if (steps == PART_PLAN) return VATE_OK;
-    k_run_lookup<W><<<pg.n_slices * pg.split, kRunThreads, pg.lds_lookup, st>>>(
-        s->G, pg, s->pool, reinterpret_cast<const uint32_t *>(s->bitmap), s->st, w.entries, w.table, w.hits,
-        w.heads);
+    auto lookup = [&](auto dists) {
+        k_run_lookup<W, decltype(dists)::value><<<pg.n_slices * pg.split, kRunThreads, pg.lds_lookup, st>>>(
+            s->G, pg, s->pool, reinterpret_cast<const uint32_t *>(s->bitmap), s->st, w.entries, w.table, w.hits,
+            w.heads);
+    };
+    if (MODE != kFinClosedForm || hist != nullptr || kprime < s->p.k) lookup(std::true_type{});
+    else lookup(std::false_type{});
     k_run_finalize<MODE><<<(pg.n_sub + pg.fgroup - 1) / pg.fgroup, kFinThreads, pg.lds_final, st>>>(
         s->G, pg, s->st, n, kprime, w.hits, w.heads, w.table, est, live, hist, win,
         static_cast<const mlp::Packed *>(weights), cf);
