@@ -814,6 +814,7 @@ constexpr int kLearnMaxK = VATE_MLP_FEATURES - 3;
 
 #include "vate_part.h"
 #include "vate_sliced.h"
+#include "vate_parts.h"
 
 __global__ void k_set_clock(Geo G, DevState *__restrict__ st, unsigned long long t, uint32_t bact0)
 {
@@ -1166,12 +1167,45 @@ static void by_slices(const vate_sketch *s, uint32_t n, bool small, F &&f)
 // Workgroups of `lds` bytes that a CU holds.
 static unsigned sliced_cap(const vate_sketch *s, uint32_t lds) { return s->n_cu * (s->G.c <= kSliceLog2 && lds <= s->lds_budget / 2 ? 2u : 1u); }
 
+// Whether the closed form goes by parts of the bitmap (k_parts_count): window
+// k, a bitmap larger than an XCD's L2, and enough gathers (a block of 32 VATs or
+// more is one) to pay for three launches and a pass over the bitmap.
+static bool parts_gather(const vate_sketch *s, uint32_t n, uint32_t kprime)
+{
+    const Geo &G = s->G;
+    if (parts_log2(G.c) == 0 || kprime != G.k) return false;
+    const uint64_t gathers = blocked_gather_ok(G, kprime) ? (G.g + (1u << G.blog) - 1u) >> G.blog : G.g;
+    return n * gathers >= kPartsMin;
+}
+
+static void launch_parts(vate_sketch *s, const uint32_t *hosts, uint32_t n, float *est, uint32_t *live, hipStream_t st)
+{
+    uint32_t *acc = live ? live : reinterpret_cast<uint32_t *>(est);
+    const uint32_t *bitmap = reinterpret_cast<const uint32_t *>(s->bitmap);
+    const Geo &G = s->G;
+    const bool blocked = blocked_gather_ok(G, G.k);
+    // lanes per host: one while the hosts alone fill the chip
+    const uint32_t gathers = blocked ? (G.g + (1u << G.blog) - 1u) >> G.blog : G.g;
+    const uint64_t threads = 2048ull * s->n_cu >> (3u - parts_log2(G.c));
+    uint32_t lg = 0;
+    while (lg < 6 && ((uint64_t)n << lg) < threads && (8u << lg) < gathers) ++lg;
+    const unsigned grid = (std::max(1u, grid_for((uint64_t)n << lg, kPartsThreads, s->n_cu)) + 7u) & ~7u;
+    k_parts_clear<<<grid_for(n, 256, 4u * s->n_cu), 256, 0, st>>>(n, acc);
+    if (blocked) k_parts_count<true><<<grid * 8u, kPartsThreads, 0, st>>>(G, bitmap, hosts, n, lg, acc);
+    else k_parts_count<false><<<grid * 8u, kPartsThreads, 0, st>>>(G, bitmap, hosts, n, lg, acc);
+    k_parts_finish<<<grid_for(n, 256, 4u * s->n_cu), 256, 0, st>>>(G, s->st, n, acc, est);
+}
+
 // The closed form without histograms.  Lanes per host: as many as keep the
 // chip's 2048 threads per CU busy, so that few hosts take few serial rounds.
 template <int W>
 static void launch_estimate(vate_sketch *s, const uint32_t *hosts, uint32_t n, uint32_t kprime, float *est,
                             uint32_t *live, hipStream_t st)
 {
+    if (parts_gather(s, n, kprime)) {
+        launch_parts(s, hosts, n, est, live, st);
+        return;
+    }
     if (blocked_gather_ok(s->G, kprime)) {
         const uint32_t nb = (s->G.g + (1u << s->G.blog) - 1u) >> s->G.blog;
         uint32_t lg = 0;
@@ -1375,14 +1409,18 @@ static uint32_t part_hosts(const vate_sketch *s, uint64_t n, size_t have)
 // ATs, g = 64 .. 1024) they break even at lookups x ATs of about 2^49: 2M
 // lookups on 2^28 ATs (36 us each way), 16M on 2^25 (70), 64M on 2^23 (240);
 // from 2^27 to 2^26 at half of that.  A plan's runs leave out the first pass:
-// half the lookups.  On 2^23 ATs the closed form stays with k_sliced, below
-// everything does (512M lookups on 2^22: 0.87 of the partitioned time by
-// gathers).
-enum PartUse { PART_FORM, PART_HIST, PART_PLANNED };   // the closed form; histograms, windows, learned; a plan
+// half the lookups.  The closed form for window k, which from 2^26 ATs on is
+// gathered by parts, breaks even at 6M to 10M there (8M on 2^28: 51 us by parts,
+// 48 partitioned).  On 2^23 ATs it stays with k_sliced, below everything does
+// (512M lookups on 2^22: 0.87 of the partitioned time by gathers).
+enum PartUse { PART_FORM, PART_HIST, PART_PLANNED };   // the closed form for k; what needs distances; a plan
 static bool partitioned(const vate_sketch *s, uint64_t n, PartUse use)
 {
-    return s->G.c >= (use == PART_FORM ? kPartLog2 + 1u : kPartLog2) &&
-           n * s->G.g >= (kPartMin >> s->G.c >> (use == PART_PLANNED ? 1 : 0)) && part_max_hosts(s, n) > 0;
+    if (s->G.c < (use == PART_FORM ? kPartLog2 + 1u : kPartLog2)) return false;
+    uint64_t least = kPartMin >> s->G.c;
+    if (use == PART_FORM) least = std::max(least, kPartFormMin);
+    if (use == PART_PLANNED) least /= 2;
+    return n * s->G.g >= least && part_max_hosts(s, n) > 0;
 }
 
 // The workspace size reported to callers: enough for the even subgroups.
@@ -1657,7 +1695,7 @@ static int estimate_ws_impl(vate_sketch *s, const uint32_t *hosts_dev, size_t n_
     if (workspace_dev == s->plan_ws) s->plan_ws = nullptr;   // the plan is overwritten
     if (hist_dev && s->p.k > (uint32_t)kMaxHistK && part_max_hosts(s, n) == 0)
         return fail(s, VATE_E_UNSUPPORTED, "per-host histogram of this geometry needs k <= 256");
-    if (!partitioned(s, n, hist_dev ? PART_HIST : PART_FORM)) {
+    if (!partitioned(s, n, hist_dev || kprime < s->p.k ? PART_HIST : PART_FORM)) {
         direct_estimate(s, hosts_dev, n, kprime, est_dev, live_dev, hist_dev, st);
         return check_launch(s, what);
     }

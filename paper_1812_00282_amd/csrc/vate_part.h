@@ -910,6 +910,7 @@ constexpr uint32_t kGatherU = 8;
 constexpr uint64_t kSlicedMin = 1u << 21;
 constexpr uint32_t kPartLog2 = 23;         // smallest pool (log2) whose lookups are partitioned
 constexpr uint64_t kPartMin = 3ull << 47;  // lookups times pool size from which they are
+constexpr uint64_t kPartFormMin = 6u << 20;   // and lookups, for the closed form for window k
 
 template <int W, int MODE>
 __global__ void __launch_bounds__(kFinThreads) k_gather(Geo G, const uint8_t *__restrict__ pool,

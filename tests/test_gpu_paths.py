@@ -170,3 +170,31 @@ def test_batch_sliced_members():
 @pytest.mark.parametrize("n", [1, 33, 2048, 2049, 16_385])
 def test_training_sample_tiles(n):
     gradient_parity(n)
+
+
+# The closed form by parts of the bitmap (2^26 ATs and more, window k): two,
+# four and eight parts, one lane per host and several, locality blocks of one
+# word, of two and more, the last block cut short; with and without live counts.
+@pytest.mark.parametrize("c,w,k,g,n_hosts,b", [
+    (26, 8, 60, 1024, 3100, 0), (27, 4, 7, 100, 40_003, 0), (28, 8, 60, 1000, 30_000, 0), (28, 4, 3, 7, 500_009, 0),
+    (26, 8, 60, 1000, 110_001, 5), (28, 8, 20, 2048, 100_001, 6), (27, 8, 60, 1500, 300_000, 7)])
+def test_estimate_by_parts(c, w, k, g, n_hosts, b):
+    rng = np.random.default_rng(c * 1000 + g)
+    gpu, ref = _pair(Config(c, w, k, g, seed_a=5, seed_b=6, block_log2=b))
+    hosts = rng.integers(0, 2**32, n_hosts, dtype=np.uint64).astype(np.uint32)
+    some = hosts[:300]
+    for t in range(3):
+        p = _stream(rng, 200_000, some, 2**32)
+        gpu.ingest(p)
+        ref.ingest(p)
+        gpu.close_slice()
+        ref.close_slice()
+    est, live, _ = gpu.estimate(hosts)
+    _, r_live, _ = ref.estimate(some)
+    np.testing.assert_array_equal(_u32(live)[:300], r_live)
+    pieces = [gpu.estimate(hosts[i:i + 300]) for i in range(0, n_hosts, max(300, n_hosts // 20))]   # few hosts: gathered
+    for j, (e, lv, _) in enumerate(pieces):
+        i = j * max(300, n_hosts // 20)
+        assert torch.equal(live[i:i + 300], lv) and torch.equal(est[i:i + 300], e)
+    alone, _, _ = gpu.estimate(hosts, want_live=False)
+    assert torch.equal(est, alone)
