@@ -157,8 +157,10 @@ int vate_estimate_workspace_bytes(const vate_sketch *s, size_t n_hosts, size_t *
  * host's distance histogram is rebuilt from them.  workspace_dev (256-byte
  * aligned, at least vate_estimate_workspace_bytes) is scratch owned by the
  * caller; calls that share a workspace must not overlap.  Sketches outside
- * the path's limits (g above the sort's capacity, the locality-blocked H)
- * fall back to vate_estimate's gather.  Errors: as vate_estimate, plus
+ * the path's limits (g above the sort's capacity, the locality-blocked H), and
+ * calls for which it does not pay (pools below 2^23 ATs, few hosts), are
+ * answered by vate_estimate's kernels, with the same results and the same
+ * demands on the workspace.  Errors: as vate_estimate, plus
  * VATE_E_INVAL for a missing or small workspace. */
 int vate_estimate_ws(vate_sketch *s, const uint32_t *hosts_dev, size_t n_hosts,
                      uint32_t kprime, float *est_dev, uint32_t *live_dev, uint32_t *hist_dev,
@@ -189,6 +191,8 @@ int vate_estimate_noalloc(vate_sketch *s, const uint32_t *hosts_dev, size_t n_ho
  *     (any slice phase; hosts_dev is read during the call's stream work only),
  *   vate_estimate_run answers a closed slice from that plan (lookups and
  *     histograms only) with vate_estimate_ws's outputs and layouts.
+ * Where vate_estimate_ws would not sort, the plan is the host list, copied
+ * into the workspace.
  * The plan belongs to the sketch and to this workspace and host count; it
  * stays valid until the workspace is used by another estimate call.  A
  * changed host list needs a new plan.  Errors: VATE_E_UNSUPPORTED (plan for a

@@ -5,8 +5,11 @@
 // Paper: Xu, Ding, Hu, "VATE: a trade-off between memory and preserving time
 // for high accuracy cardinalities estimation under sliding time window",
 // arXiv 1812.00282.  Algorithm 4 is the per-slice loop; Sec. 4.2 describes
-// its three GPU phases (scan, estimate, maintain), which map to
-// k_ingest, k_census + k_estimate and k_advance + k_preserve here.
+// its three GPU phases (scan, estimate, maintain), which map to k_ingest,
+// k_census + the estimate kernels and k_advance + k_preserve here.  An estimate
+// gathers its VATs' bits one by one (k_estimate, k_gather), from LDS slice by
+// slice (vate_sliced.h), one part of the bitmap per XCD (vate_parts.h), or
+// sorted by pool slice (vate_part.h), by the sketch and the number of hosts.
 
 #include <hip/hip_runtime.h>
 
@@ -48,7 +51,7 @@ __host__ __device__ __forceinline__ const unsigned long long *census_of(const De
 {
     return reinterpret_cast<const unsigned long long *>(st + 1);
 }
-constexpr int kMaxHistK = 256;              // largest k of the direct gather's histograms
+constexpr int kMaxHistK = 256;              // largest k of vate_estimate's histograms
 constexpr uint32_t kCensusLdsBins = 4096;   // census histogram bins kept in LDS
 
 // State block layout: header, k census counters, then (256-byte aligned) the
@@ -1409,7 +1412,10 @@ static uint32_t part_hosts(const vate_sketch *s, uint64_t n, size_t have)
 // ATs, g = 64 .. 1024) they break even at lookups x ATs of about 2^49: 2M
 // lookups on 2^28 ATs (36 us each way), 16M on 2^25 (70), 64M on 2^23 (240);
 // from 2^27 to 2^26 at half of that.  A plan's runs leave out the first pass:
-// half the lookups.  The closed form for window k, which from 2^26 ATs on is
+// half the lookups.  Beyond 2^28 ATs a pass over the bitmap of a larger pool has
+// to be earned (k' < k, gathered and partitioned: 2^30 ATs 2M lookups 44 and 77
+// us, 6M 119 and 84; 2^32 2M 44 and 616, 64M 1,223 and 1,067), so the number
+// doubles with the pool from there.  The closed form for window k, which from 2^26 ATs on is
 // gathered by parts, breaks even at 6M to 10M there (8M on 2^28: 51 us by parts,
 // 48 partitioned).  On 2^23 ATs it stays with k_sliced, below everything does
 // (512M lookups on 2^22: 0.87 of the partitioned time by gathers).
@@ -1417,7 +1423,7 @@ enum PartUse { PART_FORM, PART_HIST, PART_PLANNED };   // the closed form for k;
 static bool partitioned(const vate_sketch *s, uint64_t n, PartUse use)
 {
     if (s->G.c < (use == PART_FORM ? kPartLog2 + 1u : kPartLog2)) return false;
-    uint64_t least = kPartMin >> s->G.c;
+    uint64_t least = s->G.c <= 28 ? kPartMin >> s->G.c : (kPartMin >> 28) << (s->G.c - 28u);
     if (use == PART_FORM) least = std::max(least, kPartFormMin);
     if (use == PART_PLANNED) least /= 2;
     return n * s->G.g >= least && part_max_hosts(s, n) > 0;
