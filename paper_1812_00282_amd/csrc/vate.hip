@@ -1205,7 +1205,8 @@ template <int W>
 static void launch_estimate(vate_sketch *s, const uint32_t *hosts, uint32_t n, uint32_t kprime, float *est,
                             uint32_t *live, hipStream_t st)
 {
-    if (parts_gather(s, n, kprime)) {
+    // (the parts' counts would overwrite a host list that is also their output)
+    if (parts_gather(s, n, kprime) && hosts != (live ? live : reinterpret_cast<const uint32_t *>(est))) {
         launch_parts(s, hosts, n, est, live, st);
         return;
     }

@@ -5,7 +5,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
-from paper_1812_00282_amd.sketch import Config  # noqa: E402
+from paper_1812_00282_amd.sketch import Config, Sketch  # noqa: E402
 from test_gpu_learned import test_gradient_parity as gradient_parity  # noqa: E402
 from test_gpu_parity import _check_estimates, _check_state, _pair, _u32  # noqa: E402
 
@@ -198,3 +198,21 @@ def test_estimate_by_parts(c, w, k, g, n_hosts, b):
         assert torch.equal(live[i:i + 300], lv) and torch.equal(est[i:i + 300], e)
     alone, _, _ = gpu.estimate(hosts, want_live=False)
     assert torch.equal(est, alone)
+
+
+# The host list's own buffer as the live counts' or the estimates' output, at a
+# size that is otherwise answered by parts and at one that is not.
+@pytest.mark.parametrize("n_hosts", [300, 3100])
+def test_estimate_over_its_hosts(n_hosts):
+    rng = np.random.default_rng(n_hosts)
+    gpu = Sketch(Config(26, 8, 60, 1024, seed_a=5, seed_b=6))
+    hosts = torch.from_numpy(rng.integers(0, 2**32, n_hosts, dtype=np.uint64).astype(np.uint32).view(np.int32)).cuda()
+    gpu.ingest(_stream(rng, 200_000, hosts.cpu().numpy().view(np.uint32)[:300], 2**32))
+    gpu.close_slice()
+    est, live, _ = gpu.estimate(hosts)
+    over = hosts.clone()
+    e, _, _ = gpu.estimate(over, out=(torch.empty_like(est), over, None))
+    assert torch.equal(over, live) and torch.equal(e, est)
+    over = hosts.clone()
+    gpu.estimate(over, out=(over.view(torch.float32), None, None))
+    assert torch.equal(over.view(torch.float32), est)
