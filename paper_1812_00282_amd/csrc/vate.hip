@@ -1243,6 +1243,9 @@ static void launch_estimate(vate_sketch *s, const uint32_t *hosts, uint32_t n, u
     else go(integral_constant<int, 4>{}, integral_constant<int, 16>{});
 }
 
+// HIP refuses a grid of 2^32 threads and more: the most workgroups of 256.
+constexpr unsigned kMaxGrid256 = (1u << 24) - 1u;
+
 // The direct gather with per-host distance histograms (MODE as in
 // finish_hosts).  Hosts per workgroup: 1 while the chip has room for a
 // workgroup per host, up to 16, or 64 for the network.  Many lookups on a small
@@ -1291,7 +1294,7 @@ static void launch_gather(vate_sketch *s, const uint32_t *hosts, uint32_t n, uin
     uint32_t lg = 0;
     while (lg < most && (row_bytes << (lg + 1)) <= 32u * 1024u && ((uint64_t)n >> lg) > room * s->n_cu) ++lg;
     if (!allow_lds<k_gather<W, MODE>>(s)) return;
-    k_gather<W, MODE><<<grid_for(n, 1u << lg, 1u << 30), 256, row_bytes << lg, st>>>(
+    k_gather<W, MODE><<<grid_for(n, 1u << lg, kMaxGrid256), 256, row_bytes << lg, st>>>(
         s->G, s->pool, s->st, s->bitmap, hosts, n, lg, rowp, kprime, est, live, hist, win, net, cf);
 }
 

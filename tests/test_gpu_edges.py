@@ -1,0 +1,46 @@
+"""Edges of the estimate calls: launches past a grid's limit, workspaces between
+two layouts, outputs over the host list."""
+import ctypes
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1812_00282_amd import _lib  # noqa: E402
+from paper_1812_00282_amd.sketch import Config, Sketch  # noqa: E402
+from test_gpu_parity import _pair, _tol  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _hosts(rng, n):
+    return rng.integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)
+
+
+def _packets(rng, n, hosts):
+    return np.stack([hosts[rng.integers(0, hosts.size, n)], _hosts(rng, n)], 1)
+
+
+def test_windows_of_2_24_hosts():
+    """One host per workgroup (rows of 8191 distances) and 2^24 hosts: more
+    workgroups of 256 threads than one grid takes."""
+    k, n = 8191, 2**24
+    rng = np.random.default_rng(24)
+    gpu, ref = _pair(Config(14, 14, k, 1, seed_a=1, seed_b=2))
+    hosts = torch.randint(-2**31, 2**31, (n,), device="cuda", dtype=torch.int64,
+                          generator=torch.Generator("cuda").manual_seed(1)).to(torch.int32)
+    for t in range(3):
+        p = _packets(rng, 3000, hosts[:2000].cpu().numpy().view(np.uint32))
+        gpu.ingest(p)
+        ref.ingest(p)
+        gpu.close_slice()
+        ref.close_slice()
+    est = gpu.estimate_windows(hosts, [1, k])
+    for j, kp in enumerate((1, k)):
+        one, _, _ = gpu.estimate(hosts, kprime=kp)
+        assert torch.equal(est[:, j], one), kp
+        few = torch.cat([hosts[:500], hosts[-500:]]).cpu().numpy().view(np.uint32)
+        r_est, _, _ = ref.estimate(few, kprime=kp)
+        got = torch.cat([est[:500, j], est[-500:, j]]).cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got - r_est) <= _tol(r_est, ref.g)), kp
