@@ -1814,7 +1814,9 @@ static int check_plan(vate_sketch *s, size_t n_hosts, const void *workspace_dev,
     if (!s->closed) return fail(s, VATE_E_STATE, "estimate needs a closed slice (call vate_close_slice)");
     if (!workspace_dev || workspace_dev != s->plan_ws || n_hosts != s->plan_n)
         return fail(s, VATE_E_STATE, "no plan for this workspace and host count (call vate_estimate_plan)");
-    if (workspace_bytes < workspace_need(s, n_hosts)) return fail(s, VATE_E_INVAL, "workspace too small");
+    // (a plan of even subgroups takes more than the least that a plan may be given)
+    const size_t need = s->plan_hosts ? run_ws(s->G, n_hosts, s->plan_hosts, nullptr).bytes : workspace_need(s, n_hosts);
+    if (workspace_bytes < need) return fail(s, VATE_E_INVAL, "workspace too small");
     return VATE_OK;
 }
 

@@ -44,3 +44,41 @@ def test_windows_of_2_24_hosts():
         r_est, _, _ = ref.estimate(few, kprime=kp)
         got = torch.cat([est[:500, j], est[-500:, j]]).cpu().numpy().astype(np.float64)
         assert np.all(np.abs(got - r_est) <= _tol(r_est, ref.g)), kp
+
+
+def test_run_needs_the_plans_workspace():
+    """A plan may be laid out with fewer hosts per subgroup, and more run padding,
+    than the least workspace a plan may be given holds: a run that states less
+    than its plan's layout is refused, one that states all of it is answered."""
+    rng = np.random.default_rng(5)
+    n = 20_011                                   # 742 subgroups of 27, not 527 of 38
+    gpu = Sketch(Config(28, 8, 60, 1024, seed_a=3, seed_b=4))
+    hosts = _hosts(rng, n)
+    gpu.ingest(_packets(rng, 50_000, hosts[:300]))
+    gpu.close_slice()
+    full = gpu.workspace_bytes(n)
+    ws = torch.empty(full, dtype=torch.uint8, device="cuda")
+    h = torch.from_numpy(hosts.view(np.int32)).cuda()
+    lib, est = _lib.lib(), torch.empty(n, dtype=torch.float32, device="cuda")
+    _lib.check(lib.vate_estimate_plan(gpu.handle, h.data_ptr(), n, ws.data_ptr(), full, None), gpu.handle)
+
+    def run(stated):
+        return lib.vate_estimate_run(gpu.handle, n, 60, est.data_ptr(), None, None, ws.data_ptr(), stated, None)
+
+    assert run(full - 256) == _lib.VATE_E_INVAL
+    _lib.check(run(full), gpu.handle)
+    torch.cuda.synchronize()
+    assert torch.equal(est, gpu.estimate(hosts)[0])
+    # planned with less: the larger subgroups' layout, which then is enough
+    refused, least = 0, full
+    while least - refused > 256:
+        mid = (refused + least) // 512 * 256
+        if lib.vate_estimate_plan(gpu.handle, h.data_ptr(), n, ws.data_ptr(), mid, None) == _lib.VATE_OK:
+            least = mid
+        else:
+            refused = mid
+    _lib.check(lib.vate_estimate_plan(gpu.handle, h.data_ptr(), n, ws.data_ptr(), least, None), gpu.handle)
+    assert least < full
+    _lib.check(run(least), gpu.handle)
+    torch.cuda.synchronize()
+    assert torch.equal(est, gpu.estimate(hosts)[0])
