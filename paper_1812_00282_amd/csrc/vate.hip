@@ -15,6 +15,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <initializer_list>
 #include <type_traits>
 #include <cstdio>
 #include <cstring>
@@ -1449,6 +1450,30 @@ static size_t multi_need(const vate_sketch *s, uint64_t n)
     return align256((size_t)n * (s->p.k + 1) * 4) + align256(8ull * (s->p.k + 1));
 }
 
+// The calls with a workspace may put their outputs over the host list: the
+// partitioned path writes them when all hosts have been read.  The gathers
+// don't, so they get a copy of such a list, in the workspace (which holds 8 g
+// bytes per host and more wherever there is a partitioned geometry; where there
+// is none, every such call has always gathered).
+struct Output {
+    const void *p;
+    size_t bytes;
+};
+
+static const uint32_t *hosts_to_gather(const vate_sketch *s, const uint32_t *hosts, uint32_t n, void *workspace,
+                                       std::initializer_list<Output> outputs, hipStream_t st)
+{
+    const uintptr_t lo = reinterpret_cast<uintptr_t>(hosts), hi = lo + 4ull * n;
+    bool over = false;
+    for (const Output &o : outputs) {
+        const uintptr_t p = reinterpret_cast<uintptr_t>(o.p);
+        over |= p != 0 && p < hi && lo < p + o.bytes;
+    }
+    if (!over || part_max_hosts(s, n) == 0) return hosts;
+    k_copy_hosts<<<grid_for(n, 256, 4096), 256, 0, st>>>(hosts, n, static_cast<uint32_t *>(workspace));
+    return static_cast<const uint32_t *>(workspace);
+}
+
 // The geometry for n hosts, `hosts` per subgroup (from part_hosts).
 static PartGeo part_geo(const vate_sketch *s, uint64_t n, uint32_t hosts)
 {
@@ -1706,7 +1731,9 @@ static int estimate_ws_impl(vate_sketch *s, const uint32_t *hosts_dev, size_t n_
     if (hist_dev && s->p.k > (uint32_t)kMaxHistK && part_max_hosts(s, n) == 0)
         return fail(s, VATE_E_UNSUPPORTED, "per-host histogram of this geometry needs k <= 256");
     if (!partitioned(s, n, hist_dev || kprime < s->p.k ? PART_HIST : PART_FORM)) {
-        direct_estimate(s, hosts_dev, n, kprime, est_dev, live_dev, hist_dev, st);
+        const uint32_t *hosts = hosts_to_gather(s, hosts_dev, n, workspace_dev, {{est_dev, 4ull * n}, {live_dev, 4ull * n},
+                                                {hist_dev, 4ull * n * (s->p.k + 1)}}, st);
+        direct_estimate(s, hosts, n, kprime, est_dev, live_dev, hist_dev, st);
         return check_launch(s, what);
     }
     const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes));
@@ -1884,7 +1911,9 @@ int vate_estimate_learned_ws(vate_sketch *s, const uint32_t *hosts_dev, size_t n
     const uint32_t n = (uint32_t)n_hosts;
     if (workspace_dev == s->plan_ws) s->plan_ws = nullptr;   // the plan is overwritten
     if (!partitioned(s, n, PART_HIST)) {
-        direct_learned(s, hosts_dev, n, weights_dev, est_dev, est_cf_dev, st);
+        const uint32_t *hosts = hosts_to_gather(s, hosts_dev, n, workspace_dev,
+                                                {{est_dev, 4ull * n}, {est_cf_dev, 4ull * n}}, st);
+        direct_learned(s, hosts, n, weights_dev, est_dev, est_cf_dev, st);
         return check_launch(s, "estimate_learned_ws");
     }
     const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes));
@@ -1936,8 +1965,9 @@ int vate_estimate_multi_ws(vate_sketch *s, const uint32_t *hosts_dev, size_t n_h
         if (rc != VATE_OK) return rc;
         return check_launch(s, "estimate_multi_ws");
     }
+    const uint32_t *hosts = hosts_to_gather(s, hosts_dev, n, workspace_dev, {{est_dev, 4ull * n * m}}, st);
     by_width(s->p.width, [&](auto W) {
-        launch_gather<decltype(W)::value, kFinMulti>(s, hosts_dev, n, s->p.k, est_dev, nullptr, nullptr, win, nullptr,
+        launch_gather<decltype(W)::value, kFinMulti>(s, hosts, n, s->p.k, est_dev, nullptr, nullptr, win, nullptr,
                                                      nullptr, st);
     });
     return check_launch(s, "estimate_multi_ws");

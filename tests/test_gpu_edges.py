@@ -82,3 +82,47 @@ def test_run_needs_the_plans_workspace():
     _lib.check(run(least), gpu.handle)
     torch.cuda.synchronize()
     assert torch.equal(est, gpu.estimate(hosts)[0])
+
+
+@pytest.mark.parametrize("at", [0, 1000, 290_000])
+def test_outputs_over_the_host_list(at):
+    """The calls with a workspace read the whole host list before they write: an
+    output buffer may hold it, here from word `at` on."""
+    from paper_1812_00282_amd import learned as L
+
+    rng = np.random.default_rng(at)
+    n, k = 300_000, 60
+    gpu = Sketch(Config(16, 8, k, 64, seed_a=3, seed_b=4))
+    hosts = torch.from_numpy(_hosts(rng, n).view(np.int32)).cuda()
+    gpu.ingest(_packets(rng, 50_000, hosts.cpu().numpy().view(np.uint32)))
+    gpu.close_slice()
+    wts = L.pack((torch.randn(_lib.MLP_PARAMS, generator=torch.Generator().manual_seed(1)) * 0.05).cuda(),
+                 L.new_weights())
+    ws = torch.empty(gpu.workspace_bytes(n), dtype=torch.uint8, device="cuda")
+    lib = _lib.lib()
+
+    def over(words):                             # a buffer of that many words with the host list in it
+        b = torch.zeros(max(words, at + n), dtype=torch.int32, device="cuda")
+        b[at:at + n] = hosts
+        return b, b.data_ptr() + 4 * at
+
+    est, live, hist = gpu.estimate(hosts, kprime=7, want_hist=True)
+    free = torch.empty(n, dtype=torch.float32, device="cuda")
+    for shape, which in ((n, "est"), (n, "live"), (n * (k + 1), "hist")):
+        b, h = over(shape)
+        e, lv, hi = (b.data_ptr() if which == x else None for x in ("est", "live", "hist"))
+        _lib.check(lib.vate_estimate_ws(gpu.handle, h, n, 7, e or free.data_ptr(), lv, hi, ws.data_ptr(), ws.numel(),
+                                        None), gpu.handle)
+        want = {"est": est.view(torch.int32), "live": live, "hist": hist}[which].reshape(-1)
+        assert torch.equal(b[:shape], want), which
+    kps = np.array([1, 7, 59, 60], dtype=np.uint32)
+    want = gpu.estimate_windows(hosts, kps)
+    b, h = over(4 * n)
+    _lib.check(lib.vate_estimate_multi_ws(gpu.handle, h, n, kps.ctypes.data, 4, b.data_ptr(), ws.data_ptr(),
+                                          ws.numel(), None), gpu.handle)
+    assert torch.equal(b[:4 * n].view(torch.float32).reshape(n, 4), want)
+    learned, cf = L.estimate_learned(gpu, hosts, wts)
+    b, h = over(n)
+    _lib.check(lib.vate_estimate_learned_ws(gpu.handle, h, n, wts.data_ptr(), b.data_ptr(), free.data_ptr(),
+                                            ws.data_ptr(), ws.numel(), None), gpu.handle)
+    assert torch.equal(b[:n].view(torch.float32), learned) and torch.equal(free, cf)
