@@ -37,8 +37,8 @@ struct DevState {
     unsigned long long t;        // current slice
     uint32_t bact0;              // ACT of block 0 (Eq. 7)
     uint32_t pad0;
-    uint32_t ticket[2];          // workgroups done (k_preserve, census), zero between kernels
-    uint32_t pad1[2];
+    uint32_t ticket;             // workgroups done (k_preserve), zero between kernels
+    uint32_t pad1[3];
 };
 constexpr size_t kStateHeader = sizeof(DevState);
 static_assert(kStateHeader == 32, "state header layout");
@@ -70,11 +70,9 @@ static size_t bitmap_bytes(uint64_t N)
 }
 
 // After the bitmap: kCensusCopies partial censuses (k counters each) that the
-// census workgroups add into, so that no counter takes an atomic from every
-// workgroup (they run one after the other, about 12 ns each: 2048 workgroups
-// on the two counters of a 2^26 nibble pool with k = 2 took 23 us);
-// k_census_fold then adds them to the census and clears them (they are zero
-// between censuses).
+// workgroups of large censuses add into, so that no counter takes an atomic
+// from every one of them; k_census_fold then adds them to the census and clears
+// them (they are zero between censuses).
 constexpr uint32_t kCensusCopies = 16;
 
 static size_t copies_offset(uint32_t k, uint64_t N)
@@ -154,15 +152,14 @@ int make_geo(const vate_params *p, Geo *G, const char **why)
 // ---------------------------------------------------------------------------
 // Container access.  AT p sits at bits [p*W, p*W+W) of the pool, little-endian.
 // ---------------------------------------------------------------------------
-// Kernels of at most this many workgroups end a step themselves (the clock,
-// the census's sum) in the workgroup that finishes last, instead of in a
-// kernel of their own: a launch costs the host 3 us and the GPU 2 to 5, a
-// ticket about 12 ns per workgroup, one after the other.
+// A preservation of at most this many workgroups steps the clock itself, in the
+// workgroup that finishes last, instead of in a kernel of its own: a launch
+// costs the host 3 us and the GPU 2 to 5, a ticket about 12 ns per workgroup,
+// one after the other.
 constexpr uint32_t kTicketMax = 64;
 
 // Whether this workgroup is the last of the launch to get here (every thread
-// of it calls).  What the others have done before is only seen where it was
-// done by atomics that had returned.
+// of it calls).
 __device__ __forceinline__ bool last_workgroup(uint32_t *ticket)
 {
     __shared__ uint32_t last;
@@ -175,30 +172,23 @@ __device__ __forceinline__ bool last_workgroup(uint32_t *ticket)
     return last != 0;
 }
 
-// Adds a census workgroup's LDS histogram to copy blockIdx mod kCensusCopies.
-// The copies are added to the census by k_census_fold, or (`ends`) by the last
-// workgroup, which takes them with atomics as they were put there.
+// Whether the workgroups of a census add into the census itself: few of them,
+// or few counters, so that the atomics (one per workgroup and counter) cost less
+// than the launch that folds the partial censuses.  (A slide of a 2^20 pool of
+// 7-bit ATs, k = 60: 19 us straight, 24 by copies; 2^28 nibbles, k = 7: 36 and
+// 57; but 2^24 7-bit ATs 45 and 27.)  Folding in the workgroup that ends last
+// takes as long as its k counters times kCensusCopies: 100 us at k = 4000, 17
+// straight.
+static bool census_direct(unsigned blocks, uint32_t k) { return blocks <= 256u || (uint64_t)blocks * k <= 16384u; }
+
+// Adds a census workgroup's LDS histogram to the census (`direct`) or to copy
+// blockIdx mod kCensusCopies, from where k_census_fold adds it.
 __device__ __forceinline__ void census_flush(const Geo &G, DevState *__restrict__ st, const uint32_t *hist,
-                                             unsigned long long *__restrict__ copies, bool ends)
+                                             unsigned long long *__restrict__ copies, bool direct)
 {
-    unsigned long long *mine = copies + (size_t)(blockIdx.x % kCensusCopies) * G.k;
-    if (!ends) {
-        for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x)
-            if (hist[d]) atomicAdd(&mine[d], (unsigned long long)hist[d]);
-        return;
-    }
+    unsigned long long *to = direct ? census_of(st) : copies + (size_t)(blockIdx.x % kCensusCopies) * G.k;
     for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x)
-        if (hist[d]) {
-            const unsigned long long was = atomicAdd(&mine[d], (unsigned long long)hist[d]);
-            asm volatile("" ::"v"(was));      // returned, so performed before the ticket is taken
-        }
-    if (!last_workgroup(&st->ticket[1])) return;
-    const uint32_t used = min(gridDim.x, kCensusCopies);
-    for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x) {
-        unsigned long long sum = 0;
-        for (uint32_t c = 0; c < used; ++c) sum += atomicExch(&copies[(size_t)c * G.k + d], 0ull);
-        census_of(st)[d] += sum;
-    }
+        if (hist[d]) atomicAdd(&to[d], (unsigned long long)hist[d]);
 }
 
 // ---------------------------------------------------------------------------
@@ -280,7 +270,7 @@ __global__ void __launch_bounds__(256) k_init(Geo G, uint4 *__restrict__ pool4, 
         if (threadIdx.x == 0) {
             st->t = 0;
             st->bact0 = 0;
-            st->ticket[0] = st->ticket[1] = 0;
+            st->ticket = 0;
         }
         for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x) census_of(st)[d] = 0;
         for (uint32_t d = threadIdx.x; d < kCensusCopies * G.k; d += blockDim.x) copies[d] = 0;
@@ -516,7 +506,7 @@ __device__ __forceinline__ uint32_t census_chunk_fast(const Geo &G, const uint4 
 template <int W>
 __global__ void __launch_bounds__(256) k_census(Geo G, const uint4 *__restrict__ pool4, uint64_t nchunks,
                                                 DevState *__restrict__ st, uint8_t *__restrict__ bitmap,
-                                                unsigned long long *__restrict__ copies, bool ends)
+                                                unsigned long long *__restrict__ copies, bool direct)
 {
     __shared__ uint32_t hist[kCensusLdsBins];
     const bool lds = G.k <= kCensusLdsBins;
@@ -543,7 +533,7 @@ __global__ void __launch_bounds__(256) k_census(Geo G, const uint4 *__restrict__
         }
     }
     __syncthreads();
-    if (lds) census_flush(G, st, hist, copies, ends);
+    if (lds) census_flush(G, st, hist, copies, direct);
 }
 
 // k_census8: the census of byte counters (k <= 255).  In steady
@@ -611,7 +601,7 @@ __device__ __forceinline__ void census8_round(const Geo &G, const uint4 (&v)[kCe
 
 __global__ void __launch_bounds__(256) k_census8(Geo G, const uint4 *__restrict__ pool4, uint64_t nchunks,
                                                  DevState *__restrict__ st, uint8_t *__restrict__ bitmap,
-                                                 unsigned long long *__restrict__ copies, bool ends)
+                                                 unsigned long long *__restrict__ copies, bool direct)
 {
     constexpr int U = kCensus8U;
     static_assert(U == 4, "one 8-byte bitmap store per lane and round");
@@ -657,7 +647,7 @@ __global__ void __launch_bounds__(256) k_census8(Geo G, const uint4 *__restrict_
             if (c0 + u < nchunks) bm16[c0 + u] = (uint16_t)bits[u];
     }
     __syncthreads();
-    census_flush(G, st, L.hist, copies, ends);
+    census_flush(G, st, L.hist, copies, direct);
 }
 
 __global__ void __launch_bounds__(256) k_census_fold(Geo G, DevState *__restrict__ st,
@@ -884,7 +874,7 @@ __global__ void __launch_bounds__(256) k_preserve(Geo G, uint4 *__restrict__ poo
     for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < 2 * max_chunks;
          j += (uint64_t)gridDim.x * blockDim.x)
         preserve_chunk<W>(G, pool4, bact0, j, max_chunks);
-    if (ends && last_workgroup(&st->ticket[0])) advance_clock(G, st);
+    if (ends && last_workgroup(&st->ticket)) advance_clock(G, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -1025,28 +1015,24 @@ static void launch_init(vate_sketch *s, hipStream_t st)
 template <int W>
 static void launch_census(vate_sketch *s, hipStream_t st)
 {
-    unsigned blocks;
     const bool lds = s->G.k <= kCensusLdsBins;      // longer windows are counted straight into the census
+    const uint64_t units = W == 0 ? s->G.N / 32 : s->pool_bytes / 16;
+    const unsigned blocks = W == 0 ? grid_for(units, 256, 16u * s->n_cu)
+                          : W == 8 ? grid_for(units, 256 * kCensus8U, 4096) : grid_for(units, 256 * 4, 2048);
+    const bool direct = census_direct(blocks, s->G.k);
     if constexpr (W == 0) {
-        const uint64_t ng = s->G.N / 32;
-        blocks = grid_for(ng, 256, 8u * s->n_cu);
         by_exact_width(s->p.width, [&](auto WB) {
             k_census_x<decltype(WB)::value><<<blocks, 256, 0, st>>>(s->G, reinterpret_cast<const uint32_t *>(s->pool),
-                                                                    ng, s->st, s->bitmap, s->copies,
-                                                                    blocks <= kTicketMax);
+                                                                    units, s->st, s->bitmap, s->copies, direct);
         });
     } else {
-        const uint64_t nch = s->pool_bytes / 16;
         const uint4 *pool4 = reinterpret_cast<const uint4 *>(s->pool);
-        if constexpr (W == 8) {         // k <= 255 (2^8 >= k + 1)
-            blocks = grid_for(nch, 256 * kCensus8U, 4096);
-            k_census8<<<blocks, 256, 0, st>>>(s->G, pool4, nch, s->st, s->bitmap, s->copies, blocks <= kTicketMax);
-        } else {
-            blocks = grid_for(nch, 256 * 4, 2048);
-            k_census<W><<<blocks, 256, 0, st>>>(s->G, pool4, nch, s->st, s->bitmap, s->copies, blocks <= kTicketMax);
-        }
+        if constexpr (W == 8)           // k <= 255 (2^8 >= k + 1)
+            k_census8<<<blocks, 256, 0, st>>>(s->G, pool4, units, s->st, s->bitmap, s->copies, direct);
+        else
+            k_census<W><<<blocks, 256, 0, st>>>(s->G, pool4, units, s->st, s->bitmap, s->copies, direct);
     }
-    if (lds && blocks > kTicketMax) k_census_fold<<<(s->G.k + 255) / 256, 256, 0, st>>>(s->G, s->st, s->copies);
+    if (lds && !direct) k_census_fold<<<(s->G.k + 255) / 256, 256, 0, st>>>(s->G, s->st, s->copies);
 }
 
 // The slide of the window: the clock and Alg. 3.

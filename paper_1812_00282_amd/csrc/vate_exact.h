@@ -133,7 +133,7 @@ __global__ void __launch_bounds__(256) k_init_x(Geo G, uint32_t *__restrict__ po
         if (threadIdx.x == 0) {
             st->t = 0;
             st->bact0 = 0;
-            st->ticket[0] = st->ticket[1] = 0;
+            st->ticket = 0;
         }
         for (uint32_t d = threadIdx.x; d < G.k; d += blockDim.x) census_of(st)[d] = 0;
         for (uint32_t d = threadIdx.x; d < kCensusCopies * G.k; d += blockDim.x) copies[d] = 0;
@@ -168,7 +168,8 @@ __device__ __forceinline__ void census_group_x(const Geo &G, const uint32_t *__r
 #pragma unroll
         for (int e = 0; e < 32; ++e) {
             const uint32_t u = top - vals[e];                       // ACT + 2k - value
-            const uint32_t d = G.dr ? vals[e] : min(u, u - G.twok); // the second wraps when u < 2k
+            // (one bit holds no AT; the second of the minimum wraps when u < 2k)
+            const uint32_t d = WB == 1 || G.dr ? vals[e] : min(u, u - G.twok);
             if (vals[e] != inact && d < G.k) {
                 bits |= 1u << e;
                 atomicAdd(&hist[d], 1u);
@@ -207,7 +208,7 @@ __device__ __forceinline__ void census_group_x(const Geo &G, const uint32_t *__r
 template <int WB>
 __global__ void __launch_bounds__(256) k_census_x(Geo G, const uint32_t *__restrict__ pool32, uint64_t ngroups,
                                                   DevState *__restrict__ st, uint8_t *__restrict__ bitmap,
-                                                  unsigned long long *__restrict__ copies, bool ends)
+                                                  unsigned long long *__restrict__ copies, bool direct)
 {
     __shared__ uint32_t hist[kCensusLdsBins];
     const bool lds = G.k <= kCensusLdsBins;
@@ -219,7 +220,7 @@ __global__ void __launch_bounds__(256) k_census_x(Geo G, const uint32_t *__restr
          gi += (uint64_t)gridDim.x * blockDim.x)
         census_group_x<WB>(G, pool32, gi, bact0, lds ? hist : nullptr, census_of(st), bitmap);
     __syncthreads();
-    if (lds) census_flush(G, st, hist, copies, ends);
+    if (lds) census_flush(G, st, hist, copies, direct);
 }
 
 // Alg. 3 on the two blocks whose ACT is 0 or k; thread j < max_groups takes
@@ -271,7 +272,7 @@ __global__ void __launch_bounds__(256) k_preserve_x(Geo G, uint32_t *__restrict_
     for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < 2 * max_groups;
          j += (uint64_t)gridDim.x * blockDim.x)
         preserve_group_x<WB>(G, pool32, bact0, j, max_groups);
-    if (ends && last_workgroup(&st->ticket[0])) advance_clock(G, st);
+    if (ends && last_workgroup(&st->ticket)) advance_clock(G, st);
 }
 
 // DR maintenance: every counter of group gi grows by one, saturating at k

@@ -126,3 +126,25 @@ def test_outputs_over_the_host_list(at):
     _lib.check(lib.vate_estimate_learned_ws(gpu.handle, h, n, wts.data_ptr(), b.data_ptr(), free.data_ptr(),
                                             ws.data_ptr(), ws.numel(), None), gpu.handle)
     assert torch.equal(b[:n].view(torch.float32), learned) and torch.equal(free, cf)
+
+
+# Census workgroups add into the census itself or into partial censuses: 256
+# workgroups and more, 16384 additions and more, windows at the LDS histogram's
+# limit and beyond, for every container, exact widths and both counters.
+@pytest.mark.parametrize("c,w,k,counter", [
+    (22, 8, 60, 0), (23, 8, 60, 0), (22, 7, 32, 0), (22, 7, 33, 0), (21, 16, 300, 0), (22, 16, 300, 0), (22, 4, 7, 0),
+    (23, 4, 7, 1), (16, 13, 4000, 0), (16, 14, 4096, 0), (16, 14, 4097, 0), (21, 9, 300, 1), (22, 9, 300, 1)])
+def test_census_additions(c, w, k, counter):
+    rng = np.random.default_rng(c * 1000 + k)
+    gpu, ref = _pair(Config(c, w, k, 64, seed_a=1, seed_b=2, counter=counter))
+    hosts = _hosts(rng, 3000)
+    for t in range(4):
+        p = _packets(rng, 60_000, hosts)
+        gpu.ingest(p)
+        ref.ingest(p)
+        gpu.close_slice()
+        ref.close_slice()
+        np.testing.assert_array_equal(gpu.census(), ref.census())
+    _, r_live, _ = ref.estimate(hosts[:300], kprime=max(1, k // 2))
+    live = gpu.estimate(hosts[:300], kprime=max(1, k // 2))[1]
+    np.testing.assert_array_equal(live.cpu().numpy().view(np.uint32), r_live)
