@@ -1480,14 +1480,15 @@ static PartGeo part_geo(const vate_sketch *s, uint64_t n, uint32_t hosts)
     const uint32_t cus = std::max<uint32_t>(1u, s->n_cu);
     // Subgroups per finalize workgroup: the network takes hosts in tiles of
     // 64, so the count whose hosts leave the least of their last tile empty
-    // (the fewest on a tie), as long as the histograms fit and every CU gets a
-    // workgroup.
+    // (the fewest on a tie), as long as every CU gets a workgroup and the
+    // histograms leave a CU room for three (147 hosts per subgroup, k = 60,
+    // 300,000 hosts: three subgroups, 55 KB, take 119 us, two, 36 KB, 95).
     {
         uint32_t best = 1;
         double waste = 1e30;
         for (uint32_t f = 1; f <= 16 && (f == 1 || f * cus <= p.n_sub); ++f) {
             const uint64_t fh = f * hosts;
-            if (fh * 4ull * p.rowp > kFinHistBytes) break;
+            if (fh * 4ull * p.rowp > (f == 1 ? kFinHistBytes : kFinGroupBytes)) break;
             const double w = (double)(((fh + 63) / 64) * 64 - fh) / (double)fh;
             if (w < waste - 1e-9) waste = w, best = f;
         }

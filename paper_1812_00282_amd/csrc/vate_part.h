@@ -55,6 +55,7 @@ constexpr uint32_t kRunMaxHosts = 1024;                         // hosts per sub
 constexpr uint32_t kFinThreads = 256;
 constexpr uint32_t kLookU = 8;                                  // 16-byte entry chunks per lane and lookup pass
 constexpr uint32_t kFinHistBytes = 64u * 1024u;                 // per-subgroup histogram ceiling
+constexpr uint32_t kFinGroupBytes = 40u * 1024u;                // and for several subgroups of a finalize workgroup
 
 struct PartGeo {
     uint32_t n_slices;    // N >> kSliceLog2
@@ -678,8 +679,9 @@ __host__ __device__ __forceinline__ uint32_t hist_row_words(uint32_t k) { return
 // The outputs of hosts h0 .. h0 + nh - 1 from their histogram rows in LDS
 // (bins 0 .. k - 1 counted, bin k zero), by a workgroup of NT threads: the
 // closed form (and histograms), several windows, or the learned estimate.
-// Four threads share a host's row; a row's 16-bit halves are summed packed,
-// which cannot carry because all bins of a host add up to at most g < 2^16.
+// Four threads (fewer where there are many hosts) share a host's row; a row's
+// 16-bit halves are summed packed, which cannot carry because all bins of a host
+// add up to at most g < 2^16.
 // act: kFinMulti's window counts.  Starts after a barrier.
 template <int MODE, uint32_t NT>
 __device__ __forceinline__ void finish_hosts(const Geo &G, const DevState *__restrict__ st, uint32_t *hist,
@@ -689,30 +691,35 @@ __device__ __forceinline__ void finish_hosts(const Geo &G, const DevState *__res
                                              const unsigned long long *act, const mlp::Packed *__restrict__ P,
                                              float *__restrict__ cf_out)
 {
-    const uint32_t t = threadIdx.x, hh = t >> 2, qq = t & 3u;
+    const uint32_t t = threadIdx.x;
+    // Threads per host of the closed form: four while the workgroup's hosts
+    // leave it that many, else two or one.  (With four, only 16 lanes of a
+    // wavefront form an estimate: 510 hosts per workgroup, g = 4, 3M hosts on
+    // 2^28 ATs, finalize 129 us with four, 85 with one.)
+    const uint32_t lt = MODE != kFinClosedForm || nh <= NT / 4 ? 2u : nh <= NT / 2 ? 1u : 0u, T = 1u << lt;
+    const uint32_t hh = t >> lt, qq = t & (T - 1u);
     // this thread's share of the bins below d of a row, as packed sums, from
-    // word j on; and all four threads' total
+    // word j on; and the sum over the host's threads
     auto total = [&](uint32_t acc, const uint32_t *row, uint32_t d) -> uint32_t {
         uint32_t live = (acc & 0xFFFFu) + (acc >> 16);
         if ((d & 1u) && qq == 0) live += row[d >> 1] & 0xFFFFu;
-        live += __shfl_xor(live, 1, 64);
-        live += __shfl_xor(live, 2, 64);
+        for (uint32_t off = 1; off < T; off <<= 1) live += __shfl_xor(live, (int)off, 64);
         return live;
     };
     if constexpr (MODE == kFinClosedForm) {
         const uint64_t active_pool = pool_active(st, kprime);
-        for (uint32_t base = 0; base < nh; base += NT / 4) {
+        for (uint32_t base = 0; base < nh; base += NT >> lt) {
             const bool valid = base + hh < nh;
             uint32_t *row = hist + (valid ? base + hh : 0u) * rowp;
             uint32_t acc = 0, j = qq;
-            for (; j < kprime / 2; j += 4) acc += row[j];
+            for (; j < kprime / 2; j += T) acc += row[j];
             const uint32_t live = total(acc, row, kprime);
             if (valid && qq == 0) {
                 est[h0 + base + hh] = estimate_from_counts(G.g - live, G.N - active_pool, G.g, G.c);
                 if (live_out) live_out[h0 + base + hh] = live;
             }
             if (hist_out) {      // bin k = g - (bins 0 .. k - 1), for the histogram output only
-                for (; j < G.k / 2; j += 4) acc += row[j];
+                for (; j < G.k / 2; j += T) acc += row[j];
                 const uint32_t all = total(acc, row, G.k);
                 if (valid && qq == 0) row[G.k >> 1] += (G.g - all) << ((G.k & 1u) << 4);
             }
