@@ -1118,18 +1118,6 @@ static bool allow_lds(const vate_sketch *s)
     return true;
 }
 
-// Whether the lookups of n hosts go through LDS slice by slice (k_sliced).  The
-// closed form takes pools up to 2^23, histograms (which read the live VATs'
-// values as well) up to 2^22: at 64,000 hosts, g = 1024, 2^23 ATs the closed
-// form takes 204 us (gathered 240, partitioned 238), histograms 272 (gathered
-// 248).  Fewer lookups than kSlicedMin do not pay for the copies.
-static bool sliced(const vate_sketch *s, uint32_t n, bool hist)
-{
-    const Geo &G = s->G;
-    if (G.blog > 0 || G.c > kSlicedLog2 - (hist ? 1u : 0u)) return false;
-    return (uint64_t)n * G.g >= (kSlicedMin << (G.c > kSliceLog2 ? G.c - kSliceLog2 - 1u : 0u));
-}
-
 // log2 of the lanes per host.  As many as hold a host's VATs, P each; with one
 // slice, where going round again costs no copy, 16 at most (64 hosts per
 // workgroup) while every CU has a workgroup.
@@ -1142,15 +1130,61 @@ static uint32_t sliced_lanes(const vate_sketch *s, uint32_t n, uint32_t P)
     return lg;
 }
 
+// Whether, and in what shape, the lookups of n hosts go through LDS slice by
+// slice.  A thread tests P VATs whether the host has that many or not, and every
+// CU takes as long as the fullest, so what counts are slots: the threads of all
+// CUs in all rounds, times P.  A gathered lookup costs as much as this many
+// sixteenths of a slot (byte ATs, g = 1 to 4096, 2,000 to 3M hosts; by log2 of
+// the pool): little where the CU's first-level cache holds the bitmap (2^18), most
+// on the largest pool of one slice, and less again the more slices a slot is
+// tested against.  (2280 closed forms timed both ways: 26 take more than 1.1 times
+// the better way's time, none 1.35.)  g = 4, 3M hosts, 2^23 ATs: 59 us gathered, 303 by slices; g = 1024,
+// 130,000 hosts, 2^20 ATs: 387 and 84.  Values that have to be read for every
+// active VAT (k' < k, histograms) narrow the difference, and histogram rows leave
+// fewer hosts to a workgroup.  The network runs on 64 hosts of a workgroup's 1024
+// threads, so it goes through LDS only where lookups outweigh it (500,000 hosts,
+// 2^21 ATs: g = 128 gathered 317 us, through LDS 400 to 640; g = 1024 1862 and
+// 1367).
+enum SlicedUse { SLICED_FORM, SLICED_SHORT, SLICED_HIST, SLICED_WINDOWS, SLICED_LEARNED };
+
+struct SlicedShape {
+    uint32_t P, lg;      // VATs per thread (0: gathered), log2 of the lanes per host
+};
+
+static SlicedShape sliced_shape(const vate_sketch *s, uint32_t n, SlicedUse use, uint32_t row_bytes = 0,
+                                uint32_t room = 0)
+{
+    static const uint8_t gain[][12] = {      // up to 2^12, 2^13, ... 2^23 ATs
+        {0, 17, 22, 22, 28, 28, 33, 37, 54, 44, 23, 14},
+        {0, 0, 0, 0, 17, 21, 23, 37, 40, 37, 23, 14},
+        {0, 0, 0, 0, 0, 0, 0, 29, 29, 29, 17, 0},
+        {0, 0, 0, 0, 16, 17, 18, 35, 42, 42, 22, 0},
+        {36, 36, 36, 36, 36, 36, 36, 36, 36, 36, 18, 0},
+    };
+    const Geo &G = s->G;
+    SlicedShape best{0, 0};
+    if (G.blog > 0 || G.c > kSlicedLog2 || (use == SLICED_LEARNED && G.g < 512)) return best;
+    uint64_t least = 2ull * n * G.g * gain[use][std::max(G.c, 12u) - 12u];       // in 1/32 slots
+    for (uint32_t P = 16; P <= (G.c > kSliceLog2 ? 32u : 16u); P *= 2) {
+        uint32_t lg = sliced_lanes(s, n, P);
+        if (use == SLICED_LEARNED && lg < 4) lg = 4;      // the network takes 64 hosts at a time
+        while (lg < 6 && (row_bytes * kSlicedThreads >> lg) > room) ++lg;
+        if ((row_bytes * kSlicedThreads >> lg) > room) continue;
+        const uint64_t per_round = (uint64_t)s->n_cu * (kSlicedThreads >> lg), again = (G.g + (P << lg) - 1u) / (P << lg);
+        const uint64_t slots = (n + per_round - 1u) / per_round * s->n_cu * kSlicedThreads * P * again;
+        const uint64_t cost = slots * (P == 32 ? 23u : 32u);      // (of 32 VATs a thread each costs 0.72 as much)
+        if (cost <= least) least = cost, best = {P, lg};
+    }
+    return best;
+}
+
 // Calls f with the kernel's VATs per thread and whether there is one slice.
-// Several slices: 32 VATs, or 16 while 32 would leave CUs without hosts.
 template <class F>
-static void by_slices(const vate_sketch *s, uint32_t n, bool small, F &&f)
+static void by_slices(const vate_sketch *s, uint32_t P, F &&f)
 {
     using std::integral_constant;
     if (s->G.c <= kSliceLog2) f(integral_constant<uint32_t, 16>{}, std::true_type{});
-    else if (!small && (uint64_t)n * s->G.g >= 32ull * kSlicedThreads * s->n_cu)
-        f(integral_constant<uint32_t, 32>{}, std::false_type{});
+    else if (P == 32) f(integral_constant<uint32_t, 32>{}, std::false_type{});
     else f(integral_constant<uint32_t, 16>{}, std::false_type{});
 }
 
@@ -1207,14 +1241,14 @@ static void launch_estimate(vate_sketch *s, const uint32_t *hosts, uint32_t n, u
     }
     const uint64_t lanes = (uint64_t)s->n_cu * 2048u / n;       // lanes a host may take (n >= 1)
     using std::integral_constant;
-    if (sliced(s, n, false)) {
-        by_slices(s, n, false, [&](auto Pv, auto One) {
+    if (const SlicedShape sh = sliced_shape(s, n, kprime < s->G.k ? SLICED_SHORT : SLICED_FORM); sh.P) {
+        by_slices(s, sh.P, [&](auto Pv, auto One) {
             constexpr uint32_t P = decltype(Pv)::value;
             constexpr bool one = decltype(One)::value;
             if (!allow_lds<k_sliced<W, P, one>>(s)) return;
-            const uint32_t lg = sliced_lanes(s, n, P), lds = 4u * sliced_words(s->G);
-            k_sliced<W, P, one><<<grid_for(n, kSlicedThreads >> lg, sliced_cap(s, lds)), kSlicedThreads, lds, st>>>(
-                s->G, s->pool, s->st, s->bitmap, hosts, n, lg, kprime, est, live);
+            const uint32_t lds = 4u * sliced_words(s->G);
+            k_sliced<W, P, one><<<grid_for(n, kSlicedThreads >> sh.lg, sliced_cap(s, lds)), kSlicedThreads, lds, st>>>(
+                s->G, s->pool, s->st, s->bitmap, hosts, n, sh.lg, kprime, est, live);
         });
         return;
     }
@@ -1245,36 +1279,21 @@ static void launch_gather(vate_sketch *s, const uint32_t *hosts, uint32_t n, uin
     const uint32_t rowp = hist_row_words(s->G.k), row_bytes = rowp * 4u;
     const auto *net = static_cast<const mlp::Packed *>(weights);
     using std::integral_constant;
-    // The network runs on 64 hosts of a workgroup's 1024 threads, so it goes
-    // through LDS only where lookups outweigh it (500,000 hosts, 2^21 ATs:
-    // g = 128 gathered 317 us, through LDS 400 to 640; g = 1024 1862 and 1367).
-    if (sliced(s, n, true) && (MODE != kFinLearned || s->G.g >= 512)) {
-        constexpr uint32_t fixed = (MODE == kFinLearned ? 10u : 1u) * 1024u;
-        const uint32_t bits = 4u * sliced_words(s->G), room = s->lds_budget - bits - fixed;
-        auto rows = [&](uint32_t P) {
-            uint32_t lg = sliced_lanes(s, n, P);
-            if (MODE == kFinLearned && lg < 4) lg = 4;      // the network takes 64 hosts at a time
-            while (lg < 6 && (row_bytes * kSlicedThreads >> lg) > room) ++lg;
-            return lg;
-        };
-        // rows that fit without leaving half of the threads' VATs empty
-        auto fits = [&](uint32_t P) {
-            const uint32_t lg = rows(P);
-            return (row_bytes * kSlicedThreads >> lg) <= room && (s->G.c <= kSliceLog2 || (P << lg) < 2u * s->G.g);
-        };
-        if (fits(16)) {
-            by_slices(s, n, !fits(32), [&](auto Pv, auto One) {
-                constexpr uint32_t P = decltype(Pv)::value;
-                constexpr bool one = decltype(One)::value;
-                if (!allow_lds<k_sliced_hist<W, MODE, P, one>>(s)) return;
-                const uint32_t lg = rows(P), lds = bits + (row_bytes * kSlicedThreads >> lg);
-                k_sliced_hist<W, MODE, P, one><<<grid_for(n, kSlicedThreads >> lg, sliced_cap(s, lds + fixed)),
-                                                 kSlicedThreads, lds, st>>>(s->G, s->pool, s->st, s->bitmap, hosts, n,
-                                                                            lg, rowp, kprime, est, live, hist, win,
-                                                                            net, cf);
-            });
-            return;
-        }
+    constexpr uint32_t fixed = (MODE == kFinLearned ? 10u : 1u) * 1024u;
+    const uint32_t bits = 4u * sliced_words(s->G);
+    constexpr SlicedUse use = MODE == kFinLearned ? SLICED_LEARNED : MODE == kFinMulti ? SLICED_WINDOWS : SLICED_HIST;
+    if (const SlicedShape sh = sliced_shape(s, n, use, row_bytes, s->lds_budget - bits - fixed); sh.P) {
+        by_slices(s, sh.P, [&](auto Pv, auto One) {
+            constexpr uint32_t P = decltype(Pv)::value;
+            constexpr bool one = decltype(One)::value;
+            if (!allow_lds<k_sliced_hist<W, MODE, P, one>>(s)) return;
+            const uint32_t lds = bits + (row_bytes * kSlicedThreads >> sh.lg);
+            k_sliced_hist<W, MODE, P, one><<<grid_for(n, kSlicedThreads >> sh.lg, sliced_cap(s, lds + fixed)),
+                                             kSlicedThreads, lds, st>>>(s->G, s->pool, s->st, s->bitmap, hosts, n,
+                                                                        sh.lg, rowp, kprime, est, live, hist, win,
+                                                                        net, cf);
+        });
+        return;
     }
     // (the network takes 16 hosts a wavefront: a tile as soon as every CU has one)
     constexpr uint32_t most = MODE == kFinLearned ? 6u : 4u, room = (MODE == kFinLearned ? 2u : 8u);

@@ -63,6 +63,27 @@ static uint32_t batch_lanes(uint32_t g)
     return lg;
 }
 
+// Whether a member's lookups go through LDS: 32 slots a thread against
+// k_batch_estimate's one lane per host, for which a gathered VAT costs `gain`
+// sixteenths of a slot, a host no less than `host` slots, and 2^17 hosts as much
+// as fewer.  From 2M lookups on (4M on 2^22 ATs, 8M on 2^23): fewer don't pay for
+// a launch.  (Four members of 2M hosts, g = 8: 2^23 ATs 479 us gathered, 965
+// through LDS; 2^20 473 and 366.)
+static bool batch_sliced_pays(const vate_sketch *s, uint32_t n, uint32_t kprime)
+{
+    static const uint8_t gain[][12] = {       // up to 2^12, 2^13, ... 2^23 ATs: window k, and below
+        {12, 15, 15, 15, 18, 18, 21, 35, 48, 42, 29, 18},
+        {8, 10, 10, 10, 12, 14, 17, 35, 48, 42, 29, 18},
+    };
+    static const uint8_t host[12] = {51, 51, 51, 51, 51, 51, 51, 51, 51, 36, 23, 14};
+    const Geo &G = s->G;
+    if (G.blog > 0 || G.c > kSlicedLog2) return false;
+    if ((uint64_t)n * G.g < 1ull << (G.c > 21 ? G.c : 21)) return false;
+    const uint32_t at = std::max(G.c, 12u) - 12u, round = kBatchSlicedVats << batch_lanes(G.g);
+    const uint64_t slots = (uint64_t)round * ((G.g + round - 1u) / round);
+    return 16u * slots * n <= (uint64_t)std::max(n, 1u << 17) * std::max(16u * host[at], G.g * gain[kprime < G.k][at]);
+}
+
 // Whether some member's lookups go through LDS (a launch of their own, whose
 // shape is not tuned).
 static bool batch_sliced(const vate_batch *b)
@@ -191,7 +212,7 @@ int vate_batch_set_io(vate_batch *b, uint32_t i, const uint32_t *pairs_dev, uint
     it.est = est_dev;
     it.live = live_dev;
     // (a captured graph without k_batch_sliced keeps gathering)
-    it.sliced = n_hosts > 0 && sliced(b->sk[i], n_hosts, false) && (!b->has_graph || b->graph_sliced)
+    it.sliced = n_hosts > 0 && batch_sliced_pays(b->sk[i], n_hosts, kprime) && (!b->has_graph || b->graph_sliced)
                     ? 1u + batch_lanes(it.G.g)
                     : 0u;
     hipError_t e = hipMemcpy(b->items + i, &it, sizeof(BatchItem), hipMemcpyHostToDevice);

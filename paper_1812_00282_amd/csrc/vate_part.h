@@ -911,10 +911,6 @@ __global__ void __launch_bounds__(256) k_copy_hosts(const uint32_t *__restrict__
 // values: 509 us for 331 hosts on a 2^28 pool).
 // ---------------------------------------------------------------------------
 constexpr uint32_t kGatherU = 8;
-// Lookups from which they go slice by slice (doubling from 2^21 ATs on, with
-// the slices).  8-bit pool of 2^20 ATs, g = 1024: 2M lookups take 12 us either
-// way (launch and latency), 16M 55 us gathered and 20 through LDS.
-constexpr uint64_t kSlicedMin = 1u << 21;
 constexpr uint32_t kPartLog2 = 23;         // smallest pool (log2) whose lookups are partitioned
 constexpr uint64_t kPartMin = 3ull << 47;  // lookups times pool size from which they are
 constexpr uint64_t kPartFormMin = 6u << 20;   // and lookups, for the closed form for window k

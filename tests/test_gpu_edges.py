@@ -148,3 +148,36 @@ def test_census_additions(c, w, k, counter):
     _, r_live, _ = ref.estimate(hosts[:300], kprime=max(1, k // 2))
     live = gpu.estimate(hosts[:300], kprime=max(1, k // 2))[1]
     np.testing.assert_array_equal(live.cpu().numpy().view(np.uint32), r_live)
+
+
+# Lookups that fill their slots and lookups that don't, on pools from those whose
+# bits a cache line holds to the largest that goes through LDS: gathered, or by
+# slices with 16 or 32 VATs a thread, one round of hosts per workgroup or several.
+@pytest.mark.parametrize("c,w,k,g,n_hosts", [
+    (10, 8, 60, 1024, 20_000), (13, 8, 60, 1024, 40_000), (16, 4, 7, 128, 130_000), (16, 8, 60, 100, 130_000),
+    (18, 7, 60, 16, 400_000), (18, 8, 60, 24, 300_000), (20, 8, 60, 5, 500_000), (20, 16, 300, 64, 60_000),
+    (21, 8, 60, 8, 700_000), (21, 8, 60, 17, 500_000), (22, 8, 60, 12, 600_000), (22, 10, 300, 400, 50_000),
+    (23, 8, 60, 16, 900_000), (23, 8, 60, 128, 130_000), (23, 4, 7, 200, 130_000)])
+def test_lookups_by_slots(c, w, k, g, n_hosts):
+    rng = np.random.default_rng(c * 1000 + g)
+    gpu, ref = _pair(Config(c, w, k, g, seed_a=5, seed_b=6))
+    hosts = _hosts(rng, n_hosts)
+    for t in range(3):
+        p = _packets(rng, min(200_000, 2**c // 8), hosts)
+        gpu.ingest(p)
+        ref.ingest(p)
+        gpu.close_slice()
+        ref.close_slice()
+    few = np.r_[hosts[:700], hosts[-700:]]
+    pick = lambda x: torch.cat([x[:700], x[-700:]]).cpu().numpy()
+    kps = sorted({1, 2, k})
+    windows = gpu.estimate_windows(hosts, kps)
+    for j, kp in enumerate(kps):
+        r_est, r_live, r_hist = ref.estimate(few, kprime=kp, want_hist=k <= 256)
+        est, live, hist = gpu.estimate(hosts, kprime=kp, want_hist=k <= 256)
+        np.testing.assert_array_equal(pick(live).view(np.uint32), r_live)
+        assert np.all(np.abs(pick(est).astype(np.float64) - r_est) <= _tol(r_est, g))
+        if k <= 256:
+            np.testing.assert_array_equal(pick(hist).view(np.uint32), r_hist)
+        one, lone, _ = gpu.estimate(hosts, kprime=kp)
+        assert torch.equal(one, est) and torch.equal(lone, live) and torch.equal(windows[:, j], est)
