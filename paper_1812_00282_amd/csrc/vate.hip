@@ -698,8 +698,8 @@ __device__ __forceinline__ uint64_t pool_active(const DevState *__restrict__ st,
 // VATs sub, sub + L, ... of one host that are active for k', by U gathers in
 // flight.  The activity bitmap answers CheckAT(., k) directly; the AT value
 // (for its distance) is only read for VATs that are active at all, and only
-// when a shorter window needs it, again with all of a batch in flight.
-template <int W, int L, int U>
+// when a shorter window needs it, again with V of a batch in flight.
+template <int W, int L, int U, int V = U>
 __device__ __forceinline__ uint32_t lane_live(const Geo &G, const uint8_t *__restrict__ pool,
                                               const uint8_t *__restrict__ bitmap, uint32_t kprime, uint32_t key, bool valid, uint32_t bact0, uint32_t sub)
 {
@@ -718,12 +718,16 @@ __device__ __forceinline__ uint32_t lane_live(const Geo &G, const uint8_t *__res
             for (int u = 0; u < U; ++u) live += bit[u];
             continue;
         }
-        uint32_t val[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) val[u] = bit[u] ? load_at<W>(pool, pid[u], G.wb) : 0u;
+        for (int u0 = 0; u0 < U; u0 += V) {
+            uint32_t val[V];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (bit[u] && value_dist(G, bact0, pid[u], val[u]) < kprime) ++live;
+            for (int u = 0; u < V; ++u) val[u] = bit[u0 + u] ? load_at<W>(pool, pid[u0 + u], G.wb) : 0u;
+#pragma unroll
+            for (int u = 0; u < V; ++u)
+                if (bit[u0 + u] && value_dist(G, bact0, pid[u0 + u], val[u]) < kprime) ++live;
+            if constexpr (V < U) __builtin_amdgcn_sched_barrier(0);
+        }
     }
     return live;
 }
