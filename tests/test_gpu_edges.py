@@ -181,3 +181,25 @@ def test_lookups_by_slots(c, w, k, g, n_hosts):
             np.testing.assert_array_equal(pick(hist).view(np.uint32), r_hist)
         one, lone, _ = gpu.estimate(hosts, kprime=kp)
         assert torch.equal(one, est) and torch.equal(lone, live) and torch.equal(windows[:, j], est)
+
+
+# One lane per host: many hosts with fewer VATs than four lanes hold; both sides
+# of the rule, k and below, every kind of counter.
+@pytest.mark.parametrize("c,w,g,k,n_hosts,b", [
+    (12, 8, 1, 60, 131_073, 0), (24, 8, 63, 60, 140_001, 0), (24, 8, 64, 60, 140_001, 0), (25, 4, 16, 7, 200_003, 0),
+    (24, 7, 17, 60, 131_072, 0), (24, 16, 33, 300, 104_000, 0), (22, 8, 40, 60, 150_001, 3)])
+def test_one_lane_per_host(c, w, g, k, n_hosts, b):
+    rng = np.random.default_rng(c * 1000 + g)
+    gpu, ref = _pair(Config(c, w, k, g, seed_a=7, seed_b=8, block_log2=b))
+    hosts = _hosts(rng, n_hosts)
+    for t in range(3):
+        p = _packets(rng, 100_000, hosts)
+        gpu.ingest(p)
+        ref.ingest(p)
+        gpu.close_slice()
+        ref.close_slice()
+    for kp in sorted({1, 2, k}):
+        r_est, r_live, _ = ref.estimate(hosts, kprime=kp)
+        est, live, _ = gpu.estimate(hosts, kprime=kp)
+        np.testing.assert_array_equal(live.cpu().numpy().view(np.uint32), r_live)
+        assert np.all(np.abs(est.cpu().numpy().astype(np.float64) - r_est) <= _tol(r_est, g))
