@@ -1195,15 +1195,36 @@ static void by_slices(const vate_sketch *s, uint32_t P, F &&f)
 // Workgroups of `lds` bytes that a CU holds.
 static unsigned sliced_cap(const vate_sketch *s, uint32_t lds) { return s->n_cu * (s->G.c <= kSliceLog2 && lds <= s->lds_budget / 2 ? 2u : 1u); }
 
+// Gathers per host of the closed form for window k: its VATs, or its locality
+// blocks where those are whole words of the bitmap.
+static uint32_t parts_gathers(const Geo &G)
+{
+    return blocked_gather_ok(G, G.k) ? (G.g + (1u << G.blog) - 1u) >> G.blog : G.g;
+}
+
 // Whether the closed form goes by parts of the bitmap (k_parts_count): window
-// k, a bitmap larger than an XCD's L2, and enough gathers (a block of 32 VATs or
-// more is one) to pay for three launches and a pass over the bitmap.
+// k, a bitmap larger than an XCD's L2, enough gathers (a block of 32 VATs or
+// more is one) to pay for three launches and a pass over the bitmap, and enough
+// of them per host: every part hashes a host's gathers by the batch whether the
+// host has that many or not.  3M hosts with one gather each: 2^26 ATs 40 us
+// gathered, 72 by parts, 2^28 58 and 216; with three 2^26 at par, 2^28 149 and
+// 214; with five 2^28 at par (blocks with six: 500,000 hosts of five 46 and 50).
+// Blocks of eight words and more, which the other gather reads word by word, pay
+// with half as many (1M hosts, two blocks of 256 VATs, 2^27 ATs: 135 and 101).
+// Smaller blocks share one line among their VATs, so a host takes as many lines
+// as it has blocks, but is hashed VAT by VAT: 4M hosts with one block of eight on
+// 2^26 ATs 87 and 121, and eight parts do not pay at all (150,000 hosts, 128 such
+// blocks, 2^28 ATs: 515 and 666).
 static bool parts_gather(const vate_sketch *s, uint32_t n, uint32_t kprime)
 {
     const Geo &G = s->G;
-    if (parts_log2(G.c) == 0 || kprime != G.k) return false;
-    const uint64_t gathers = blocked_gather_ok(G, kprime) ? (G.g + (1u << G.blog) - 1u) >> G.blog : G.g;
-    return n * gathers >= kPartsMin;
+    const uint32_t pl = parts_log2(G.c);
+    if (pl == 0 || kprime != G.k) return false;
+    const uint64_t gathers = parts_gathers(G);
+    const bool words = blocked_gather_ok(G, kprime), shared = G.blog > 0 && !words;
+    if (shared && pl == 3 && G.blog > 1) return false;
+    const uint64_t lines = shared ? gathers >> G.blog : G.blog >= 8 ? 2u * gathers : gathers;
+    return n * gathers >= kPartsMin && lines > std::max(2u, (1u << pl) / 2u + (words ? 1u : 0u));
 }
 
 static void launch_parts(vate_sketch *s, const uint32_t *hosts, uint32_t n, float *est, uint32_t *live, hipStream_t st)
@@ -1212,11 +1233,12 @@ static void launch_parts(vate_sketch *s, const uint32_t *hosts, uint32_t n, floa
     const uint32_t *bitmap = reinterpret_cast<const uint32_t *>(s->bitmap);
     const Geo &G = s->G;
     const bool blocked = blocked_gather_ok(G, G.k);
-    // lanes per host: one while the hosts alone fill the chip
-    const uint32_t gathers = blocked ? (G.g + (1u << G.blog) - 1u) >> G.blog : G.g;
+    // lanes per host: one while the hosts alone fill the chip, and no more than
+    // a host's gathers fill
+    const uint32_t gathers = parts_gathers(G), batch = blocked ? kPartsBlockU : kPartsU;
     const uint64_t threads = 2048ull * s->n_cu >> (3u - parts_log2(G.c));
     uint32_t lg = 0;
-    while (lg < 6 && ((uint64_t)n << lg) < threads && (8u << lg) < gathers) ++lg;
+    while (lg < 6 && ((uint64_t)n << lg) < threads && (batch << (lg + 1u)) <= gathers) ++lg;
     const unsigned grid = (std::max(1u, grid_for((uint64_t)n << lg, kPartsThreads, s->n_cu)) + 7u) & ~7u;
     k_parts_clear<<<grid_for(n, 256, 4u * s->n_cu), 256, 0, st>>>(n, acc);
     if (blocked) k_parts_count<true><<<grid * 8u, kPartsThreads, 0, st>>>(G, bitmap, hosts, n, lg, acc);

@@ -16,6 +16,7 @@
 
 constexpr uint32_t kPartsThreads = 256;
 constexpr uint32_t kPartsU = 16;           // gathers in flight per lane
+constexpr uint32_t kPartsBlockU = 8;       // and blocks, two words each at a time
 constexpr uint64_t kPartsMin = 3u << 19;   // gathers from which they go by parts (2M on 2^28: 37 us before, 22)
 
 // log2 of the parts: 2^25 ATs (4 MiB) each, eight at most.
@@ -46,7 +47,7 @@ __global__ void __launch_bounds__(kPartsThreads) k_parts_count(Geo G, const uint
         uint32_t live = 0;
         if constexpr (BLOCKED) {
             const uint32_t beta = 1u << G.blog, words = beta >> 5, nb = valid ? (G.g + beta - 1u) >> G.blog : 0u;
-            constexpr uint32_t U = 8;          // blocks in flight, two words each at a time
+            constexpr uint32_t U = kPartsBlockU;
             for (uint32_t q0 = sub; q0 < nb; q0 += U * lanes)
                 for (uint32_t x = 0; x < words; x += 2) {
                     uint32_t a[U], b[U];

@@ -203,3 +203,31 @@ def test_one_lane_per_host(c, w, g, k, n_hosts, b):
         est, live, _ = gpu.estimate(hosts, kprime=kp)
         np.testing.assert_array_equal(live.cpu().numpy().view(np.uint32), r_live)
         assert np.all(np.abs(est.cpu().numpy().astype(np.float64) - r_est) <= _tol(r_est, g))
+
+
+# Gathers per host from which the bitmap is taken by parts, and one fewer: two,
+# four and eight parts, VATs and blocks of one, two and eight words.
+@pytest.mark.parametrize("c,g,n_hosts,b", [
+    (26, 2, 900_000, 0), (26, 3, 600_001, 0), (27, 3, 600_001, 0), (28, 4, 500_003, 0), (28, 5, 400_001, 0),
+    (28, 33, 60_000, 0), (27, 70, 600_001, 5), (27, 100, 500_001, 5), (28, 300, 400_001, 6), (28, 330, 300_000, 6),
+    (27, 300, 800_001, 8), (28, 600, 530_000, 8), (26, 16, 200_001, 3), (26, 24, 200_001, 3), (28, 20, 200_000, 1),
+    (28, 100, 50_000, 3)])
+def test_few_gathers_by_parts(c, g, n_hosts, b):
+    rng = np.random.default_rng(c * 1000 + g)
+    gpu, ref = _pair(Config(c, 4, 7, g, seed_a=9, seed_b=10, block_log2=b))
+    hosts = _hosts(rng, n_hosts)
+    for t in range(3):
+        p = _packets(rng, 300_000, hosts[:4000])
+        gpu.ingest(p)
+        ref.ingest(p)
+        gpu.close_slice()
+        ref.close_slice()
+    est, live, _ = gpu.estimate(hosts)
+    few = np.r_[hosts[:4000], hosts[-300:]]
+    r_est, r_live, _ = ref.estimate(few)
+    pick = lambda x: torch.cat([x[:4000], x[-300:]]).cpu().numpy()
+    np.testing.assert_array_equal(pick(live).view(np.uint32), r_live)
+    assert np.all(np.abs(pick(est).astype(np.float64) - r_est) <= _tol(r_est, g))
+    for i in range(0, n_hosts, 40_000):                    # few hosts: gathered
+        e, lv, _ = gpu.estimate(hosts[i:i + 2000])
+        assert torch.equal(live[i:i + 2000], lv) and torch.equal(est[i:i + 2000], e)
