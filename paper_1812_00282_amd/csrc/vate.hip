@@ -1301,8 +1301,8 @@ static void launch_estimate(vate_sketch *s, const uint32_t *hosts, uint32_t n, u
 
 // The direct gather with per-host distance histograms (MODE as in
 // finish_hosts).  Hosts per workgroup: 1 while the chip has room for a
-// workgroup per host, up to 16, or 64 for the network.  Many lookups on a small
-// pool: k_sliced_hist, where the rows fit beside the bits.
+// workgroup per host, up to 256, or 64 for windows and the network.  Lookups that
+// fill the slots of k_sliced_hist on a small pool go there.
 template <int W, int MODE>
 static void launch_gather(vate_sketch *s, const uint32_t *hosts, uint32_t n, uint32_t kprime, float *est,
                           uint32_t *live, uint32_t *hist, const Windows &win, const void *weights, float *cf,
@@ -1328,9 +1328,29 @@ static void launch_gather(vate_sketch *s, const uint32_t *hosts, uint32_t n, uin
         return;
     }
     // (the network takes 16 hosts a wavefront: a tile as soon as every CU has one)
-    constexpr uint32_t most = MODE == kFinLearned ? 6u : 4u, room = (MODE == kFinLearned ? 2u : 8u);
+    constexpr uint32_t room = MODE == kFinLearned ? 2u : 8u, kept = MODE == kFinLearned ? 6u : 4u;
+    // More hosts per workgroup, while each CU has six, where a thread then takes no
+    // more than two batches of gathers (four where the first-level cache holds the
+    // bitmap), or an eighth fewer slots stay empty; and 32 where there are sixteen
+    // such workgroups.  (300,000 histograms, k = 60, 2^20 ATs, 16 hosts per workgroup
+    // and more: g = 1 65 us and, with 256, 25; g = 64 87 and, with 64, 73; g = 256
+    // 245 and, with 32, 248, on 2^14 ATs 116 and 107.)
+    constexpr uint32_t most = MODE == kFinClosedForm ? 8u : 6u;
+    auto slots = [&](uint32_t lg) {
+        const uint32_t batch = kGatherU * (kFinThreads >> lg);
+        return (s->G.g + batch - 1u) / batch * batch;
+    };
+    auto more = [&](uint32_t lg) {
+        if ((row_bytes << (lg + 1)) > 32u * 1024u) return false;
+        const uint64_t groups = (uint64_t)n >> lg;
+        if (lg < kept) return groups > room * s->n_cu;
+        const uint32_t batches = s->G.c <= 18 ? 4u : 2u;
+        return (lg == 4 && groups > 16u * s->n_cu) ||
+               (groups > 6u * s->n_cu && (batches * kGatherU * (kFinThreads >> (lg + 1)) >= s->G.g ||
+                                          8u * slots(lg + 1) <= 7u * slots(lg)));
+    };
     uint32_t lg = 0;
-    while (lg < most && (row_bytes << (lg + 1)) <= 32u * 1024u && ((uint64_t)n >> lg) > room * s->n_cu) ++lg;
+    while (lg < most && more(lg)) ++lg;
     if (!allow_lds<k_gather<W, MODE>>(s)) return;
     k_gather<W, MODE><<<grid_for(n, 1u << lg, kMaxGrid256), 256, row_bytes << lg, st>>>(
         s->G, s->pool, s->st, s->bitmap, hosts, n, lg, rowp, kprime, est, live, hist, win, net, cf);

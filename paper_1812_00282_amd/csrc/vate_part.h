@@ -900,15 +900,15 @@ __global__ void __launch_bounds__(256) k_copy_hosts(const uint32_t *__restrict__
 }
 
 // ---------------------------------------------------------------------------
-// k_gather: the direct gather with a distance histogram per host: 2^lg hosts
-// per workgroup of kFinThreads threads, whose lanes share a host's VATs
-// (kFinThreads >> lg of them, kGatherU gathers in flight per lane, then the
+// k_gather: the direct gather with a distance histogram per host: 2^lg hosts (up
+// to one per thread) per workgroup of kFinThreads threads, which share a host's
+// VATs (kFinThreads >> lg of them, kGatherU gathers in flight per lane, then the
 // values of a batch's active ATs in flight together).  The histograms are
 // counted in LDS rows and finished as in k_run_finalize.  It is bound by the
 // latency of those two gathers while there are few hosts: one host per
-// workgroup then (a wavefront per 64 hosts and a lane per host, as before,
-// took 64 serial rounds of bitmap gathers at g = 1024 and up to 1024 of
-// values: 509 us for 331 hosts on a 2^28 pool).
+// workgroup then (a wavefront per 64 hosts and a lane per host took 64 serial
+// rounds of bitmap gathers at g = 1024 and up to 1024 of values: 509 us for 331
+// hosts on a 2^28 pool).
 // ---------------------------------------------------------------------------
 constexpr uint32_t kGatherU = 8;
 constexpr uint32_t kPartLog2 = 23;         // smallest pool (log2) whose lookups are partitioned

@@ -231,3 +231,33 @@ def test_few_gathers_by_parts(c, g, n_hosts, b):
     for i in range(0, n_hosts, 40_000):                    # few hosts: gathered
         e, lv, _ = gpu.estimate(hosts[i:i + 2000])
         assert torch.equal(live[i:i + 2000], lv) and torch.equal(est[i:i + 2000], e)
+
+
+# Histograms and windows of many hosts with few VATs: 16 to 256 hosts per
+# workgroup, rows that fit fewer, the remainder of a workgroup's hosts.
+@pytest.mark.parametrize("c,w,k,g,n_hosts,counter", [
+    (18, 8, 60, 1, 400_003, 0), (24, 8, 60, 20, 300_001, 0), (24, 4, 7, 60, 200_001, 0), (25, 8, 61, 128, 120_001, 0),
+    (24, 16, 256, 9, 180_001, 0), (22, 7, 60, 16, 500_000, 0), (24, 8, 59, 300, 70_001, 1), (24, 16, 100, 40, 20_000, 0)])
+def test_many_hosts_per_workgroup(c, w, k, g, n_hosts, counter):
+    rng = np.random.default_rng(c * 1000 + g)
+    gpu, ref = _pair(Config(c, w, k, g, seed_a=7, seed_b=8, counter=counter))
+    hosts = _hosts(rng, n_hosts)
+    for t in range(3):
+        p = _packets(rng, 200_000, hosts)
+        gpu.ingest(p)
+        ref.ingest(p)
+        gpu.close_slice()
+        ref.close_slice()
+    few = np.r_[hosts[:1500], hosts[-1500:]]
+    pick = lambda x: torch.cat([x[:1500], x[-1500:]]).cpu().numpy()
+    kps = sorted({1, 2, 3, k - 1, k})
+    windows = gpu.estimate_windows(hosts, kps)
+    for j, kp in enumerate(kps):
+        r_est, r_live, r_hist = ref.estimate(few, kprime=kp, want_hist=True)
+        est, live, hist = gpu.estimate(hosts, kprime=kp, want_hist=True)
+        np.testing.assert_array_equal(pick(live).view(np.uint32), r_live)
+        np.testing.assert_array_equal(pick(hist).view(np.uint32), r_hist)
+        assert np.all(np.abs(pick(est).astype(np.float64) - r_est) <= _tol(r_est, g))
+        assert torch.equal(hist.sum(1), torch.full((n_hosts,), g, device="cuda"))
+        one, lone, _ = gpu.estimate(hosts, kprime=kp)
+        assert torch.equal(one, est) and torch.equal(lone, live) and torch.equal(windows[:, j], est)
