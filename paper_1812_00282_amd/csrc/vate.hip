@@ -1549,21 +1549,20 @@ static PartGeo part_geo(const vate_sketch *s, uint64_t n, uint32_t hosts)
     p.dr = kRunThreads % G.g;
     p.fast = G.a >= (1ull << kSliceLog2) ? 1u : 0u;
     const uint32_t cus = std::max<uint32_t>(1u, s->n_cu);
-    // Subgroups per finalize workgroup: the network takes hosts in tiles of
-    // 64, so the count whose hosts leave the least of their last tile empty
-    // (the fewest on a tie), as long as every CU gets a workgroup and the
-    // histograms leave a CU room for three (147 hosts per subgroup, k = 60,
-    // 300,000 hosts: three subgroups, 55 KB, take 119 us, two, 36 KB, 95).
+    // Subgroups per finalize workgroup: the network takes hosts in tiles of 64,
+    // so the count that leaves the fullest CU the fewest tiles (the fewest
+    // subgroups on a tie), as long as the histograms leave a CU room for three
+    // workgroups.  (300,000 hosts, k = 60, 147 per subgroup: three, 55 KB, take
+    // 119 us, two, 36 KB, 95.  600,000 hosts, k = 7, 768 subgroups of 782: one each
+    // 201 us for the estimate, two 230.)
     {
-        uint32_t best = 1;
-        double waste = 1e30;
-        for (uint32_t f = 1; f <= 16 && (f == 1 || f * cus <= p.n_sub); ++f) {
+        uint64_t least = ~0ull;
+        for (uint32_t f = 1; f <= 16; ++f) {
             const uint64_t fh = f * hosts;
             if (fh * 4ull * p.rowp > (f == 1 ? kFinHistBytes : kFinGroupBytes)) break;
-            const double w = (double)(((fh + 63) / 64) * 64 - fh) / (double)fh;
-            if (w < waste - 1e-9) waste = w, best = f;
+            const uint64_t tiles = ((p.n_sub + f - 1u) / f + cus - 1u) / cus * ((fh + 63) / 64);
+            if (tiles < least) least = tiles, p.fgroup = f;
         }
-        p.fgroup = best;
     }
     p.lds_scatter = (uint32_t)part_lds(G, hosts);
     {   // lookup LDS: bits, rank tables, run counters, then as many live ATs'

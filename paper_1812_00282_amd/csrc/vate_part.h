@@ -692,11 +692,11 @@ __device__ __forceinline__ void finish_hosts(const Geo &G, const DevState *__res
                                              float *__restrict__ cf_out)
 {
     const uint32_t t = threadIdx.x;
-    // Threads per host of the closed form: four while the workgroup's hosts
+    // Threads per host of closed forms: four while the workgroup's hosts
     // leave it that many, else two or one.  (With four, only 16 lanes of a
     // wavefront form an estimate: 510 hosts per workgroup, g = 4, 3M hosts on
     // 2^28 ATs, finalize 129 us with four, 85 with one.)
-    const uint32_t lt = MODE != kFinClosedForm || nh <= NT / 4 ? 2u : nh <= NT / 2 ? 1u : 0u, T = 1u << lt;
+    const uint32_t lt = MODE == kFinLearned || nh <= NT / 4 ? 2u : nh <= NT / 2 ? 1u : 0u, T = 1u << lt;
     const uint32_t hh = t >> lt, qq = t & (T - 1u);
     // this thread's share of the bins below d of a row, as packed sums, from
     // word j on; and the sum over the host's threads
@@ -734,17 +734,17 @@ __device__ __forceinline__ void finish_hosts(const Geo &G, const DevState *__res
             }
         }
     } else if constexpr (MODE == kFinMulti) {
-        for (uint32_t base = 0; base < nh; base += NT / 4) {
+        for (uint32_t base = 0; base < nh; base += NT >> lt) {
             const bool valid = base + hh < nh;
             const uint32_t *row = hist + (valid ? base + hh : 0u) * rowp;
             float *e = est + (size_t)(h0 + base + hh) * win.m;
             uint32_t acc = 0, j = qq;
-            for (uint32_t w0 = 0; w0 < win.m; w0 += 4) {   // four windows, one estimate per thread
+            for (uint32_t w0 = 0; w0 < win.m; w0 += T) {   // T windows, one estimate per thread
                 uint32_t mine = 0;
-                for (uint32_t w = w0; w < min(w0 + 4u, win.m); ++w) {
-                    for (; j < win.kp[w] / 2; j += 4) acc += row[j];
+                for (uint32_t w = w0; w < min(w0 + T, win.m); ++w) {
+                    for (; j < win.kp[w] / 2; j += T) acc += row[j];
                     const uint32_t live = total(acc, row, win.kp[w]);
-                    if ((w & 3u) == qq) mine = live;
+                    if ((w & (T - 1u)) == qq) mine = live;
                 }
                 if (valid && w0 + qq < win.m)
                     e[w0 + qq] = estimate_from_counts(G.g - mine, G.N - act[w0 + qq], G.g, G.c);
