@@ -1294,7 +1294,7 @@ static void launch_estimate(vate_sketch *s, const uint32_t *hosts, uint32_t n, u
     };
     if (lanes >= 64 && s->G.g <= 256) go(integral_constant<int, 64>{}, integral_constant<int, 4>{});
     else if (lanes >= 64) go(integral_constant<int, 64>{}, integral_constant<int, 16>{});
-    else if (lanes >= 16 || (lanes > 5 && s->G.g >= 256)) go(integral_constant<int, 16>{}, integral_constant<int, 16>{});
+    else if (lanes >= 16 || ((lanes > 5 || s->G.c >= 26) && s->G.g >= 256)) go(integral_constant<int, 16>{}, integral_constant<int, 16>{});
     else if (lanes > 5 || s->G.g >= 64) go(integral_constant<int, 4>{}, integral_constant<int, 16>{});
     else go(integral_constant<int, 1>{}, integral_constant<int, 16>{});
 }
@@ -1327,7 +1327,9 @@ static void launch_gather(vate_sketch *s, const uint32_t *hosts, uint32_t n, uin
         });
         return;
     }
-    // (the network takes 16 hosts a wavefront: a tile as soon as every CU has one)
+    // (the network takes 16 hosts a wavefront: a tile as soon as every CU has one, the
+    // last two wavefronts' where each has four and the network outweighs the gathers:
+    // 100,000 hosts, 2^28 ATs, k = 7, g = 1000 1731 us with 64 hosts, 1641 with 32)
     constexpr uint32_t room = MODE == kFinLearned ? 2u : 8u, kept = MODE == kFinLearned ? 6u : 4u;
     // More hosts per workgroup, while each CU has six, where a thread then takes no
     // more than two batches of gathers (four where the first-level cache holds the
@@ -1343,7 +1345,7 @@ static void launch_gather(vate_sketch *s, const uint32_t *hosts, uint32_t n, uin
     auto more = [&](uint32_t lg) {
         if ((row_bytes << (lg + 1)) > 32u * 1024u) return false;
         const uint64_t groups = (uint64_t)n >> lg;
-        if (lg < kept) return groups > room * s->n_cu;
+        if (lg < kept) return groups > (lg == 5 ? 4u : room) * s->n_cu && (lg < 5 || s->G.g < (s->G.c <= 18 ? 512u : 256u));
         const uint32_t batches = s->G.c <= 18 ? 4u : 2u;
         return (lg == 4 && groups > 16u * s->n_cu) ||
                (groups > 6u * s->n_cu && (batches * kGatherU * (kFinThreads >> (lg + 1)) >= s->G.g ||
@@ -1553,8 +1555,8 @@ static PartGeo part_geo(const vate_sketch *s, uint64_t n, uint32_t hosts)
     // so the count that leaves the fullest CU the fewest tiles (the fewest
     // subgroups on a tie), as long as the histograms leave a CU room for three
     // workgroups.  (300,000 hosts, k = 60, 147 per subgroup: three, 55 KB, take
-    // 119 us, two, 36 KB, 95.  600,000 hosts, k = 7, 768 subgroups of 782: one each
-    // 201 us for the estimate, two 230.)
+    // 119 us, two, 36 KB, 95.  600,000 hosts, k = 7, 768 subgroups of 782: two each
+    // 230 us for the estimate, one 177.)
     {
         uint64_t least = ~0ull;
         for (uint32_t f = 1; f <= 16; ++f) {
