@@ -172,14 +172,14 @@ __device__ __forceinline__ bool last_workgroup(uint32_t *ticket)
     return last != 0;
 }
 
-// Whether the workgroups of a census add into the census itself: few of them,
-// or few counters, so that the atomics (one per workgroup and counter) cost less
-// than the launch that folds the partial censuses.  (A slide of a 2^20 pool of
-// 7-bit ATs, k = 60: 19 us straight, 24 by copies; 2^28 nibbles, k = 7: 36 and
-// 57; but 2^24 7-bit ATs 45 and 27.)  Folding in the workgroup that ends last
-// takes as long as its k counters times kCensusCopies: 100 us at k = 4000, 17
-// straight.
-static bool census_direct(unsigned blocks, uint32_t k) { return blocks <= 256u || (uint64_t)blocks * k <= 16384u; }
+// Whether the workgroups of a census add into the census itself: so few that the
+// atomics, one per workgroup and counter and one after the other on a counter,
+// cost less than the launch that folds the partial censuses (steady traffic, a
+// slice of 2^20 7-bit ATs, k = 60: 27 us straight, 29 by copies; 2^22 32 and 32;
+// 2^24 55 and 39; 2^24 2-bit ATs, k = 1: 68 and 58).  Folding in the workgroup
+// that ends last takes as long as its k counters times kCensusCopies: 100 us at
+// k = 4000, 18 straight.
+static bool census_direct(unsigned blocks) { return blocks <= 256u; }
 
 // Adds a census workgroup's LDS histogram to the census (`direct`) or to copy
 // blockIdx mod kCensusCopies, from where k_census_fold adds it.
@@ -1024,9 +1024,9 @@ static void launch_census(vate_sketch *s, hipStream_t st)
 {
     const bool lds = s->G.k <= kCensusLdsBins;      // longer windows are counted straight into the census
     const uint64_t units = W == 0 ? s->G.N / 32 : s->pool_bytes / 16;
-    const unsigned blocks = W == 0 ? grid_for(units, 256, 16u * s->n_cu)
+    const unsigned blocks = W == 0 ? grid_for(units, 256, (s->G.c >= 27 ? 16u : 8u) * s->n_cu)
                           : W == 8 ? grid_for(units, 256 * kCensus8U, 4096) : grid_for(units, 256 * 4, 2048);
-    const bool direct = census_direct(blocks, s->G.k);
+    const bool direct = census_direct(blocks);
     if constexpr (W == 0) {
         by_exact_width(s->p.width, [&](auto WB) {
             k_census_x<decltype(WB)::value><<<blocks, 256, 0, st>>>(s->G, reinterpret_cast<const uint32_t *>(s->pool),
