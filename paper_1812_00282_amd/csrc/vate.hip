@@ -286,7 +286,7 @@ __global__ void __launch_bounds__(256) k_init(Geo G, uint4 *__restrict__ pool4, 
 // set like exact-width counters (set_bits).
 // ---------------------------------------------------------------------------
 template <int W>
-__device__ __forceinline__ void set_at(uint8_t *__restrict__ pool, uint32_t pid, uint32_t act)
+__device__ __forceinline__ void set_at(uint8_t *__restrict__ pool, uint32_t pid, uint32_t act, bool crowded)
 {
     if constexpr (W == 8) {
         pool[pid] = (uint8_t)act;
@@ -294,7 +294,9 @@ __device__ __forceinline__ void set_at(uint8_t *__restrict__ pool, uint32_t pid,
         reinterpret_cast<uint16_t *>(pool)[pid] = (uint16_t)act;
     } else {
         const uint32_t s = (pid & 7u) << 2;
-        set_bits(reinterpret_cast<uint32_t *>(pool) + (pid >> 3), 0xFu << s, act << s);
+        uint32_t *word = reinterpret_cast<uint32_t *>(pool) + (pid >> 3);
+        if (crowded) put_bits(word, 0xFu << s, act << s);
+        else set_bits(word, 0xFu << s, act << s);
     }
 }
 
@@ -315,9 +317,20 @@ __device__ __forceinline__ void seen_clear(uint32_t *seen)
 template <int W>
 constexpr bool kUsesSeen = W == 0 || W == 4;
 
+// Whether n packets crowd a small pool's words: several for each word (of up to
+// 2^15), so that most swaps would fail, but not so many for each counter that
+// most find it set.  Then counters are put without a look at them (2^16 nibbles,
+// k = 2, a slice of 260,000 packets 87 us by swaps and 61 so, 1M 147 and 113, 4M
+// 150 and 327; 2^16 3-bit ATs 260,000 78 and 47).
+__host__ __device__ __forceinline__ bool crowded_words(const Geo &G, uint64_t n)
+{
+    const uint64_t words = G.N * G.wb / 32u;
+    return words <= 32768u && n >= words && n < (G.wb <= 4 ? 32u : 4u) * G.N;
+}
+
 template <int W>
 __device__ __forceinline__ void ingest_one(const Geo &G, uint8_t *__restrict__ pool, uint32_t bact0,
-                                           uint32_t aip, uint32_t bip, uint32_t *seen)
+                                           uint32_t aip, uint32_t bip, uint32_t *seen, bool crowded)
 {
     uint32_t vid = bh(G, bip);
     uint32_t pid = vat_pid(G, host_key(G, aip), vid);
@@ -327,14 +340,15 @@ __device__ __forceinline__ void ingest_one(const Geo &G, uint8_t *__restrict__ p
     // SetAT stores the block's ACT; a DR is reset to 0
     uint32_t val = G.dr ? 0u : block_act(G, bact0, block_of(G, pid));
     if constexpr (W == 0)
-        set_x(reinterpret_cast<uint32_t *>(pool), pid, G.wb, val);
+        set_x(reinterpret_cast<uint32_t *>(pool), pid, G.wb, val, crowded);
     else
-        set_at<W>(pool, pid, val);
+        set_at<W>(pool, pid, val, crowded);
 }
 
 template <int W, bool ALIGNED16>
 __global__ void __launch_bounds__(256) k_ingest(Geo G, const uint32_t *__restrict__ pairs, uint64_t n,
-                                                uint8_t *__restrict__ pool, const DevState *__restrict__ st)
+                                                uint8_t *__restrict__ pool, const DevState *__restrict__ st,
+                                                bool crowded)
 {
     __shared__ uint32_t seen[kUsesSeen<W> ? kSeen : 1];
     if constexpr (kUsesSeen<W>) {
@@ -348,15 +362,36 @@ __global__ void __launch_bounds__(256) k_ingest(Geo G, const uint32_t *__restric
             const uint64_t j = base + (uint64_t)half * 512 + 2ull * threadIdx.x;   // first of 2 packets
             if (ALIGNED16 && j + 2 <= n) {
                 uint4 v = reinterpret_cast<const uint4 *>(pairs)[j >> 1];
-                ingest_one<W>(G, pool, bact0, v.x, v.y, seen);
-                ingest_one<W>(G, pool, bact0, v.z, v.w, seen);
+                ingest_one<W>(G, pool, bact0, v.x, v.y, seen, crowded);
+                ingest_one<W>(G, pool, bact0, v.z, v.w, seen, crowded);
             } else {
                 for (uint64_t q = j; q < j + 2 && q < n; ++q) {
                     uint2 v = reinterpret_cast<const uint2 *>(pairs)[q];
-                    ingest_one<W>(G, pool, bact0, v.x, v.y, seen);
+                    ingest_one<W>(G, pool, bact0, v.x, v.y, seen, crowded);
                 }
             }
         }
+    }
+}
+
+// Few packets of widths with a filter: a packet per thread at a time, whose two
+// round trips (the word's read, the swap) are all there is to wait for, by one
+// workgroup per CU (more of them swap slower: 130,000 packets on 2^24 nibbles 48
+// us by 256 workgroups, 58 by 512).  4,000 packets of 10-bit ATs on 2^16, a
+// slice: four per thread 37.6 us, 23.5 so.
+constexpr uint64_t kFewPackets = 1u << 18;
+
+template <int W>
+__global__ void __launch_bounds__(256) k_ingest_few(Geo G, const uint32_t *__restrict__ pairs, uint64_t n,
+                                                    uint8_t *__restrict__ pool, const DevState *__restrict__ st)
+{
+    __shared__ uint32_t seen[kSeen];
+    seen_clear(seen);
+    __syncthreads();
+    const uint32_t bact0 = st->bact0;
+    for (uint64_t j = (uint64_t)blockIdx.x * 256 + threadIdx.x; j < n; j += (uint64_t)gridDim.x * 256) {
+        const uint2 v = reinterpret_cast<const uint2 *>(pairs)[j];
+        ingest_one<W>(G, pool, bact0, v.x, v.y, seen, false);
     }
 }
 
@@ -1076,13 +1111,19 @@ static void launch_dr_maintain(vate_sketch *s, hipStream_t st)
 template <int W>
 static void launch_ingest(vate_sketch *s, const uint32_t *pairs, uint64_t n, hipStream_t st)
 {
+    const bool crowded = kUsesSeen<W> && crowded_words(s->G, n);
+    if constexpr (kUsesSeen<W>)
+        if (n <= kFewPackets && !crowded) {
+            k_ingest_few<W><<<grid_for(n, 256, s->n_cu), 256, 0, st>>>(s->G, pairs, n, s->pool, s->st);
+            return;
+        }
     // Widths with a filter: few enough workgroups that each sees several
     // thousand packets.  Others: one workgroup per 1024 packets.
     unsigned blocks = grid_for(n, 1024, kUsesSeen<W> ? 4u * s->n_cu : 1u << 30);
     if ((reinterpret_cast<uintptr_t>(pairs) & 15u) == 0)
-        k_ingest<W, true><<<blocks, 256, 0, st>>>(s->G, pairs, n, s->pool, s->st);
+        k_ingest<W, true><<<blocks, 256, 0, st>>>(s->G, pairs, n, s->pool, s->st, crowded);
     else
-        k_ingest<W, false><<<blocks, 256, 0, st>>>(s->G, pairs, n, s->pool, s->st);
+        k_ingest<W, false><<<blocks, 256, 0, st>>>(s->G, pairs, n, s->pool, s->st, crowded);
 }
 
 static void dispatch_init(vate_sketch *s, hipStream_t st)

@@ -149,9 +149,13 @@ __global__ void __launch_bounds__(256) k_batch_preserve(const BatchItem *__restr
 }
 
 template <int W>
-__device__ __forceinline__ void batch_ingest_tile(const BatchItem &it, uint64_t p0, uint64_t p1, uint32_t *seen)
+__device__ __forceinline__ void batch_ingest_tile(const BatchItem &it, uint64_t p0, uint64_t p1, uint64_t n,
+                                                  uint32_t *seen)
 {
     const uint32_t bact0 = it.st->bact0;
+    // (few packets: a tile's are one chain per thread, which need not wait for swaps;
+    // four members with 10,000 each, 2^18 3-bit ATs, a slice 310 us by swaps, 281 so)
+    const bool crowded = kUsesSeen<W> && (n <= 1u << 17 || crowded_words(it.G, n));
     if constexpr (kUsesSeen<W>) {      // the filter belongs to one sketch (the tile's)
         seen_clear(seen);
         __syncthreads();
@@ -159,11 +163,11 @@ __device__ __forceinline__ void batch_ingest_tile(const BatchItem &it, uint64_t 
     for (uint64_t j = p0 + 2ull * threadIdx.x; j < p1; j += 2ull * blockDim.x) {
         if (j + 2 <= p1) {
             const uint4 v = *reinterpret_cast<const uint4 *>(it.pairs + 2 * j);
-            ingest_one<W>(it.G, it.pool, bact0, v.x, v.y, seen);
-            ingest_one<W>(it.G, it.pool, bact0, v.z, v.w, seen);
+            ingest_one<W>(it.G, it.pool, bact0, v.x, v.y, seen, crowded);
+            ingest_one<W>(it.G, it.pool, bact0, v.z, v.w, seen, crowded);
         } else {
             const uint2 v = *reinterpret_cast<const uint2 *>(it.pairs + 2 * j);
-            ingest_one<W>(it.G, it.pool, bact0, v.x, v.y, seen);
+            ingest_one<W>(it.G, it.pool, bact0, v.x, v.y, seen, crowded);
         }
     }
 }
@@ -182,11 +186,11 @@ __global__ void __launch_bounds__(256) k_batch_ingest(const BatchItem *__restric
         const uint32_t s = find_item(tab->prefix[PH_INGEST], S, tile);
         const BatchItem &it = items[s];
         const uint64_t p0 = (tile - tab->prefix[PH_INGEST][s]) * tune.ingest_tile;
-        const uint64_t p1 = min(p0 + tune.ingest_tile, min((uint64_t)n_pairs[s], it.pairs_cap));
-        if (it.width == 0) batch_ingest_tile<0>(it, p0, p1, seen);
-        else if (it.width == 4) batch_ingest_tile<4>(it, p0, p1, seen);
-        else if (it.width == 8) batch_ingest_tile<8>(it, p0, p1, seen);
-        else batch_ingest_tile<16>(it, p0, p1, seen);
+        const uint64_t n = min((uint64_t)n_pairs[s], it.pairs_cap), p1 = min(p0 + tune.ingest_tile, n);
+        if (it.width == 0) batch_ingest_tile<0>(it, p0, p1, n, seen);
+        else if (it.width == 4) batch_ingest_tile<4>(it, p0, p1, n, seen);
+        else if (it.width == 8) batch_ingest_tile<8>(it, p0, p1, n, seen);
+        else batch_ingest_tile<16>(it, p0, p1, n, seen);
     }
 }
 

@@ -47,15 +47,28 @@ __device__ __forceinline__ void set_bits(uint32_t *__restrict__ p, uint32_t m, u
     }
 }
 
-__device__ __forceinline__ void set_x(uint32_t *__restrict__ words, uint64_t pid, uint32_t wb, uint32_t val)
+// The same without a look at the word, by two atomics that nothing waits for:
+// every interleaving of a slice's writers, who all bring v, ends at v.
+__device__ __forceinline__ void put_bits(uint32_t *__restrict__ p, uint32_t m, uint32_t v)
+{
+    atomicOr(p, v);
+    atomicAnd(p, ~m | v);
+}
+
+__device__ __forceinline__ void set_x(uint32_t *__restrict__ words, uint64_t pid, uint32_t wb, uint32_t val, bool crowded)
 {
     const uint64_t o = pid * wb;
     uint32_t *p = words + (o >> 5);
     const uint32_t sh = (uint32_t)o & 31u;
     const uint32_t n0 = min(wb, 32u - sh);             // bits in the first word
     const uint32_t m0 = low_mask(n0);
-    set_bits(p, m0 << sh, (val & m0) << sh);
-    if (n0 < wb) set_bits(p + 1, low_mask(wb - n0), val >> n0);
+    if (crowded) {
+        put_bits(p, m0 << sh, (val & m0) << sh);
+        if (n0 < wb) put_bits(p + 1, low_mask(wb - n0), val >> n0);
+    } else {
+        set_bits(p, m0 << sh, (val & m0) << sh);
+        if (n0 < wb) set_bits(p + 1, low_mask(wb - n0), val >> n0);
+    }
 }
 
 // The 32 counters of a group (its wb words in order).  WB: the width at

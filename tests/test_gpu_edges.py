@@ -261,3 +261,44 @@ def test_many_hosts_per_workgroup(c, w, k, g, n_hosts, counter):
         assert torch.equal(hist.sum(1), torch.full((n_hosts,), g, device="cuda"))
         one, lone, _ = gpu.estimate(hosts, kprime=kp)
         assert torch.equal(one, est) and torch.equal(lone, live) and torch.equal(windows[:, j], est)
+
+
+# Counters set by swaps or put without a look, by how many packets meet on a word:
+# both sides of the words' and the packets' limits, one packet a thread and four,
+# hot counters, widths whose counters straddle words, both kinds of counter.
+@pytest.mark.parametrize("c,w,k,counter,n", [
+    (16, 4, 2, 0, 8191), (16, 4, 2, 0, 8192), (16, 4, 7, 0, 2_097_152), (18, 4, 7, 0, 40_000), (19, 4, 7, 1, 300_001),
+    (14, 3, 3, 0, 1536), (18, 3, 3, 0, 262_145), (16, 7, 60, 0, 262_143), (16, 7, 60, 0, 262_144), (15, 10, 300, 1, 30_001),
+    (17, 15, 300, 0, 262_144), (22, 10, 300, 0, 262_145), (10, 4, 7, 0, 5)])
+def test_ingest_words(c, w, k, counter, n):
+    rng = np.random.default_rng(c * 1000 + w)
+    gpu, ref = _pair(Config(c, w, k, 64, seed_a=3, seed_b=4, counter=counter))
+    hosts = _hosts(rng, 20_000)
+    for t in range(3):
+        p = _packets(rng, n, hosts)
+        p[rng.random(n) < 0.2] = (hosts[0], 7)
+        gpu.ingest(p)
+        ref.ingest(p)
+        gpu.close_slice()
+        ref.close_slice()
+        pool = gpu.read_state()[0]
+        assert np.array_equal(pool, ref.packed_pool()), t
+
+
+def test_batch_ingest_words():
+    from paper_1812_00282_amd.batch import Batch
+
+    geo = [(16, 4, 7, 200_000), (18, 3, 3, 131_072), (18, 10, 300, 131_073), (14, 7, 60, 20_000), (20, 4, 7, 150_000)]
+    rng = np.random.default_rng(4)
+    pairs = [_pair(Config(c, w, k, 64, seed_a=c, seed_b=w)) for c, w, k, _ in geo]
+    hosts = [_hosts(rng, 5000) for _ in geo]
+    b = Batch([g for g, _ in pairs], [n for *_, n in geo], hosts)
+    for t in range(3):
+        sl = [_packets(rng, n, h) for (*_, n), h in zip(geo, hosts)]
+        b.load(sl)
+        b.slice()
+        b.synchronize()
+        for (gpu, ref), p in zip(pairs, sl):
+            ref.ingest(p)
+            ref.close_slice()
+            assert np.array_equal(gpu.read_state()[0], ref.packed_pool()), t
