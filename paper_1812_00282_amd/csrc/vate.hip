@@ -1574,8 +1574,9 @@ static const uint32_t *hosts_to_gather(const vate_sketch *s, const uint32_t *hos
     return static_cast<const uint32_t *>(workspace);
 }
 
-// The geometry for n hosts, `hosts` per subgroup (from part_hosts).
-static PartGeo part_geo(const vate_sketch *s, uint64_t n, uint32_t hosts)
+// The geometry for n hosts, `hosts` per subgroup (from part_hosts); `network`: for
+// the learned estimate.
+static PartGeo part_geo(const vate_sketch *s, uint64_t n, uint32_t hosts, bool network)
 {
     const Geo &G = s->G;
     const uint64_t ns = part_slices(G);
@@ -1592,19 +1593,22 @@ static PartGeo part_geo(const vate_sketch *s, uint64_t n, uint32_t hosts)
     p.dr = kRunThreads % G.g;
     p.fast = G.a >= (1ull << kSliceLog2) ? 1u : 0u;
     const uint32_t cus = std::max<uint32_t>(1u, s->n_cu);
-    // Subgroups per finalize workgroup: the network takes hosts in tiles of 64,
-    // so the count that leaves the fullest CU the fewest tiles (the fewest
-    // subgroups on a tie), as long as the histograms leave a CU room for three
-    // workgroups.  (300,000 hosts, k = 60, 147 per subgroup: three, 55 KB, take
-    // 119 us, two, 36 KB, 95.  600,000 hosts, k = 7, 768 subgroups of 782: two each
-    // 230 us for the estimate, one 177.)
+    // Subgroups per finalize workgroup, as long as the histograms leave a CU room
+    // for three workgroups.  The network takes hosts in tiles of 64, so the count
+    // that leaves the fullest CU the fewest tiles (the fewest subgroups on a tie):
+    // 300,000 hosts, k = 60, 147 per subgroup: three, 55 KB, take 119 us, two, 36
+    // KB, 95; 600,000 hosts, k = 7, 768 subgroups of 782: two each 230 us for the
+    // estimate, one 177.  Without it as many as have a thread per host, while
+    // each CU has four workgroups (250,000 hosts, k = 16, 38 per subgroup, a slice:
+    // 318 us with three, 310 with six).
     {
         uint64_t least = ~0ull;
         for (uint32_t f = 1; f <= 16; ++f) {
-            const uint64_t fh = f * hosts;
+            const uint64_t fh = f * hosts, groups = (p.n_sub + f - 1u) / f;
             if (fh * 4ull * p.rowp > (f == 1 ? kFinHistBytes : kFinGroupBytes)) break;
-            const uint64_t tiles = ((p.n_sub + f - 1u) / f + cus - 1u) / cus * ((fh + 63) / 64);
-            if (tiles < least) least = tiles, p.fgroup = f;
+            if (!network && f > 1 && (fh > kFinThreads || groups < 4u * cus)) break;
+            const uint64_t tiles = (groups + cus - 1u) / cus * ((fh + 63) / 64);
+            if (!network || tiles < least) least = tiles, p.fgroup = f;
         }
     }
     p.lds_scatter = (uint32_t)part_lds(G, hosts);
@@ -1836,7 +1840,7 @@ static int estimate_ws_impl(vate_sketch *s, const uint32_t *hosts_dev, size_t n_
         direct_estimate(s, hosts, n, kprime, est_dev, live_dev, hist_dev, st);
         return check_launch(s, what);
     }
-    const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes));
+    const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes), false);
     const int rc = launch_part_w<kFinClosedForm>(s, pg, workspace_dev, hosts_dev, n, kprime, est_dev, live_dev,
                                                  hist_dev, Windows{}, nullptr, nullptr, st);
     if (rc != VATE_OK) return rc;
@@ -1918,7 +1922,7 @@ int vate_estimate_plan(vate_sketch *s, const uint32_t *hosts_dev, size_t n_hosts
     hipStream_t st = static_cast<hipStream_t>(stream);
     const uint32_t n = (uint32_t)n_hosts;
     if (partitioned(s, n, PART_PLANNED)) {
-        const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes));
+        const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes), false);
         const int rc = launch_part_w<kFinClosedForm>(s, pg, workspace_dev, hosts_dev, n, s->p.k, nullptr, nullptr,
                                                      nullptr, Windows{}, nullptr, nullptr, st, PART_PLAN);
         if (rc != VATE_OK) return rc;
@@ -1963,7 +1967,7 @@ int vate_estimate_run(vate_sketch *s, size_t n_hosts, uint32_t kprime, float *es
         direct_estimate(s, static_cast<const uint32_t *>(workspace_dev), n, kprime, est_dev, live_dev, hist_dev, st);
         return check_launch(s, "estimate_run");
     }
-    rc = launch_part_w<kFinClosedForm>(s, part_geo(s, n, s->plan_hosts), workspace_dev, nullptr, n, kprime, est_dev,
+    rc = launch_part_w<kFinClosedForm>(s, part_geo(s, n, s->plan_hosts, false), workspace_dev, nullptr, n, kprime, est_dev,
                                        live_dev, hist_dev, Windows{}, nullptr, nullptr, st, PART_RUN);
     if (rc != VATE_OK) return rc;
     return check_launch(s, "estimate_run");
@@ -1985,7 +1989,7 @@ int vate_estimate_learned_run(vate_sketch *s, size_t n_hosts, const void *weight
         direct_learned(s, static_cast<const uint32_t *>(workspace_dev), n, weights_dev, est_dev, est_cf_dev, st);
         return check_launch(s, "estimate_learned_run");
     }
-    rc = launch_part_w<kFinLearned>(s, part_geo(s, n, s->plan_hosts), workspace_dev, nullptr, n, s->p.k, est_dev,
+    rc = launch_part_w<kFinLearned>(s, part_geo(s, n, s->plan_hosts, true), workspace_dev, nullptr, n, s->p.k, est_dev,
                                     nullptr, nullptr, Windows{}, weights_dev, est_cf_dev, st, PART_RUN);
     if (rc != VATE_OK) return rc;
     return check_launch(s, "estimate_learned_run");
@@ -2016,7 +2020,7 @@ int vate_estimate_learned_ws(vate_sketch *s, const uint32_t *hosts_dev, size_t n
         direct_learned(s, hosts, n, weights_dev, est_dev, est_cf_dev, st);
         return check_launch(s, "estimate_learned_ws");
     }
-    const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes));
+    const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes), true);
     const int rc = launch_part_w<kFinLearned>(s, pg, workspace_dev, hosts_dev, n, s->p.k, est_dev, nullptr, nullptr,
                                               Windows{}, weights_dev, est_cf_dev, st);
     if (rc != VATE_OK) return rc;
@@ -2059,7 +2063,7 @@ int vate_estimate_multi_ws(vate_sketch *s, const uint32_t *hosts_dev, size_t n_h
     if (s->p.k > (uint32_t)kMaxHistK && part_max_hosts(s, n) == 0)
         return fail(s, VATE_E_UNSUPPORTED, "several windows for this geometry need k <= 256");
     if (partitioned(s, n, PART_HIST)) {
-        const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes));
+        const PartGeo pg = part_geo(s, n, part_hosts(s, n, workspace_bytes), false);
         const int rc = launch_part_w<kFinMulti>(s, pg, workspace_dev, hosts_dev, n, s->p.k, est_dev, nullptr,
                                                 nullptr, win, nullptr, nullptr, st);
         if (rc != VATE_OK) return rc;
