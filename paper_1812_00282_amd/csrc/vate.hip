@@ -964,7 +964,7 @@ struct vate_sketch {
     uint8_t *pool;
     DevState *st;
     uint8_t *bitmap;             // activity bitmap inside the state block
-    unsigned long long *copies;  // k_census8's partial censuses inside the state block
+    unsigned long long *copies;  // partial censuses inside the state block
     size_t pool_bytes, state_bytes;
     uint64_t max_block_chunks;   // chunks a due block can overlap
     int closed;                  // 1: slice ended, estimates allowed
@@ -1527,6 +1527,7 @@ static uint32_t part_hosts(const vate_sketch *s, uint64_t n, size_t have)
 enum PartUse { PART_FORM, PART_HIST, PART_PLANNED };   // the closed form for k; what needs distances; a plan
 static bool partitioned(const vate_sketch *s, uint64_t n, PartUse use)
 {
+    static_assert(kPartLog2 >= kSliceLog2 + 3u, "the lookup gives each of 8 XCDs whole slices");
     if (s->G.c < (use == PART_FORM ? kPartLog2 + 1u : kPartLog2)) return false;
     uint64_t least = s->G.c <= 28 ? kPartMin >> s->G.c : (kPartMin >> 28) << (s->G.c - 28u);
     if (use == PART_FORM) least = std::max(least, kPartFormMin);
@@ -1582,7 +1583,6 @@ static PartGeo part_geo(const vate_sketch *s, uint64_t n, uint32_t hosts, bool n
     const uint64_t ns = part_slices(G);
     PartGeo p{};
     p.n_slices = (uint32_t)ns;
-    p.xcd = ns >= 8 ? 1u : 0u;
     p.rowp = hist_row_words(G.k);
     p.hosts = hosts;
     p.n_sub = (uint32_t)((n + hosts - 1) / hosts);

@@ -69,7 +69,6 @@ struct PartGeo {
     uint32_t dq, dr;      // kRunThreads = dq * g + dr
     uint32_t fast;        // every block holds a whole slice's ATs: a slice meets at most two blocks
     uint32_t rowp;        // u32 words per packed 16-bit histogram row: ceil((k + 1) / 2), made odd
-    uint32_t xcd;         // give the workgroups of one slice to one XCD
     uint32_t split;       // lookup workgroups per slice, each over a range of subgroups
     uint32_t span;        // subgroups per range (a multiple of win)
     uint32_t win;         // subgroups per wavefront and window of the lookup (a power of two, at most 64)
@@ -319,16 +318,10 @@ __global__ void __launch_bounds__(kRunThreads) k_run_lookup(Geo G, PartGeo PG, c
     uint8_t *dist8 = reinterpret_cast<uint8_t *>(rcnt + kRunThreads);
     uint16_t *dist16 = reinterpret_cast<uint16_t *>(dist8);
 
-    uint32_t b, part;
-    if (PG.xcd) {              // XCD x mod 8 takes a contiguous range of slices
-        const uint32_t r = blockIdx.x & 7u, u = blockIdx.x >> 3;
-        const uint32_t per = PG.n_slices / 8u;
-        part = u % PG.split;
-        b = r * per + u / PG.split;
-    } else {
-        part = blockIdx.x % PG.split;
-        b = blockIdx.x / PG.split;
-    }
+    // XCD x mod 8 takes a contiguous range of slices (pools of 2^23 ATs and more:
+    // eight slices at least, a power of two)
+    const uint32_t u = blockIdx.x >> 3, part = u % PG.split;
+    const uint32_t b = (blockIdx.x & 7u) * (PG.n_slices / 8u) + u / PG.split;
     const uint32_t s_lo = part * PG.span, s_hi = min(PG.n_sub, s_lo + PG.span);
     const uint32_t t = threadIdx.x, lane = t & 63u, wv = t >> 6;
     {

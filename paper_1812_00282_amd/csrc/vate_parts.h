@@ -1,6 +1,7 @@
 // The closed form for window k by gathers of one part of the bitmap per XCD:
-// many hosts on pools of 2^26 ATs and more, for callers without a workspace.
-// Included into vate.hip inside namespace vate.
+// hosts with several gathers each on pools of 2^26 ATs and more, where the lookups
+// are not partitioned (no workspace, or too few hosts).  Included into vate.hip
+// inside namespace vate.
 //
 // Each XCD has an L2 of 4 MiB.  The bitmap of 2^28 ATs is 32 MiB, and gathers
 // from anywhere in it fill lines from beyond L2, 6.5e10 a second on the chip; a
