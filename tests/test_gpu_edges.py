@@ -302,3 +302,40 @@ def test_batch_ingest_words():
             ref.ingest(p)
             ref.close_slice()
             assert np.array_equal(gpu.read_state()[0], ref.packed_pool()), t
+
+
+# Hosts set again after the capture: a list that would go through LDS in a graph
+# that has no such launch is gathered, and a graph that has one gathers a short list.
+@pytest.mark.parametrize("first,then", [(100, 4000), (4000, 100)])
+def test_batch_hosts_set_after_capture(first, then):
+    from paper_1812_00282_amd.batch import Batch
+
+    rng = np.random.default_rng(first)
+    pairs = [_pair(Config(c, 8, 60, 1024, seed_a=c, seed_b=2)) for c in (20, 24)]
+    lists = [_hosts(rng, first), _hosts(rng, 300)]
+    b = Batch([g for g, _ in pairs], [20_000] * 2, lists)
+
+    def slices(step):
+        sl = [_packets(rng, 20_000, h[:50]) for h in lists]
+        b.load(sl)
+        step()
+        b.synchronize()
+        for (_, ref), p in zip(pairs, sl):
+            ref.ingest(p)
+            ref.close_slice()
+
+    slices(b.slice)
+    b.capture()
+    slices(b.replay)
+    lists[0] = _hosts(rng, then)
+    h = torch.from_numpy(lists[0].view(np.int32)).cuda()
+    est = torch.full((then,), float("nan"), device="cuda")
+    live = torch.full((then,), -1, dtype=torch.int32, device="cuda")
+    assert _lib.lib().vate_batch_set_io(b._h, 0, b.pairs[0].data_ptr(), b.pairs[0].shape[0], h.data_ptr(), then, 60,
+                                        est.data_ptr(), live.data_ptr()) == _lib.VATE_OK
+    for _ in range(3):
+        slices(b.replay)
+        for (_, ref), hosts, lv, e in ((pairs[0], lists[0], live, est), (pairs[1], lists[1], b.live[1], b.est[1])):
+            r_est, r_live, _ = ref.estimate(hosts)
+            np.testing.assert_array_equal(lv.cpu().numpy().view(np.uint32), r_live)
+            assert np.all(np.abs(e.cpu().numpy().astype(np.float64) - r_est) <= _tol(r_est, 1024))
