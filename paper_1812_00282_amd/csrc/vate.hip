@@ -321,7 +321,9 @@ constexpr bool kUsesSeen = W == 0 || W == 4;
 // 2^15), so that most swaps would fail, but not so many for each counter that
 // most find it set.  Then counters are put without a look at them (2^16 nibbles,
 // k = 2, a slice of 260,000 packets 87 us by swaps and 61 so, 1M 147 and 113, 4M
-// 150 and 327; 2^16 3-bit ATs 260,000 78 and 47).
+// 150 and 327; 2^16 3-bit ATs 260,000 78 and 47).  Beyond 2^15 words
+// the few hosts that send most decide: 2^19 nibbles, 1M packets of evenly spread
+// hosts 139 us by swaps and 114 without a look, of Zipf(1.3) hosts 97 and 136.
 __host__ __device__ __forceinline__ bool crowded_words(const Geo &G, uint64_t n)
 {
     const uint64_t words = G.N * G.wb / 32u;
